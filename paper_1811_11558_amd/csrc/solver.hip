@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "contact.hpp"
 #include "kernels.hpp"
 #include "solver.hpp"
 
@@ -28,13 +29,6 @@ namespace fvim {
 namespace {
 constexpr int NT = 256;
 constexpr int RB = 1024;          // max reduction blocks
-constexpr int NSCAL = 32;
-
-// device scalar slots
-enum {
-  S_GBAR = 0, S_G, S_GOLD, S_BETA, S_RBAR, S_TAU, S_DELTA, S_SCALE, S_ERR, S_NIOL, S_SUMP, S_CNT, S_W, S_DA,
-  S_DOT0, S_DOT1, S_DOT2, S_KKT, S_TAU0
-};
 
 // ---------------------------------------------------------------- reductions
 // Block partial sums of NS quantities; block b writes part[k * RB + b].
@@ -121,107 +115,15 @@ int nblocks(size_t n) {
 }
 
 // ------------------------------------------------------------ PK kernels
-// g = u - h; sums over the contact set of g and of 1
-__global__ __launch_bounds__(NT) void k_pk_gap(const double* __restrict__ u, const double* __restrict__ h,
-                                              const double* __restrict__ p, double* __restrict__ g, size_t n,
-                                              double* part) {
-  double v[2] = {0.0, 0.0};
-  for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < n; i += (size_t)gridDim.x * NT) {
-    double gi = u[i] - h[i];
-    g[i] = gi;
-    if (p[i] > 0.0) {
-      v[0] += gi;
-      v[1] += 1.0;
-    }
-  }
-  block_sums<2>(v, part);
-}
-
-// g -= gbar; sum over the contact set of g^2
-__global__ __launch_bounds__(NT) void k_pk_grad(const double* __restrict__ p, double* __restrict__ g, size_t n,
-                                               const double* __restrict__ sc, double* part) {
-  const double gbar = sc[S_GBAR];
-  double v[1] = {0.0};
-  for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < n; i += (size_t)gridDim.x * NT) {
-    double gi = g[i] - gbar;
-    g[i] = gi;
-    if (p[i] > 0.0) v[0] += gi * gi;
-  }
-  block_sums<1>(v, part);
-}
-
-// t = g + beta t on the contact set, 0 elsewhere
-__global__ __launch_bounds__(NT) void k_pk_dir(const double* __restrict__ p, const double* __restrict__ g,
-                                              double* __restrict__ t, size_t n, const double* __restrict__ sc) {
-  const double beta = sc[S_BETA];
-  // beta = 0 (first iteration, restart) must not read the previous
-  // direction: 0 * t would carry a NaN through
+// (the iteration itself is in contact.hip)
+// Initial pressure: the warm start p renormalised to the load (sc[S_DOT0] =
+// sum p), or uniform when it is all zero.
+__global__ __launch_bounds__(NT) void k_pk_start(double* __restrict__ p, size_t n, const double* __restrict__ sc) {
+  const double sp = sc[S_DOT0], W = sc[S_W], dA = sc[S_DA];
+  const bool warm = sp > 0.0 && isfinite(sp);
+  const double f = warm ? W / (dA * sp) : W / ((double)n * dA);
   for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < n; i += (size_t)gridDim.x * NT)
-    t[i] = (p[i] > 0.0) ? g[i] + (beta != 0.0 ? beta * t[i] : 0.0) : 0.0;
-}
-
-// sums over the contact set of r and 1
-__global__ __launch_bounds__(NT) void k_pk_rmean(const double* __restrict__ p, const double* __restrict__ r,
-                                                size_t n, double* part) {
-  double v[2] = {0.0, 0.0};
-  for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < n; i += (size_t)gridDim.x * NT)
-    if (p[i] > 0.0) {
-      v[0] += r[i];
-      v[1] += 1.0;
-    }
-  block_sums<2>(v, part);
-}
-
-// sums over the contact set of g t and (r - rbar) t
-__global__ __launch_bounds__(NT) void k_pk_tau(const double* __restrict__ p, const double* __restrict__ g,
-                                              const double* __restrict__ r, const double* __restrict__ t,
-                                              size_t n, const double* __restrict__ sc, double* part) {
-  const double rbar = sc[S_RBAR];
-  double v[2] = {0.0, 0.0};
-  for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < n; i += (size_t)gridDim.x * NT)
-    if (p[i] > 0.0) {
-      v[0] += g[i] * t[i];
-      v[1] += (r[i] - rbar) * t[i];
-    }
-  block_sums<2>(v, part);
-}
-
-// step, projection onto p >= 0, re-admission of the overlap set (points of
-// negative gap enter with a pressure proportional to the overlap; when the
-// conjugate-gradient step vanishes -- the gap already uniform on the contact
-// set, e.g. a set of one point -- with the step of a point load, 1 / M_ii)
-__global__ __launch_bounds__(NT) void k_pk_update(double* __restrict__ p, double* __restrict__ pold,
-                                                 const double* __restrict__ g, const double* __restrict__ t,
-                                                 size_t n, const double* __restrict__ sc, double* part) {
-  const double tau = sc[S_TAU];
-  const double tre = tau != 0.0 ? tau : sc[S_TAU0];
-  double v[2] = {0.0, 0.0};
-  for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < n; i += (size_t)gridDim.x * NT) {
-    double po = p[i];
-    pold[i] = po;
-    double pn = po - tau * t[i];
-    if (pn < 0.0) pn = 0.0;
-    if (pn == 0.0 && g[i] < 0.0) {
-      pn = -tre * g[i];
-      v[1] += 1.0;
-    }
-    p[i] = pn;
-    v[0] += pn;
-  }
-  block_sums<2>(v, part);
-}
-
-// p *= scale; sum |p - p_old|
-__global__ __launch_bounds__(NT) void k_pk_scale(double* __restrict__ p, const double* __restrict__ pold, size_t n,
-                                                const double* __restrict__ sc, double* part) {
-  const double s = sc[S_SCALE];
-  double v[1] = {0.0};
-  for (size_t i = (size_t)blockIdx.x * NT + threadIdx.x; i < n; i += (size_t)gridDim.x * NT) {
-    double pn = p[i] * s;
-    p[i] = pn;
-    v[0] += fabs(pn - pold[i]);
-  }
-  block_sums<1>(v, part);
+    p[i] = warm ? p[i] * f : f;
 }
 
 // KKT certificate of a contact solution: with g the gap (u3 - h minus its
@@ -239,52 +141,15 @@ __global__ __launch_bounds__(NT) void k_pk_kkt(const double* __restrict__ p, con
   block_max<3>(v, part);
 }
 
-// One-block finishing steps of the PK iteration: turn partial sums into the
-// scalars the next kernel needs.
-// Final reductions into the device scalars; the slots the host reads after
-// stages 5 and 6 are also written to mirror (mapped host memory), so reading
-// them needs no copy.
-__global__ __launch_bounds__(NT) void k_pk_final(int stage, const double* part, int nb, double* sc,
-                                                double* mirror) {
-  if (stage == 0) {            // mean gap on the contact set
-    double a = final_sum(part, 0, nb), c = final_sum(part, 1, nb);
-    if (threadIdx.x == 0) {
-      sc[S_GBAR] = c > 0.0 ? a / c : 0.0;
-      sc[S_CNT] = c;
-    }
-  } else if (stage == 1) {     // CG coefficient
-    double G = final_sum(part, 0, nb);
-    if (threadIdx.x == 0) {
-      double gold = sc[S_GOLD];
-      sc[S_BETA] = (gold > 0.0) ? sc[S_DELTA] * G / gold : 0.0;
-      sc[S_G] = G;
-      sc[S_GOLD] = G;
-    }
-  } else if (stage == 2) {     // mean of M t on the contact set
-    double a = final_sum(part, 0, nb), c = final_sum(part, 1, nb);
-    if (threadIdx.x == 0) sc[S_RBAR] = c > 0.0 ? a / c : 0.0;
-  } else if (stage == 3) {     // step length
-    double a = final_sum(part, 0, nb), b = final_sum(part, 1, nb);
-    if (threadIdx.x == 0) sc[S_TAU] = (b != 0.0) ? a / b : 0.0;
-  } else if (stage == 4) {     // load renormalisation and restart flag
-    double sp = final_sum(part, 0, nb), nol = final_sum(part, 1, nb);
-    if (threadIdx.x == 0) {
-      sc[S_SUMP] = sp;
-      sc[S_SCALE] = sp > 0.0 ? sc[S_W] / (sc[S_DA] * sp) : 1.0;
-      sc[S_NIOL] = nol;
-      sc[S_DELTA] = nol > 0.0 ? 0.0 : 1.0;
-    }
-  } else if (stage == 5) {     // convergence measure dA sum |dp| / W
-    double d = final_sum(part, 0, nb);
-    if (threadIdx.x == 0) {
-      const double err = sc[S_DA] * d / sc[S_W];
-      sc[S_ERR] = err;
-      mirror[S_ERR] = err;
-    }
-  } else if (stage == 7) {     // KKT certificate max(on, off) / max |h|
+// One-block totals into the device scalars.  KKT: the certificate
+// max(on, off) / max |h|; else the sums of up to three quantities, also
+// written to mirror (mapped host memory), so reading them needs no copy.
+template <bool KKT>
+__global__ __launch_bounds__(NT) void k_pk_final(const double* part, int nb, double* sc, double* mirror) {
+  if (KKT) {
     double on = final_max(part, 0, nb), off = final_max(part, 1, nb), hm = final_max(part, 2, nb);
     if (threadIdx.x == 0) sc[S_KKT] = fmax(on, off) / (hm > 0.0 ? hm : 1e-300);
-  } else if (stage == 6) {     // generic: sums of up to three quantities
+  } else {
     double a = final_sum(part, 0, nb), b = final_sum(part, 1, nb), c = final_sum(part, 2, nb);
     if (threadIdx.x == 0) {
       sc[S_DOT0] = mirror[S_DOT0] = a;
@@ -292,21 +157,6 @@ __global__ __launch_bounds__(NT) void k_pk_final(int stage, const double* part, 
       sc[S_DOT2] = mirror[S_DOT2] = c;
     }
   }
-}
-
-// compliance multiplier per mode, mode-major [kx][ky]: 2 / (E* |q|) / (nx ny), 0 at k = 0
-__global__ __launch_bounds__(NT) void k_compliance(cpx<double>* __restrict__ s, int nx, int ny, double lx,
-                                                  double ly, double fac) {
-  const int kxh = nx / 2 + 1;
-  const int m = blockIdx.x * NT + threadIdx.x;
-  if (m >= kxh * ny) return;
-  const int kx = m / ny, ky = m - kx * ny;
-  const int k2 = (ky * 2 <= ny) ? ky : ky - ny;
-  const double twopi = 6.283185307179586476925286766559;
-  const double q1 = twopi * kx / lx, q2 = twopi * k2 / ly;
-  const double q = sqrt(q1 * q1 + q2 * q2);
-  const double c = (m == 0) ? 0.0 : fac / q;
-  s[m] = mk(s[m].x * c, s[m].y * c);
 }
 
 __global__ __launch_bounds__(NT) void k_fill(double* x, size_t n, double v) {
@@ -605,10 +455,10 @@ __global__ __launch_bounds__(NT) void k_aa_step(double* __restrict__ x, const do
 struct SolverWork {
   size_t ns = 0, V = 0;
   int lp = 0;                   // log2(ns)
-  double* surf = nullptr;       // 15 surface arrays
-  void* specA = nullptr;        // complex kxh*ny
-  void* specB = nullptr;
+  double* surf = nullptr;       // SURF surface arrays
+  void* spec = nullptr;         // complex kxh*ny
   double* part = nullptr;       // 3 * RB partial sums
+  double* pkpart = nullptr;     // block sums of the contact iteration
   double* sc = nullptr;         // device scalars
   double* hsc = nullptr;        // pinned host copy
   double* hmap = nullptr;       // mapped host memory written by k_pk_final (host view)
@@ -618,10 +468,9 @@ struct SolverWork {
   double* rpart = nullptr;      // partial-sum pairs of the fused residual evaluation
   int rpart_count = 0;
   int* layers = nullptr;        // [nz] plastic-layer flags of the trial point, zact, zwrite
-  // one contact iteration captured as a HIP graph, replayed on a private
-  // stream fenced by events against the context stream
+  // the contact iterations between two convergence checks captured as a HIP
+  // graph (on a private stream), replayed on the context stream
   hipStream_t cap = nullptr;
-  hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipGraph_t pk_graph = nullptr;
   hipGraphExec_t pk_exec = nullptr;
   const double* g_h = nullptr;
@@ -668,22 +517,14 @@ struct SolverWork {
 };
 
 constexpr int CAP_TRIES = 4;
+constexpr int SURF = 13;         // surface arrays: contact 3, Algorithm 1 4 + two tractions
 
-// The private capture stream and the events that fence it against the
-// context stream.
+// The private capture stream.
 static int cap_ensure(SolverWork* w) {
   std::lock_guard<std::recursive_mutex> lk(device_lock());
   if (!w->cap && hipStreamCreateWithFlags(&w->cap, hipStreamNonBlocking) != hipSuccess) {
     w->cap = nullptr;
     return fail(FVIM_EHIP, "graph stream");
-  }
-  if (!w->ev_in && hipEventCreateWithFlags(&w->ev_in, hipEventDisableTiming) != hipSuccess) {
-    w->ev_in = nullptr;
-    return fail(FVIM_EHIP, "graph event");
-  }
-  if (!w->ev_out && hipEventCreateWithFlags(&w->ev_out, hipEventDisableTiming) != hipSuccess) {
-    w->ev_out = nullptr;
-    return fail(FVIM_EHIP, "graph event");
   }
   return FVIM_OK;
 }
@@ -708,9 +549,9 @@ static int sw_ensure(fvim_ctx* c) {
   while (((size_t)1 << w->lp) < w->ns) ++w->lp;
   w->V = w->ns * c->grid.nz;
   const size_t nm = (size_t)(c->grid.nx / 2 + 1) * c->grid.ny;
-  bool ok = hipMalloc((void**)&w->surf, sizeof(double) * w->ns * 15) == hipSuccess &&
-            hipMalloc(&w->specA, sizeof(cpx<double>) * nm) == hipSuccess &&
-            hipMalloc(&w->specB, sizeof(cpx<double>) * nm) == hipSuccess &&
+  bool ok = hipMalloc((void**)&w->surf, sizeof(double) * w->ns * SURF) == hipSuccess &&
+            hipMalloc(&w->spec, sizeof(cpx<double>) * nm) == hipSuccess &&
+            hipMalloc((void**)&w->pkpart, sizeof(double) * pk_part_count(c->grid.nx, c->grid.ny)) == hipSuccess &&
             hipMalloc((void**)&w->part, sizeof(double) * 3 * RB) == hipSuccess &&
             hipMalloc((void**)&w->sc, sizeof(double) * NSCAL) == hipSuccess &&
             hipHostMalloc((void**)&w->hsc, sizeof(double) * NSCAL, hipHostMallocDefault) == hipSuccess &&
@@ -734,8 +575,8 @@ void solver_release(fvim_ctx* c) {
   if (!w) return;
   std::lock_guard<std::recursive_mutex> lk(device_lock());
   if (w->surf) hipFree(w->surf);
-  if (w->specA) hipFree(w->specA);
-  if (w->specB) hipFree(w->specB);
+  if (w->spec) hipFree(w->spec);
+  if (w->pkpart) hipFree(w->pkpart);
   if (w->part) hipFree(w->part);
   if (w->sc) hipFree(w->sc);
   if (w->hsc) hipHostFree(w->hsc);
@@ -759,8 +600,6 @@ void solver_release(fvim_ctx* c) {
   }
   if (w->pk_exec) hipGraphExecDestroy(w->pk_exec);
   if (w->pk_graph) hipGraphDestroy(w->pk_graph);
-  if (w->ev_in) hipEventDestroy(w->ev_in);
-  if (w->ev_out) hipEventDestroy(w->ev_out);
   if (w->cap) hipStreamDestroy(w->cap);
   delete w;
   c->sw = nullptr;
@@ -769,11 +608,12 @@ void solver_release(fvim_ctx* c) {
 size_t solver_footprint(const fvim_grid* g, size_t V) {
   const size_t ns = (size_t)g->nx * g->ny;
   const size_t nm = (size_t)(g->nx / 2 + 1) * g->ny;
-  // surface arrays (15 + Anderson history 2 AA_MMAX + 3 + adhesion 5), volume work
-  // arrays (6 tensors + 1 scalar), residual partial sums, compliance
-  // spectra, reduction buffers
-  return sizeof(double) * (ns * (23 + 2 * AA_MMAX) + 37 * V + 2 * (size_t)operator_resid_parts(*g)) +
-         2 * sizeof(cpx<double>) * nm +
+  // surface arrays (SURF + Anderson history 2 AA_MMAX + 3 + adhesion 5), volume
+  // work arrays (6 tensors + 1 scalar), residual partial sums, block sums of
+  // the contact iteration, compliance spectrum, reduction buffers
+  return sizeof(double) * (ns * (SURF + 8 + 2 * AA_MMAX) + 37 * V + 2 * (size_t)operator_resid_parts(*g) +
+                           (size_t)pk_part_count(g->nx, g->ny)) +
+         sizeof(cpx<double>) * nm +
          sizeof(double) * aa_nsums(AA_MMAX) * (RB + 2) + 64 * 1024;
 }
 
@@ -794,72 +634,27 @@ static int read_scalars_on(fvim_ctx* c, hipStream_t st, int first, int n) {
 
 static int read_scalars(fvim_ctx* c, int first, int n) { return read_scalars_on(c, c->stream, first, n); }
 
-static int set_scalar(fvim_ctx* c, int slot, double v) {
-  SolverWork* w = c->sw;
-  w->hsc[slot] = v;
-  hipError_t e = hipMemcpyAsync(w->sc + slot, w->hsc + slot, sizeof(double), hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  if (e != hipSuccess) return fail_hip(e, "scalar upload");
-  return FVIM_OK;
-}
+static double contact_modulus(const fvim_ctx* c) { return c->mat.E / (1.0 - c->mat.nu * c->mat.nu); }
 
 // u = M[p] . e3 at z = 0 for a normal surface load p (one plane).
 static int compliance(fvim_ctx* c, const double* p, double* u, hipStream_t st) {
-  SolverWork* w = c->sw;
-  const int nx = c->grid.nx, ny = c->grid.ny, kxh = nx / 2 + 1;
-  const cpx<double>* twx = (const cpx<double>*)c->twx64;
-  const cpx<double>* twy = (const cpx<double>*)c->twy64;
-  cpx<double>* A = (cpx<double>*)w->specA;
-  cpx<double>* B = (cpx<double>*)w->specB;
-  hipError_t e;
-  if ((e = launch_x_r2c<double>(p, A, nx, ny, 1, twx, st)) != hipSuccess) return fail_hip(e, "compliance x");
-  if ((e = launch_y_fwd<double>(A, B, ny, kxh, 1, 1, twy, st)) != hipSuccess) return fail_hip(e, "compliance y");
-  const double estar = c->mat.E / (1.0 - c->mat.nu * c->mat.nu);
-  const double fac = 2.0 / estar / ((double)nx * ny);
-  const int nm = kxh * ny;
-  hipLaunchKernelGGL(k_compliance, dim3((nm + NT - 1) / NT), dim3(NT), 0, st, B, nx, ny, c->grid.lx, c->grid.ly,
-                     fac);
-  if ((e = launch_y_inv<double>(B, A, ny, kxh, 1, 1, twy, st)) != hipSuccess) return fail_hip(e, "compliance y^-1");
-  OutSegments seg;
-  seg.n = 1;
-  seg.first[0] = 0;
-  seg.ptr[0] = u;
-  if ((e = launch_x_c2r<double>(A, seg, nx, ny, 1, 1.0, twx, st)) != hipSuccess)
-    return fail_hip(e, "compliance x^-1");
-  return FVIM_OK;
+  hipError_t e = launch_compliance(c->grid.nx, c->grid.ny, c->grid.lx, c->grid.ly, contact_modulus(c),
+                                   (const cpx<double>*)c->twx64, (const cpx<double>*)c->twy64, p, u,
+                                   (cpx<double>*)c->sw->spec, st);
+  return e == hipSuccess ? FVIM_OK : fail_hip(e, "compliance");
 }
 
-// One Polonsky-Keer iteration as a fixed sequence of launches on st (no host
-// dependency: every scalar lives in device memory), so it can be captured.
-static int pk_iteration(fvim_ctx* c, hipStream_t st, const double* h, double* p) {
-  SolverWork* w = c->sw;
-  const size_t n = w->ns;
-  const int nb = nblocks(n);
-  const dim3 G(nb), Bk(NT);
-  double* u = w->surf;
-  double* g = w->surf + n;
-  double* t = w->surf + 2 * n;
-  double* r = w->surf + 3 * n;
-  double* pold = w->surf + 4 * n;
-  int rc;
-  if ((rc = compliance(c, p, u, st))) return rc;
-  hipLaunchKernelGGL(k_pk_gap, G, Bk, 0, st, u, h, p, g, n, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 0, w->part, nb, w->sc, w->dmap);
-  hipLaunchKernelGGL(k_pk_grad, G, Bk, 0, st, p, g, n, w->sc, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 1, w->part, nb, w->sc, w->dmap);
-  hipLaunchKernelGGL(k_pk_dir, G, Bk, 0, st, p, g, t, n, w->sc);
-  if ((rc = compliance(c, t, r, st))) return rc;
-  hipLaunchKernelGGL(k_pk_rmean, G, Bk, 0, st, p, r, n, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 2, w->part, nb, w->sc, w->dmap);
-  hipLaunchKernelGGL(k_pk_tau, G, Bk, 0, st, p, g, r, t, n, w->sc, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 3, w->part, nb, w->sc, w->dmap);
-  hipLaunchKernelGGL(k_pk_update, G, Bk, 0, st, p, pold, g, t, n, w->sc, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 4, w->part, nb, w->sc, w->dmap);
-  hipLaunchKernelGGL(k_pk_scale, G, Bk, 0, st, p, pold, n, w->sc, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 5, w->part, nb, w->sc, w->dmap);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail_hip(e, "contact iteration");
-  return FVIM_OK;
+// Contact iterations between two reads of the convergence measure.
+static int pk_check_period(size_t n) { return n <= 4096 ? 1 : 4; }
+
+// The iterations up to the next check and their convergence measure, as a
+// fixed sequence of launches on st (no host dependency: every scalar lives in
+// device memory), so it can be captured.
+static int pk_iterations(const PkBufs& b, int count, hipStream_t st) {
+  hipError_t e = hipSuccess;
+  for (int k = 0; k < count && e == hipSuccess; ++k) e = launch_pk_iteration(b, st);
+  if (e == hipSuccess) e = launch_pk_err(b, st);
+  return e == hipSuccess ? FVIM_OK : fail_hip(e, "contact iteration");
 }
 
 // Polonsky-Keer on the context stream.  p: in warm start (all zero ->
@@ -873,15 +668,17 @@ int pk_solve(fvim_ctx* c, const double* h, double W, double tol, int max_iter, d
   const size_t n = w->ns;
   const int nb = nblocks(n);
   const dim3 G(nb), Bk(NT);
-  double* u = w->surf;
-  double* g = w->surf + n;
-  double* t = w->surf + 2 * n;
+  double* g = w->surf;
+  double* t = w->surf + n;
+  const PkBufs pk = {c->grid.nx, c->grid.ny, c->grid.lx, c->grid.ly, contact_modulus(c), (const cpx<double>*)c->twx64,
+                     (const cpx<double>*)c->twy64, h, p, w->surf + 2 * n, g, t, (cpx<double>*)w->spec, w->pkpart,
+                     w->sc, w->dmap};
   const double dA = c->grid.lx * c->grid.ly / (double)n;
   // scalars: load, area, restart state, the point-load step 1 / M_ii
   if (!(w->mdiag > 0.0)) {
     // M_ii: the mean over the nx x ny modes of 2 / (E* |q|), mode 0 dropped
     const int nx = c->grid.nx, ny = c->grid.ny;
-    const double estar = c->mat.E / (1.0 - c->mat.nu * c->mat.nu);
+    const double estar = contact_modulus(c);
     const double twopi = 6.283185307179586476925286766559;
     double sum = 0.0;
     for (int ky = 0; ky < ny; ++ky)
@@ -904,72 +701,52 @@ int pk_solve(fvim_ctx* c, const double* h, double W, double tol, int max_iter, d
   hipLaunchKernelGGL(k_fill, G, Bk, 0, st, t, n, 0.0);
   // initial pressure: warm start renormalised to W, or uniform
   hipLaunchKernelGGL(k_sum_abs, G, Bk, 0, st, p, n, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 6, w->part, nb, w->sc, w->dmap);
-  if ((rc = read_scalars(c, S_DOT0, 2))) return rc;
-  const double sp = w->hsc[S_DOT0];
-  if (!(sp > 0.0) || !std::isfinite(sp)) {
-    hipLaunchKernelGGL(k_fill, G, Bk, 0, st, p, n, W / (n * dA));
-  } else {
-    if ((rc = set_scalar(c, S_SCALE, W / (dA * sp)))) return rc;
-    hipLaunchKernelGGL(k_pk_scale, G, Bk, 0, st, p, p, n, w->sc, w->part);
-  }
+  hipLaunchKernelGGL(k_pk_final<false>, dim3(1), Bk, 0, st, w->part, nb, w->sc, w->dmap);
+  hipLaunchKernelGGL(k_pk_start, G, Bk, 0, st, p, n, w->sc);
+  if ((e = launch_pk_first(pk, st)) != hipSuccess) return fail_hip(e, "contact start");
   int it = 0;
   double err = INFINITY;
-  const int check = n <= 4096 ? 1 : 4;        // host convergence check period
-  hipStream_t run = st;
+  const int check = pk_check_period(n);
   bool graph = c->use_graphs && w->cap_fail < CAP_TRIES;
-  if (graph) {
+  if (graph && (!w->pk_exec || w->g_h != h || w->g_p != p)) {
     if ((rc = cap_ensure(w))) return rc;
-    if ((e = hipEventRecord(w->ev_in, st)) != hipSuccess) return fail_hip(e, "event");
-    if ((e = hipStreamWaitEvent(w->cap, w->ev_in, 0)) != hipSuccess) return fail_hip(e, "event wait");
-    run = w->cap;
-    if (!w->pk_exec || w->g_h != h || w->g_p != p) {
-      if (w->pk_exec) { hipGraphExecDestroy(w->pk_exec); w->pk_exec = nullptr; }
-      if (w->pk_graph) { hipGraphDestroy(w->pk_graph); w->pk_graph = nullptr; }
-      std::lock_guard<std::recursive_mutex> lk(device_lock());
-      if ((e = hipStreamBeginCapture(run, hipStreamCaptureModeThreadLocal)) != hipSuccess)
-        return fail_hip(e, "graph capture");
-      int rc2 = pk_iteration(c, run, h, p);
-      e = hipStreamEndCapture(run, &w->pk_graph);
-      if (rc2 || e != hipSuccess || !w->pk_graph ||
-          hipGraphInstantiate(&w->pk_exec, w->pk_graph, nullptr, nullptr, 0) != hipSuccess) {
-        // the capture was invalidated (for instance by a device-wide
-        // synchronisation in another thread): nothing it recorded ran, so
-        // this solve iterates with direct launches
-        capture_failed(w, &w->pk_graph, &w->pk_exec);
-        graph = false;
-      } else {
-        w->g_h = h;
-        w->g_p = p;
-      }
-    }
-  }
-  for (it = 1; it <= max_iter; ++it) {
-    if (graph) {
-      if ((e = hipGraphLaunch(w->pk_exec, run)) != hipSuccess) return fail_hip(e, "graph launch");
+    if (w->pk_exec) { hipGraphExecDestroy(w->pk_exec); w->pk_exec = nullptr; }
+    if (w->pk_graph) { hipGraphDestroy(w->pk_graph); w->pk_graph = nullptr; }
+    std::lock_guard<std::recursive_mutex> lk(device_lock());
+    if ((e = hipStreamBeginCapture(w->cap, hipStreamCaptureModeThreadLocal)) != hipSuccess)
+      return fail_hip(e, "graph capture");
+    int rc2 = pk_iterations(pk, check, w->cap);
+    e = hipStreamEndCapture(w->cap, &w->pk_graph);
+    if (rc2 || e != hipSuccess || !w->pk_graph ||
+        hipGraphInstantiate(&w->pk_exec, w->pk_graph, nullptr, nullptr, 0) != hipSuccess) {
+      // the capture was invalidated (for instance by a device-wide
+      // synchronisation in another thread): nothing it recorded ran, so
+      // this solve iterates with direct launches
+      capture_failed(w, &w->pk_graph, &w->pk_exec);
+      graph = false;
     } else {
-      if ((rc = pk_iteration(c, run, h, p))) return rc;
-    }
-    if (it % check == 0 || it == max_iter) {
-      if ((rc = read_scalars_on(c, run, S_ERR, 1))) return rc;
-      err = w->hsc[S_ERR];
-      if (!std::isfinite(err)) return fail(FVIM_EINVAL, "contact_solve: non-finite iterate (check h and W)");
-      if (err < tol) break;
+      w->g_h = h;
+      w->g_p = p;
     }
   }
-  if (run != st) {
-    if ((e = hipEventRecord(w->ev_out, run)) != hipSuccess) return fail_hip(e, "event");
-    if ((e = hipStreamWaitEvent(st, w->ev_out, 0)) != hipSuccess) return fail_hip(e, "event wait");
+  while (it < max_iter) {
+    const int count = std::min(check, max_iter - it);
+    if (graph && count == check) {
+      if ((e = hipGraphLaunch(w->pk_exec, st)) != hipSuccess) return fail_hip(e, "graph launch");
+    } else {
+      if ((rc = pk_iterations(pk, count, st))) return rc;
+    }
+    it += count;
+    if ((rc = read_scalars(c, S_ERR, 1))) return rc;
+    err = w->hsc[S_ERR];
+    if (!std::isfinite(err)) return fail(FVIM_EINVAL, "contact_solve: non-finite iterate (check h and W)");
+    if (err < tol) break;
   }
   const bool conv = err < tol;
-  if (it > max_iter) it = max_iter;
-  // final gap and certificate
-  if ((rc = compliance(c, p, u, st))) return rc;
-  hipLaunchKernelGGL(k_pk_gap, G, Bk, 0, st, u, h, p, g, n, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 0, w->part, nb, w->sc, w->dmap);
-  hipLaunchKernelGGL(k_pk_grad, G, Bk, 0, st, p, g, n, w->sc, w->part);
+  // final gap (g = M[p] - h is that of the last iterate) and certificate
+  if ((e = launch_pk_gap_mean(pk, st)) != hipSuccess) return fail_hip(e, "contact gap");
   hipLaunchKernelGGL(k_pk_kkt, G, Bk, 0, st, p, g, h, n, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), Bk, 0, st, 7, w->part, nb, w->sc, w->dmap);
+  hipLaunchKernelGGL(k_pk_final<true>, dim3(1), Bk, 0, st, w->part, nb, w->sc, w->dmap);
   if (gap) {
     e = hipMemcpyAsync(gap, g, sizeof(double) * n, hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) return fail_hip(e, "gap copy");
@@ -1156,7 +933,7 @@ static int wdots(fvim_ctx* c, const double* a1, const double* a0, const double* 
   const int nb = nblocks(n6);
   hipLaunchKernelGGL(k_wdots, dim3(nb), dim3(NT), 0, c->stream, a1, a0, b1, b0, w->lp, (unsigned)c->grid.nz, c->wz,
                      n6, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), dim3(NT), 0, c->stream, 6, w->part, nb, w->sc, w->dmap);
+  hipLaunchKernelGGL(k_pk_final<false>, dim3(1), dim3(NT), 0, c->stream, w->part, nb, w->sc, w->dmap);
   int rc = read_scalars(c, S_DOT0, 3);
   if (rc) return rc;
   const double sc = inner_scale(c);
@@ -1562,7 +1339,7 @@ static int surf_norms(fvim_ctx* c, const double* a, const double* b, double* dno
   SolverWork* w = c->sw;
   const int nb = nblocks(w->ns);
   hipLaunchKernelGGL(k_sq2, dim3(nb), dim3(NT), 0, c->stream, a, b, w->ns, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), dim3(NT), 0, c->stream, 6, w->part, nb, w->sc, w->dmap);
+  hipLaunchKernelGGL(k_pk_final<false>, dim3(1), dim3(NT), 0, c->stream, w->part, nb, w->sc, w->dmap);
   int rc = read_scalars(c, S_DOT0, 2);
   if (rc) return rc;
   *dnorm = std::sqrt(w->hsc[S_DOT0]);
@@ -1680,7 +1457,7 @@ static int sdot(fvim_ctx* c, const double* a, const double* b, double out[3]) {
   SolverWork* w = c->sw;
   const int nb = nblocks(w->ns);
   hipLaunchKernelGGL(k_sdot3, dim3(nb), dim3(NT), 0, c->stream, a, b, w->ns, w->part);
-  hipLaunchKernelGGL(k_pk_final, dim3(1), dim3(NT), 0, c->stream, 6, w->part, nb, w->sc, w->dmap);
+  hipLaunchKernelGGL(k_pk_final<false>, dim3(1), dim3(NT), 0, c->stream, w->part, nb, w->sc, w->dmap);
   int rc = read_scalars(c, S_DOT0, 3);
   if (rc) return rc;
   out[0] = w->hsc[S_DOT0];
@@ -2078,13 +1855,13 @@ int elastoplastic_solve(fvim_ctx* c, const double* h, const double* W_steps, int
   hipStream_t st = c->stream;
   const size_t n = w->ns, V = w->V;
   // surface work arrays (after the 5 used by the contact solver)
-  double* H0 = w->surf + 5 * n;
-  double* H = w->surf + 6 * n;
-  double* dUp = w->surf + 7 * n;
-  double* dU = w->surf + 8 * n;
-  double* T = w->surf + 9 * n;        // 3 planes: 9, 10, 11
+  double* H0 = w->surf + 3 * n;
+  double* H = w->surf + 4 * n;
+  double* dUp = w->surf + 5 * n;
+  double* dU = w->surf + 6 * n;
+  double* T = w->surf + 7 * n;        // 3 planes: 7, 8, 9
   double* pcur = T + 2 * n;           // normal component of T
-  double* dT = w->surf + 12 * n;      // 3 planes: 12, 13, 14
+  double* dT = w->surf + 10 * n;      // 3 planes: 10, 11, 12
   const int aam = o->literal_alg1 ? 0 : o->anderson_m;
   if (aam > 0 && (rc = aa_ensure(c))) return rc;
   if (o->solver == 2 && (rc = kry_ensure(c, krylov_dim(o)))) return rc;

@@ -60,6 +60,27 @@ def test_contact_matches_oracle(n, W, seed):
     assert abs(info["kkt_residual"] - kkt) <= 1e-12 * max(kkt, 1e-300), (info["kkt_residual"], kkt)
 
 
+@pytest.mark.parametrize("nx,ny", [(4, 4), (8, 4), (4, 32), (128, 8), (16, 1024), (4, 4096), (2048, 8), (4096, 4)])
+def test_contact_matches_oracle_at_the_transform_lengths(nx, ny):
+    """The contact iteration's own surface transforms at their shortest and
+    longest lengths (several sequences per wave, one per block of up to 1024
+    threads, blocks only partly filled), even and odd powers of two, on
+    non-square cells: the minimiser and its gap (bound of the square cases)."""
+    ly = max(ny / nx, 1 / 64)
+    g = grid_dict(nx, ny, 2, 1.0, ly)
+    h = rough_surface(nx, ny, hurst=0.8, k_roll=1, k_cut=max(1, max(nx, ny) // 16), rms_slope=0.1, seed=nx + ny,
+                      ly=ly)
+    _say("contact", nx, ny)
+    ref, rgap, rinfo = oc.contact_solve(h, 0.02 * ly, g, E, NU, tol=1e-14, max_iter=20000)
+    ctx = _ctx(g)
+    p, gap, info = ctx.contact_solve(torch.from_numpy(h).cuda(), 0.02 * ly, tol=1e-14, max_iter=20000, want_gap=True)
+    torch.cuda.synchronize()
+    err, gerr = _rel(p.cpu().numpy(), ref), _rel(gap.cpu().numpy(), rgap)
+    _say("iters gpu/oracle", info["iters"], rinfo["iters"], "rel err p", err, "gap", gerr)
+    assert err < 1e-11 and gerr < 1e-11
+    ctx.close()
+
+
 def test_contact_matches_oracle_rough_1024():
     """The rough-surface workload's contact solve at its full size: 1024^2,
     Hurst 0.8, PSD plateau for 1 <= |k| < 4, cut-off |k| = 256, rms slope
