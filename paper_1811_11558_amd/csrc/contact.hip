@@ -35,10 +35,6 @@ constexpr int GT = 256;                 // threads of the pointwise kernels
 constexpr int GB = 256;                 // their most blocks
 
 // blocks of the row kernels of an nx x ny surface (pairs of rows)
-template <int LOGN>
-int row_blocks(int ny) {
-  return (ny / 2 + Surf<LOGN>::SEQ - 1) / Surf<LOGN>::SEQ;
-}
 int pk_row_blocks(int nx, int ny) {
   const int m = nx / 4, nth = m < 64 ? 64 : m, seq = nth / m;
   return (ny / 2 + seq - 1) / seq;
@@ -474,28 +470,34 @@ hipError_t launch_columns(int nx, int ny, double lx, double ly, double estar, co
 
 int pk_part_count(int nx, int ny) { return PROWS * pk_ldp(nx, ny); }
 
-hipError_t launch_compliance(int nx, int ny, double lx, double ly, double estar, const cpx<double>* twx,
-                             const cpx<double>* twy, const double* in, double* out, cpx<double>* X, hipStream_t st) {
-#define CALL(L)                                                                                                  \
-  hipLaunchKernelGGL((k_rows_fwd<L>), dim3(row_blocks<L>(ny)), dim3(Surf<L>::NTH), 0, st, in, X, ny, twx)
-  FVIM_SURF_SWITCH(surf_log2(nx), CALL)
-#undef CALL
-  hipError_t e = launch_columns(nx, ny, lx, ly, estar, twy, X, nullptr, 0, 0, nullptr, st);
-  if (e != hipSuccess) return e;
-#define CALL(L)                                                                                                   \
-  hipLaunchKernelGGL((k_rows_inv<L>), dim3(row_blocks<L>(ny)), dim3(Surf<L>::NTH), 0, st, X, out, ny, twx)
+hipError_t launch_rows_fwd(int nx, int ny, const double* in, cpx<double>* X, const cpx<double>* twx, hipStream_t st) {
+#define CALL(L) \
+  hipLaunchKernelGGL((k_rows_fwd<L>), dim3(pk_row_blocks(nx, ny)), dim3(Surf<L>::NTH), 0, st, in, X, ny, twx)
   FVIM_SURF_SWITCH(surf_log2(nx), CALL)
 #undef CALL
   return hipGetLastError();
 }
 
+hipError_t launch_rows_inv(int nx, int ny, const cpx<double>* X, double* out, const cpx<double>* twx, hipStream_t st) {
+#define CALL(L) \
+  hipLaunchKernelGGL((k_rows_inv<L>), dim3(pk_row_blocks(nx, ny)), dim3(Surf<L>::NTH), 0, st, X, out, ny, twx)
+  FVIM_SURF_SWITCH(surf_log2(nx), CALL)
+#undef CALL
+  return hipGetLastError();
+}
+
+hipError_t launch_compliance(int nx, int ny, double lx, double ly, double estar, const cpx<double>* twx,
+                             const cpx<double>* twy, const double* in, double* out, cpx<double>* X, hipStream_t st) {
+  hipError_t e = launch_rows_fwd(nx, ny, in, X, twx, st);
+  if (e == hipSuccess) e = launch_columns(nx, ny, lx, ly, estar, twy, X, nullptr, 0, 0, nullptr, st);
+  return e == hipSuccess ? launch_rows_inv(nx, ny, X, out, twx, st) : e;
+}
+
 hipError_t launch_pk_first(const PkBufs& b, hipStream_t st) {
   const int ldp = pk_ldp(b.nx, b.ny), nbr = pk_row_blocks(b.nx, b.ny);
-#define CALL(L)                                                                                                     \
-  hipLaunchKernelGGL((k_rows_fwd<L>), dim3(nbr), dim3(Surf<L>::NTH), 0, st, (const double*)b.p, b.X, b.ny, b.twx)
-  FVIM_SURF_SWITCH(surf_log2(b.nx), CALL)
-#undef CALL
-  hipError_t e = launch_columns(b.nx, b.ny, b.lx, b.ly, b.estar, b.twy, b.X, nullptr, 0, 0, nullptr, st);
+  hipError_t e = launch_rows_fwd(b.nx, b.ny, b.p, b.X, b.twx, st);
+  if (e != hipSuccess) return e;
+  e = launch_columns(b.nx, b.ny, b.lx, b.ly, b.estar, b.twy, b.X, nullptr, 0, 0, nullptr, st);
   if (e != hipSuccess) return e;
 #define CALL(L)                                                                                               \
   hipLaunchKernelGGL((k_pk_gap<L, true>), dim3(nbr), dim3(Surf<L>::NTH), 0, st, b.X, b.h, b.p, b.pold, b.g, b.ny, \

@@ -29,6 +29,10 @@ struct PkBufs {
 // doubles of block sums an nx x ny problem needs
 int pk_part_count(int nx, int ny);
 
+// Row transforms of one surface plane to and from its row spectrum X[y][kx].
+hipError_t launch_rows_fwd(int nx, int ny, const double* in, cpx<double>* X, const cpx<double>* twx, hipStream_t st);
+hipError_t launch_rows_inv(int nx, int ny, const cpx<double>* X, double* out, const cpx<double>* twx, hipStream_t st);
+
 // out = M[in] . e3 at z = 0 of one surface plane (2 / (E* |q|) per mode, mode
 // 0 dropped); X as in PkBufs.
 hipError_t launch_compliance(int nx, int ny, double lx, double ly, double estar, const cpx<double>* twx,

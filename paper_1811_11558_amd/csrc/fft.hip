@@ -277,16 +277,6 @@ hipError_t launch_x_r2c(const InSegments& seg, cpx<T>* out, int nx, int ny, size
 }
 
 template <typename T>
-hipError_t launch_x_r2c(const double* in, cpx<T>* out, int nx, int ny, size_t nplanes, const cpx<T>* tw,
-                        hipStream_t st, double* bsum, bool stream_in) {
-  InSegments seg;
-  seg.n = 1;
-  seg.first[0] = seg.first[1] = 0;
-  seg.ptr[0] = seg.ptr[1] = in;
-  return launch_x_r2c<T>(seg, out, nx, ny, nplanes, tw, st, bsum, stream_in, LayerSkip{}, FftChoice{});
-}
-
-template <typename T>
 hipError_t launch_y_fwd(const cpx<T>* in, cpx<T>* out, int ny, int kxh, int NP, int ldp, const cpx<T>* tw,
                         hipStream_t st, bool stream_in, const LayerSkip& skip, FftChoice ch) {
   if (ldp < NP) return hipErrorInvalidValue;
@@ -436,8 +426,6 @@ int x_r2c_batch_blocks_per_plane(int nx, int ny) {
   template int x_r2c_batch_blocks_per_plane<T>(int, int);                                                       \
   template hipError_t launch_x_r2c<T>(const InSegments&, cpx<T>*, int, int, size_t, const cpx<T>*, hipStream_t, \
                                       double*, bool, const LayerSkip&, FftChoice);                              \
-  template hipError_t launch_x_r2c<T>(const double*, cpx<T>*, int, int, size_t, const cpx<T>*, hipStream_t,     \
-                                      double*, bool);                                                           \
   template hipError_t launch_y_fwd<T>(const cpx<T>*, cpx<T>*, int, int, int, int, const cpx<T>*, hipStream_t,   \
                                       bool, const LayerSkip&, FftChoice);                                       \
   template hipError_t launch_y_inv<T>(const cpx<T>*, cpx<T>*, int, int, int, int, const cpx<T>*, hipStream_t,   \

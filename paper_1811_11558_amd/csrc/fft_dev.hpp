@@ -466,7 +466,7 @@ __device__ __forceinline__ void x_c2r_body(cpx<T>* buf, double* red, int lb, con
       // row 2 pr + 1.  The operator's outputs are not read again by the
       // operator, so they are stored as streaming (non-temporal) writes,
       // which do not displace the spectrum buffers from the last-level
-      // cache; the contact solver's compliance, read at once by the next
+      // cache.
       // kernel, keeps ordinary stores.
       const int tot4 = hp * (N / 2);
       for (int i = threadIdx.x; i < tot4; i += NT) {

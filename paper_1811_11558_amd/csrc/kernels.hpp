@@ -48,9 +48,6 @@ hipError_t launch_x_r2c(const InSegments& seg, cpx<T>* out, int nx, int ny, size
                         hipStream_t st, double* bsum = nullptr, bool stream_in = false,
                         const LayerSkip& skip = LayerSkip{}, FftChoice ch = FftChoice{});
 template <typename T>
-hipError_t launch_x_r2c(const double* in, cpx<T>* out, int nx, int ny, size_t nplanes, const cpx<T>* tw,
-                        hipStream_t st, double* bsum = nullptr, bool stream_in = false);
-template <typename T>
 int x_r2c_blocks_per_plane(int nx, int ny, FftChoice ch = FftChoice{});
 // the most blocks per plane any choice gives (buffers sized for tuning)
 template <typename T>

@@ -58,6 +58,33 @@ def test_tangential_matches_oracle(nx, ny, lx, ly, mu, qdir):
     ctx.close()
 
 
+@pytest.mark.parametrize("nx,ny", [(4, 4), (8, 4), (4, 32), (128, 8), (16, 1024), (4, 4096), (2048, 8), (4096, 4)])
+def test_tangential_matches_oracle_at_the_transform_lengths(nx, ny):
+    """The iteration's two-plane surface transforms at their shortest and
+    longest lengths (several sequences per wave, blocks partly filled, up to
+    1024 threads per sequence; columns of 4096 transform their planes one
+    after the other), non-square cells.  Both sides stop at a change of 1e-13;
+    with a contraction of 1 - 1/sqrt(4096) per iteration each is within some
+    64 x 1e-13 of the minimiser in that measure: bound 1e-10."""
+    from paper_1811_11558_amd import Context
+    ly = max(ny / nx, 1 / 64)
+    g = grid_dict(nx, ny, 4, 1.0, ly, 0.25)
+    h = rough_surface(nx, ny, hurst=0.8, k_roll=1, k_cut=max(1, max(nx, ny) // 16), rms_slope=0.1, seed=nx + ny,
+                      ly=ly)
+    p = np.clip(h - np.quantile(h, 0.7), 0.0, None)
+    mu = 0.4
+    Q = np.array((0.3, -0.4)) * mu * ly * p.mean()
+    _say("tangential", nx, ny)
+    ref, rinfo = fr.tangential_solve(g, E, NU, p, Q, mu, tol=1e-13)
+    ctx = Context(g, E, NU)
+    q, info = ctx.tangential_solve(torch.from_numpy(p).cuda(), mu, Q, tol=1e-13)
+    torch.cuda.synchronize()
+    err = _rel(q.cpu().numpy(), ref)
+    _say("iters gpu/oracle", info["iters"], rinfo["iters"], "err", err)
+    assert err <= 1e-10
+    ctx.close()
+
+
 def test_tangential_cattaneo_mindlin_nu0():
     """Hertz pressure, Q = 0.5 mu P, nu = 0: the Cattaneo-Mindlin traction
     and stick radius within the discretisation error of 128^2 points."""
