@@ -147,7 +147,7 @@ int tune_depth(fvim_ctx* c, const cpx<T>* in, cpx<T>* out, const DepthParams& pr
   hipEvent_t a, b;
   if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) return fail(FVIM_EHIP, "events");
   float best = 1e30f;
-  int best_id = depth_default_config(prm.nz);
+  int best_id = depth_default_config<T>(prm.nz);
   for (int id = 0; id < depth_num_configs(); ++id) {
     if (!depth_config_valid(id, prm.nz)) continue;
     hipError_t e = launch_depth<T>(in, out, prm, id, st);
@@ -355,7 +355,6 @@ int op_layout(fvim_ctx* c, const double* eps_p, const double* traction, double* 
 // the twiddles, the node table and the Nyquist replica records.
 template <typename T>
 void op_bind(fvim_ctx* c, OpPlan<T>& P, void* bufA, void* bufB, double* k0buf, const void* mt, bool side) {
-  const size_t nmodes = (size_t)P.prm.kxh * P.prm.ny;
   if (P.k0x) {
     P.wsum = k0buf;                                // block sums of every input plane
     P.tsum = P.wsum + (size_t)P.prm.off_t * P.wbpp;
@@ -369,7 +368,7 @@ void op_bind(fvim_ctx* c, OpPlan<T>& P, void* bufA, void* bufB, double* k0buf, c
   P.B = (cpx<T>*)bufB;
   // with the side stream the Nyquist modes keep a launch of their own, which
   // can run beside the main one; otherwise their sign replicas join it
-  P.prm.rep_out = side ? nullptr : (void*)(P.A + nmodes * (size_t)P.prm.ld_out);
+  P.prm.rep_out = side ? nullptr : (void*)(P.A + (size_t)P.prm.kxh * P.prm.ny * (size_t)P.prm.ld_out);
 }
 
 // op_layout plus the workspace the context owns (grown on demand) and the
@@ -408,78 +407,78 @@ void op_refresh_sums(fvim_ctx* c, OpPlan<T>& P) {
 
 static int ilog2i(int n) { return 31 - __builtin_clz((unsigned)n); }
 
-// Tuning of the forward transforms on the live input: the row transform's
-// choices (its output then recomputed with the fastest), then the column
-// transform's on that output.
+// Launches of the transform stages: real fields -> A -> mode-major B; mode-major
+// A (the depth pass's output) -> B -> outputs.
 template <typename T>
-int tune_forward(fvim_ctx* c, OpPlan<T>& P) {
-  const int nx = c->grid.nx, ny = c->grid.ny, kxh = nx / 2 + 1;
+hipError_t run_x_fwd(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, FftChoice ch) {
+  return launch_x_r2c<T>(P.iseg, P.A, c->grid.nx, c->grid.ny, (size_t)P.np_in, P.twx, st, P.wsum, P.nt, P.skip, ch);
+}
+template <typename T>
+hipError_t run_y_fwd(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, FftChoice ch) {
+  return launch_y_fwd<T>(P.A, P.B, c->grid.ny, P.prm.kxh, P.np_in, P.prm.ld_in, P.twy, st, P.nt, P.skip, ch);
+}
+template <typename T>
+hipError_t run_y_inv(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, FftChoice ch) {
+  return launch_y_inv<T>(P.A, P.B, c->grid.ny, P.prm.kxh, P.np, P.prm.ld_out, P.twy, st, P.nt, ch);
+}
+template <typename T>
+hipError_t run_x_inv(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, FftChoice ch) {
+  return launch_x_c2r<T>(P.B, P.seg, c->grid.nx, c->grid.ny, (size_t)P.np, 1.0, P.twx, st, P.padd, P.ep, true, ch);
+}
+
+// Tuning on the live input: each transform's choices in turn on what the
+// stages before it leave with theirs, the depth layouts between.  The
+// application runs as a whole afterwards, so what the timed launches leave in
+// the buffers and outputs is written again.
+template <typename T>
+int tune_operator(fvim_ctx* c, OpPlan<T>& P) {
   hipStream_t st = c->stream;
-  int rc = time_choices(c, ilog2i(nx), [&](FftChoice ch) {
-    return launch_x_r2c<T>(P.iseg, P.A, nx, ny, (size_t)P.np_in, P.twx, st, P.wsum, P.nt, P.skip, ch);
-  }, &P.ch[0]);
+  const int lx = ilog2i(c->grid.nx), ly = ilog2i(c->grid.ny);
+  hipError_t e;
+  int rc = time_choices(c, lx, [&](FftChoice ch) { return run_x_fwd<T>(c, P, st, ch); }, &P.ch[0]);
   if (rc) return rc;
   op_refresh_sums<T>(c, P);
-  hipError_t e = launch_x_r2c<T>(P.iseg, P.A, nx, ny, (size_t)P.np_in, P.twx, st, P.wsum, P.nt, P.skip, P.ch[0]);
-  if (e != hipSuccess) return fail_hip(e, "x_r2c");
-  return time_choices(c, ilog2i(ny), [&](FftChoice ch) {
-    return launch_y_fwd<T>(P.A, P.B, ny, kxh, P.np_in, P.prm.ld_in, P.twy, st, P.nt, P.skip, ch);
-  }, &P.ch[1]);
-}
-
-// Tuning of the inverse transforms on the depth pass's output (the outputs
-// are written again by the application's own inverse afterwards).
-template <typename T>
-int tune_inverse(fvim_ctx* c, OpPlan<T>& P) {
-  const int nx = c->grid.nx, ny = c->grid.ny, kxh = nx / 2 + 1;
-  hipStream_t st = c->stream;
-  hipError_t e;
+  if ((e = run_x_fwd<T>(c, P, st, P.ch[0])) != hipSuccess) return fail_hip(e, "x_r2c");
+  if ((rc = time_choices(c, ly, [&](FftChoice ch) { return run_y_fwd<T>(c, P, st, ch); }, &P.ch[1]))) return rc;
+  if ((e = run_y_fwd<T>(c, P, st, P.ch[1])) != hipSuccess) return fail_hip(e, "y_fwd");
+  if ((rc = tune_depth<T>(c, P.B, P.A, P.prm))) return rc;
   if (P.k0x && (e = launch_k0_fields(P.wsum, P.wbpp, P.tsum, P.wbpp, P.padd, P.prm, st)) != hipSuccess)
     return fail_hip(e, "k0");
-  int rc = time_choices(c, ilog2i(ny), [&](FftChoice ch) {
-    return launch_y_inv<T>(P.A, P.B, ny, kxh, P.np, P.prm.ld_out, P.twy, st, P.nt, ch);
-  }, &P.ch[2]);
-  if (rc) return rc;
-  if ((e = launch_y_inv<T>(P.A, P.B, ny, kxh, P.np, P.prm.ld_out, P.twy, st, P.nt, P.ch[2])) != hipSuccess)
-    return fail_hip(e, "y_inv");
-  return time_choices(c, ilog2i(nx), [&](FftChoice ch) {
-    return launch_x_c2r<T>(P.B, P.seg, nx, ny, (size_t)P.np, 1.0, P.twx, st, P.padd, P.ep, true, ch);
-  }, &P.ch[3]);
+  if ((rc = time_choices(c, ly, [&](FftChoice ch) { return run_y_inv<T>(c, P, st, ch); }, &P.ch[2]))) return rc;
+  if ((e = run_y_inv<T>(c, P, st, P.ch[2])) != hipSuccess) return fail_hip(e, "y_inv");
+  return time_choices(c, lx, [&](FftChoice ch) { return run_x_inv<T>(c, P, st, ch); }, &P.ch[3]);
 }
 
-// Forward transforms of the input planes: real fields -> mode-major B.
+// One application: forward transforms, depth pass, mean mode (float32 path) and
+// inverse transforms.  ss != st: the Nyquist modes' depth launch runs on ss
+// beside the other modes'.
 template <typename T>
-int op_forward(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, StageTimer& tm) {
-  const int nx = c->grid.nx, ny = c->grid.ny, kxh = nx / 2 + 1;
+int op_run(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, hipStream_t ss, StageTimer& tm) {
   hipError_t e;
   tm.begin(FVIM_STAGE_XFWD, st);
-  if ((e = launch_x_r2c<T>(P.iseg, P.A, nx, ny, (size_t)P.np_in, P.twx, st, P.wsum, P.nt, P.skip, P.ch[0])) !=
-      hipSuccess)
-    return fail_hip(e, "x_r2c");
+  if ((e = run_x_fwd<T>(c, P, st, P.ch[0])) != hipSuccess) return fail_hip(e, "x_r2c");
   tm.end();
   tm.begin(FVIM_STAGE_YFWD, st);
-  if ((e = launch_y_fwd<T>(P.A, P.B, ny, kxh, P.np_in, P.prm.ld_in, P.twy, st, P.nt, P.skip, P.ch[1])) !=
-      hipSuccess)
-    return fail_hip(e, "y_fwd");
+  if ((e = run_y_fwd<T>(c, P, st, P.ch[1])) != hipSuccess) return fail_hip(e, "y_fwd");
   tm.end();
-  return FVIM_OK;
-}
-
-// Mean mode (float32 path) and inverse transforms: mode-major A -> outputs.
-template <typename T>
-int op_inverse(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, StageTimer& tm) {
-  const int nx = c->grid.nx, ny = c->grid.ny, kxh = nx / 2 + 1;
-  hipError_t e;
+  if (ss != st && (e = join(c->ev_spec, st, ss)) != hipSuccess) return fail_hip(e, "fork");
+  tm.begin(FVIM_STAGE_DEPTH, st);
+  if ((e = launch_depth<T>(P.B, P.A, P.prm, c->depth_cfg, st, 1)) != hipSuccess) return fail_hip(e, "depth");
+  tm.end();
+  if (depth_nyq_launch<T>(P.prm)) {
+    tm.begin(FVIM_STAGE_DEPTH_NYQ, ss);
+    if ((e = launch_depth<T>(P.B, P.A, P.prm, c->depth_cfg, ss, 2)) != hipSuccess)
+      return fail_hip(e, "depth (Nyquist modes)");
+    tm.end();
+  }
+  if (ss != st && (e = join(c->ev_nyq, ss, st)) != hipSuccess) return fail_hip(e, "join");
   if (P.k0x && (e = launch_k0_fields(P.wsum, P.wbpp, P.tsum, P.wbpp, P.padd, P.prm, st)) != hipSuccess)
     return fail_hip(e, "k0");
   tm.begin(FVIM_STAGE_YINV, st);
-  if ((e = launch_y_inv<T>(P.A, P.B, ny, kxh, P.np, P.prm.ld_out, P.twy, st, P.nt, P.ch[2])) != hipSuccess)
-    return fail_hip(e, "y_inv");
+  if ((e = run_y_inv<T>(c, P, st, P.ch[2])) != hipSuccess) return fail_hip(e, "y_inv");
   tm.end();
   tm.begin(FVIM_STAGE_XINV, st);
-  if ((e = launch_x_c2r<T>(P.B, P.seg, nx, ny, (size_t)P.np, 1.0, P.twx, st, P.padd, P.ep, true, P.ch[3])) !=
-      hipSuccess)
-    return fail_hip(e, "x_c2r");
+  if ((e = run_x_inv<T>(c, P, st, P.ch[3])) != hipSuccess) return fail_hip(e, "x_c2r");
   tm.end();
   return FVIM_OK;
 }
@@ -529,13 +528,10 @@ int operator_apply_t(fvim_ctx* c, const double* eps_p, const double* traction, d
   // the Nyquist-mode depth launch may run on the side stream beside the main
   // one (disjoint modes); measured slower in float64, so off by default
   hipStream_t ss = side ? c->side : st;
-  hipError_t e;
   StageTimer tm(c, scratch == nullptr);
   // tuning (plain applications only): take the process record for this
   // shape, else time every transform choice and depth layout on this call
-  const bool tune = c->tune_pending && !scratch && !ep;
-  bool timed = false;
-  if (tune) {
+  if (c->tune_pending && !scratch && !ep) {
     const TuneKey key{c->grid.nx, c->grid.ny, c->grid.nz, P.np_in, P.np, (int)sizeof(T), c->arch};
     TuneRec rec{};
     bool have = false;
@@ -547,47 +543,25 @@ int operator_apply_t(fvim_ctx* c, const double* eps_p, const double* traction, d
         have = true;
       }
     }
-    if (have) {
-      for (int k = 0; k < 4; ++k) P.ch[k] = c->fft[prec_index<T>()][k] = rec.ch[k];
-      c->depth_cfg = rec.depth_cfg;
-      c->tune_pending = 0;
-      op_refresh_sums<T>(c, P);
-    } else {
-      if ((rc = tune_forward<T>(c, P))) return rc;
-      timed = true;
+    if (!have) {
+      if ((rc = tune_operator<T>(c, P))) return rc;
+      for (int k = 0; k < 4; ++k) rec.ch[k] = P.ch[k];
+      rec.depth_cfg = c->depth_cfg;
+      std::lock_guard<std::mutex> lk(g_tune_mx);
+      tune_records()[key] = rec;
     }
-  }
-  if ((rc = op_forward<T>(c, P, st, tm))) return rc;
-  if (timed) {
+    for (int k = 0; k < 4; ++k) P.ch[k] = c->fft[prec_index<T>()][k] = rec.ch[k];
+    c->depth_cfg = rec.depth_cfg;
     c->tune_pending = 0;
-    int rc2 = tune_depth<T>(c, P.B, P.A, P.prm);
-    if (rc2) return rc2;
+    op_refresh_sums<T>(c, P);
   }
-  if (ss != st && (e = join(c->ev_spec, st, ss)) != hipSuccess) return fail_hip(e, "fork");
-  tm.begin(FVIM_STAGE_DEPTH, st);
-  if ((e = launch_depth<T>(P.B, P.A, P.prm, c->depth_cfg, st, 1)) != hipSuccess) return fail_hip(e, "depth");
-  tm.end();
-  tm.begin(FVIM_STAGE_DEPTH_NYQ, ss);
-  if ((e = launch_depth<T>(P.B, P.A, P.prm, c->depth_cfg, ss, 2)) != hipSuccess)
-    return fail_hip(e, "depth (Nyquist modes)");
-  tm.end();
-  if (ss != st && (e = join(c->ev_nyq, ss, st)) != hipSuccess) return fail_hip(e, "join");
-  if (timed) {
-    if ((rc = tune_inverse<T>(c, P))) return rc;
-    for (int k = 0; k < 4; ++k) c->fft[prec_index<T>()][k] = P.ch[k];
-    const TuneKey key{c->grid.nx, c->grid.ny, c->grid.nz, P.np_in, P.np, (int)sizeof(T), c->arch};
-    TuneRec rec{};
-    for (int k = 0; k < 4; ++k) rec.ch[k] = P.ch[k];
-    rec.depth_cfg = c->depth_cfg;
-    std::lock_guard<std::mutex> lk(g_tune_mx);
-    tune_records()[key] = rec;
-  }
-  return op_inverse<T>(c, P, st, tm);
+  return op_run<T>(c, P, st, ss, tm);
 }
 
-// Several contexts (grids may differ) on the stream of the first: every
-// context's forward transforms, one depth launch per part for up to
-// DEPTH_BATCH_MAX contexts at a time, every context's inverse transforms.
+// Several contexts (grids may differ) on the stream of the first.  Grids whose
+// transform lengths are both at most 2^XFORM_BATCH_MAX_LOGN share one launch per
+// stage (up to XFORM_BATCH_MAX or DEPTH_BATCH_MAX grids each, the default
+// choices); longer ones run their own applications, with their own choices.
 template <typename T>
 int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps, const double* const* tr,
                            double* const* strain, double* const* stress, double* const* disp,
@@ -602,37 +576,35 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
   };
   for (int i = 0; i < n; ++i) cs[i]->stream = st;   // one stream orders the whole batch
   int rc = 0, maxnz = 0;
+  fvim_ctx* c0 = cs[0];
+  StageTimer tm(c0);
+  std::vector<int> bat;
   for (int i = 0; i < n && !rc; ++i) {
     rc = op_plan<T>(cs[i], eps ? eps[i] : nullptr, tr ? tr[i] : nullptr, strain ? strain[i] : nullptr,
                     stress ? stress[i] : nullptr, disp ? disp[i] : nullptr, surf_u3 ? surf_u3[i] : nullptr, P[i]);
     if (!rc && P[i].np == 0) rc = fail(FVIM_EINVAL, "batch: every context needs an output");
-    maxnz = std::max(maxnz, cs[i]->grid.nz);
-  }
-  if (rc) return restore(rc);
-  fvim_ctx* c0 = cs[0];
-  if ((rc = ctx_reserve(c0, &c0->dbatch, &c0->dbatch_bytes, sizeof(DepthBatch)))) return restore(rc);
-  StageTimer tm(c0);
-  // the persistent single-launch form (FVIM_OPT_PERSISTENT): float64, strain
-  // only, every grid within the batched transform lengths, one table each
-  bool persist = c0->persistent && std::is_same<T, double>::value && !stress && !disp && !surf_u3 &&
-                 n <= XFORM_BATCH_MAX && n <= DEPTH_BATCH_MAX;
-  for (int i = 0; i < n && persist; ++i)
-    persist = ilog2i(cs[i]->grid.nx) <= XFORM_BATCH_MAX_LOGN && ilog2i(cs[i]->grid.ny) <= XFORM_BATCH_MAX_LOGN &&
-              !P[i].k0x;
-  // Grids whose transform lengths are both at most 2^XFORM_BATCH_MAX_LOGN
-  // share one launch per transform stage (up to XFORM_BATCH_MAX grids each,
-  // the default choices); longer ones keep launches of their own.
-  std::vector<int> bat;
-  for (int i = 0; i < n; ++i) {
+    if (rc) break;
     if (ilog2i(cs[i]->grid.nx) <= XFORM_BATCH_MAX_LOGN && ilog2i(cs[i]->grid.ny) <= XFORM_BATCH_MAX_LOGN) {
       bat.push_back(i);
+      maxnz = std::max(maxnz, cs[i]->grid.nz);
       for (int k = 0; k < 4; ++k) P[i].ch[k] = FftChoice{};
       P[i].wbpp = x_r2c_batch_blocks_per_plane<T>(cs[i]->grid.nx, cs[i]->grid.ny);
       if (P[i].k0x) P[i].tsum = P[i].wsum + (size_t)P[i].prm.off_t * P[i].wbpp;
-    } else if ((rc = op_forward<T>(cs[i], P[i], st, tm))) {
-      return restore(rc);
     }
   }
+  if (rc) return restore(rc);
+  const int nb = (int)bat.size();
+  for (int i = 0; i < n; ++i) {
+    if (std::find(bat.begin(), bat.end(), i) != bat.end()) continue;
+    if ((rc = op_run<T>(cs[i], P[i], st, st, tm))) return restore(rc);
+  }
+  if (nb == 0) return restore(FVIM_OK);
+  if ((rc = ctx_reserve(c0, &c0->dbatch, &c0->dbatch_bytes, sizeof(DepthBatch)))) return restore(rc);
+  // the persistent single-launch form (FVIM_OPT_PERSISTENT): float64, strain
+  // only, every grid a shared one, one table each
+  bool persist = c0->persistent && std::is_same<T, double>::value && !stress && !disp && !surf_u3 && nb == n &&
+                 n <= XFORM_BATCH_MAX && n <= DEPTH_BATCH_MAX;
+  for (int i = 0; i < n && persist; ++i) persist = !P[i].k0x;
   // the table of one stage of the batched grids bat[i0 ..], at most
   // XFORM_BATCH_MAX of them
   auto fill_xform = [&](int kind, size_t i0, XformBatch& b) {
@@ -682,23 +654,24 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     }
     return FVIM_OK;
   };
-  const int cfg = depth_default_config(maxnz);
-  const int gpb = depth_groups_per_block(cfg);
-  // the depth table of grids i0 .. i0 + DEPTH_BATCH_MAX - 1
+  const int cfg = depth_batch_config(maxnz);
+  // the depth table of the grids bat[i0 .. i0 + DEPTH_BATCH_MAX - 1]
   auto fill_depth = [&](int i0, DepthBatch& b) {
     b = DepthBatch{};
-    b.n = std::min(DEPTH_BATCH_MAX, n - i0);
+    b.n = std::min(DEPTH_BATCH_MAX, nb - i0);
     for (int k = 0; k < b.n; ++k) {
-      const DepthParams& p = P[i0 + k].prm;
-      b.prm[k] = p;
+      const OpPlan<T>& p = P[bat[i0 + k]];
+      b.prm[k] = p.prm;
       // the Nyquist sign replicas join the main launch (records after the
       // spectrum in A, reserved by op_plan), whatever the side-stream option
-      b.prm[k].rep_out = (void*)(P[i0 + k].A + (size_t)p.kxh * p.ny * p.ld_out);
+      b.prm[k].rep_out = (void*)(p.A + (size_t)p.prm.kxh * p.prm.ny * p.prm.ld_out);
       depth_derive(b.prm[k]);
-      b.in[k] = P[i0 + k].B;
-      b.out[k] = P[i0 + k].A;
-      b.first_main[k + 1] = b.first_main[k] + (p.kxh * p.ny + depth_replicas(p.ny, p.kxh) + gpb - 1) / gpb;
-      b.first_nyq[k + 1] = b.first_nyq[k] + (p.ny + p.kxh - 1);           // one block per Nyquist mode
+      b.in[k] = p.B;
+      b.out[k] = p.A;
+      int nm, nq;
+      depth_blocks<T>(cfg, b.prm[k], &nm, &nq);
+      b.first_main[k + 1] = b.first_main[k] + nm;
+      b.first_nyq[k + 1] = b.first_nyq[k] + nq;
     }
   };
   if (persist) {
@@ -714,7 +687,7 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     (void)hipGetLastError();
   }
   if ((rc = xform(0, FVIM_STAGE_XFWD)) || (rc = xform(1, FVIM_STAGE_YFWD))) return restore(rc);
-  for (int i0 = 0; i0 < n; i0 += DEPTH_BATCH_MAX) {
+  for (int i0 = 0; i0 < nb; i0 += DEPTH_BATCH_MAX) {
     DepthBatch b;
     fill_depth(i0, b);
     tm.begin(FVIM_STAGE_DEPTH, st);
@@ -722,16 +695,11 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     tm.end();
     if (e != hipSuccess) return restore(fail_hip(e, "batched depth pass"));
   }
-  for (int i = 0; i < n && !rc; ++i) {
-    const bool in_batch = std::find(bat.begin(), bat.end(), i) != bat.end();
-    if (!in_batch) {
-      rc = op_inverse<T>(cs[i], P[i], st, tm);
-    } else if (P[i].k0x) {
-      hipError_t e = launch_k0_fields(P[i].wsum, P[i].wbpp, P[i].tsum, P[i].wbpp, P[i].padd, P[i].prm, st);
-      if (e != hipSuccess) rc = fail_hip(e, "k0");
-    }
+  for (int i : bat) {
+    if (!P[i].k0x) continue;
+    hipError_t e = launch_k0_fields(P[i].wsum, P[i].wbpp, P[i].tsum, P[i].wbpp, P[i].padd, P[i].prm, st);
+    if (e != hipSuccess) return restore(fail_hip(e, "k0"));
   }
-  if (rc) return restore(rc);
   if ((rc = xform(2, FVIM_STAGE_YINV)) || (rc = xform(3, FVIM_STAGE_XINV))) return restore(rc);
   return restore(FVIM_OK);
 }
@@ -918,7 +886,9 @@ int fvim_get_option(fvim_ctx* c, int key, int* value) {
   if (!c || !value) return fail(FVIM_EINVAL, "NULL argument");
   switch (key) {
     case FVIM_OPT_DEPTH_CONFIG:
-      *value = c->depth_cfg >= 0 ? c->depth_cfg : depth_default_config(c->grid.nz);
+      *value = c->depth_cfg >= 0 ? c->depth_cfg
+               : c->precision == FVIM_FP64 ? depth_default_config<double>(c->grid.nz)
+                                           : depth_default_config<float>(c->grid.nz);
       return FVIM_OK;
     case FVIM_OPT_TUNE:
       *value = c->tune_pending;

@@ -40,11 +40,16 @@
 
 namespace fvim {
 namespace {
+// Waves per SIMD a layout's registers are held to: the float64 one-wave layout
+// fits 3 (at most 168 registers; the batched form takes up to 170 otherwise).
+template <typename T, int LPM, int P>
+constexpr int depth_waves() { return sizeof(T) == 8 && LPM == 64 && P == 1 ? 3 : 1; }
+
 // NTL: the input spectrum is read with streaming loads (last use); NU:
 // non-uniform depth nodes (prm.hz)
 template <typename T, int LPM, int P, bool DISP, bool WANTX, bool NYQ, bool NTL, bool NU = false>
-__global__ __launch_bounds__(NT) void k_depth(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
-                                             DepthParams prm) {
+__global__ __launch_bounds__(NT, (depth_waves<T, LPM, P>()))
+void k_depth(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, DepthParams prm) {
   depth_modes<T, LPM, P, DISP, WANTX, NYQ, NTL, NU>(in, out, prm, blockIdx.x);
 }
 
@@ -52,7 +57,8 @@ __global__ __launch_bounds__(NT) void k_depth(const cpx<T>* __restrict__ in, cpx
 // first[c] <= b < first[c + 1] (main or Nyquist block counts); the table is
 // in device memory, so its fields are block-uniform loads.
 template <typename T, int LPM, int P, bool DISP, bool WANTX, bool NYQ>
-__global__ __launch_bounds__(NT) void k_depth_batch(const DepthBatch* __restrict__ b) {
+__global__ __launch_bounds__(NT, (depth_waves<T, LPM, P>()))
+void k_depth_batch(const DepthBatch* __restrict__ b) {
   depth_batch_block<T, LPM, P, DISP, WANTX, NYQ>(b, (int)blockIdx.x);
 }
 
@@ -96,14 +102,21 @@ __global__ __launch_bounds__(NT) void k_mode_table(ModeConst<T>* __restrict__ ta
   tab[m] = c;
 }
 
+// Blocks of the main launch with gpb lane groups per block: the modes, and with
+// rep_out the sign replicas, in blocks of their own where the pass averages them.
+template <typename T>
+int main_blocks(int gpb, const DepthParams& p) {
+  const int nm = p.kxh * p.ny, nr = p.rep_out ? depth_replicas(p.ny, p.kxh) : 0;
+  return mean_in_pass<T>() ? (nm + gpb - 1) / gpb + (nr + gpb - 1) / gpb : (nm + nr + gpb - 1) / gpb;
+}
+
 template <typename T, int LPM, int P, bool DISP, bool WANTX>
 hipError_t launch_two(const cpx<T>* in, cpx<T>* out, const DepthParams& p, hipStream_t st,
                       int part) {
   constexpr int GPB = NT / LPM;
   const int nnyq = p.ny + p.kxh - 1;
   if (part != 2) {
-    const int nmodes = p.kxh * p.ny + (p.rep_out ? depth_replicas(p.ny, p.kxh) : 0);
-    const unsigned nb = (unsigned)((nmodes + GPB - 1) / GPB);
+    const unsigned nb = (unsigned)main_blocks<T>(GPB, p);
     // streaming loads only where a load instruction reads whole lines (one
     // node per lane): with P > 1 the lanes read every P-th element and the
     // rest of the line would be fetched again
@@ -133,8 +146,9 @@ hipError_t launch_two(const cpx<T>* in, cpx<T>* out, const DepthParams& p, hipSt
   }
   if (part != 1) {
     if (p.rep_out) {
-      hipLaunchKernelGGL(k_nyq_average<T>, dim3((unsigned)nnyq), dim3(NT), 0, st, out,
-                         static_cast<const cpx<T>*>(p.rep_out), p.nx, p.ny, p.kxh, p.ld_out, p.np_out);
+      if (!mean_in_pass<T>())
+        hipLaunchKernelGGL(k_nyq_average<T>, dim3((unsigned)nnyq), dim3(NT), 0, st, out,
+                           static_cast<const cpx<T>*>(p.rep_out), p.nx, p.ny, p.kxh, p.ld_out, p.np_out);
     } else {
       const unsigned nb2 = (unsigned)((nnyq + GPB - 1) / GPB);
       if (p.hz)
@@ -178,8 +192,10 @@ bool depth_config_valid(int id, int nz) {
   return nz <= cap && 4 * nz > cap;
 }
 
-// Default without tuning: the fewest nodes per lane that keeps <= 64 lanes.
-int depth_default_config(int nz) {
+// Layout of a batched pass over grids of at most nz nodes: the fewest nodes per
+// lane that keeps <= 64 lanes.  (Two nodes per lane up to 128 nodes: a grid's sums
+// then do not depend on which of these layouts the rest of the batch asks for.)
+int depth_batch_config(int nz) {
   if (nz <= 16) return 0;
   if (nz <= 32) return 1;
   if (nz <= 64) return 3;
@@ -187,6 +203,19 @@ int depth_default_config(int nz) {
   if (nz <= 256) return 6;
   return 7;
 }
+
+// Default of one grid's pass without tuning: the same, but for 32 < nz <= 64 in
+// float64 one node per lane of a wave (reads whole lines, mode constants in scalar
+// registers, DPP scans): against 32 lanes x 2 nodes 8.8 / 15.7 us at 16^2 x 64,
+// 23.8 / 29.5 at 128^2 x 64, 76.8 / 99.0 at 256^2 x 64, 1231 / 1373 at 1024^2 x 64,
+// 17.1 / 19.6 at 64 x 128 x 33 and 62.9 / 61.6 at 256^2 x 33.  In float32 it is the
+// slower one (57.6 / 45.7 us at 256^2 x 64).
+template <typename T>
+int depth_default_config(int nz) {
+  return sizeof(T) == 8 && nz > 32 && nz <= 64 ? 4 : depth_batch_config(nz);
+}
+template int depth_default_config<double>(int);
+template int depth_default_config<float>(int);
 
 template <typename T>
 hipError_t launch_mode_table(ModeConst<T>* tab, int nx, int ny, double lx, double ly, double h, hipStream_t st) {
@@ -206,7 +235,11 @@ void depth_derive(DepthParams& p) {
   p.ik2 = 1.0 / (2.0 * kap + 2.0);
 }
 
-int depth_groups_per_block(int cfg) { return NT / kCfgs[cfg].lpm; }
+template <typename T>
+void depth_blocks(int cfg, const DepthParams& p, int* main, int* nyq) {
+  *main = main_blocks<T>(NT / kCfgs[cfg].lpm, p);
+  *nyq = mean_in_pass<T>() ? 0 : p.ny + p.kxh - 1;
+}
 
 // main launch (every mode, and the Nyquist sign replicas as modes of their
 // own), then one block per Nyquist mode averaging its replicas
@@ -261,7 +294,7 @@ hipError_t launch_depth(const cpx<T>* in, cpx<T>* out, const DepthParams& prm, i
   if (!prm.mtab) return hipErrorInvalidValue;
   DepthParams p = prm;
   depth_derive(p);
-  if (!depth_config_valid(cfg, p.nz)) cfg = depth_default_config(p.nz);
+  if (!depth_config_valid(cfg, p.nz)) cfg = depth_default_config<T>(p.nz);
   switch (cfg) {
     case 0: return launch_cfg<T, 16, 1>(in, out, p, st, part);
     case 1: return launch_cfg<T, 16, 2>(in, out, p, st, part);
@@ -279,6 +312,8 @@ template hipError_t launch_depth<double>(const cpx<double>*, cpx<double>*, const
                                          int);
 template hipError_t launch_depth<float>(const cpx<float>*, cpx<float>*, const DepthParams&, int, hipStream_t, int);
 template hipError_t launch_mode_table<double>(ModeConst<double>*, int, int, double, double, double, hipStream_t);
+template void depth_blocks<double>(int, const DepthParams&, int*, int*);
+template void depth_blocks<float>(int, const DepthParams&, int*, int*);
 template hipError_t launch_depth_batch<double>(const DepthBatch&, DepthBatch*, int, hipStream_t);
 template hipError_t launch_depth_batch<float>(const DepthBatch&, DepthBatch*, int, hipStream_t);
 template hipError_t launch_mode_table<float>(ModeConst<float>*, int, int, double, double, double, hipStream_t);

@@ -232,16 +232,50 @@ __device__ __forceinline__ void depth_modes(const cpx<T>* __restrict__ in, cpx<T
   constexpr int GPB = NT / LPM;
   // one wave per mode on uniform nodes: the scans and lane moves use DPP
   constexpr bool DPPS = LPM == 64 && !NU;
-  const int g = threadIdx.x / LPM;
+  constexpr bool MEAN = mean_in_pass<T>() && !NYQ;
+  constexpr bool WMEAN = MEAN && LPM == 16;        // a mode's replicas are in one wave
+  int g = threadIdx.x / LPM;
+  // (one wave per mode: the mode constants are the same in all its lanes and
+  // stay in scalar registers, 153 vector registers instead of 177 for 64 lanes x
+  // 1 node)
+  if constexpr (MEAN && LPM == 64) g = __builtin_amdgcn_readfirstlane(g);
   const int l = threadIdx.x - g * LPM;
-  const int gid = block * GPB + g;
+  int gid = block * GPB + g;
   int kx, ky;
   // vrep >= 0: this group evaluates sign replica vrep of a Nyquist mode,
   // unweighted, into replica record vslot of prm.rep_out.  Replica records:
   // 2 j, 2 j + 1 for Nyquist mode j (the kx = nx/2 column first, then the
-  // ky = ny/2 row), then replicas 2 and 3 of the corner
+  // ky = ny/2 row), then replicas 2 and 3 of the corner.  MEAN: the replicas
+  // have the first blocks (at the end their barrier and second pass would be the
+  // launch's tail), the corner's 4 first, then the pairs of the column and of the
+  // row, so that a mode's replicas are neighbouring groups of one block, which
+  // forms their mean: value by value where they are in one wave, else from the
+  // records after a barrier (2 of 23 us of an application at 32 x 32 x 16).
   int vrep = -1, vslot = 0;
-  if (NYQ) {
+  if constexpr (MEAN) {
+    const int nrep_all = prm.rep_out ? depth_replicas(prm.ny, prm.kxh) : 0;
+    const int nrb = (nrep_all + GPB - 1) / GPB;
+    if (block < nrb) {                  // the same for the whole block
+      // idle groups of the last such block: the last replica again, the same values
+      vslot = min(gid, nrep_all - 1);
+      if (vslot < 4) {
+        kx = prm.nx / 2;
+        ky = prm.ny / 2;
+        vrep = vslot;
+      } else {
+        const int j = (vslot - 4) >> 1;
+        vrep = vslot & 1;
+        if (j < prm.ny - 1) { kx = prm.nx / 2; ky = j < prm.ny / 2 ? j : j + 1; }
+        else { kx = j - (prm.ny - 1); ky = prm.ny / 2; }
+      }
+    } else {
+      gid -= nrb * GPB;
+      if (gid >= prm.kxh * prm.ny) return;   // the whole lane group leaves together
+      kx = gid / prm.ny;
+      ky = gid - kx * prm.ny;
+      if (kx * 2 == prm.nx || ky * 2 == prm.ny) return;
+    }
+  } else if (NYQ) {
     if (gid >= prm.ny + prm.kxh - 1) return;
     if (gid < prm.ny) { kx = prm.nx / 2; ky = gid; }
     else { kx = gid - prm.ny; ky = prm.ny / 2; }
@@ -265,7 +299,7 @@ __device__ __forceinline__ void depth_modes(const cpx<T>* __restrict__ in, cpx<T
   const int mode = kx * prm.ny + ky;
   const int nz = prm.nz;
   const cpx<T>* __restrict__ src = in + (size_t)mode * prm.ld_in;
-  cpx<T>* __restrict__ dst = vrep >= 0 ? static_cast<cpx<T>*>(prm.rep_out) + (size_t)vslot * prm.ld_out
+  cpx<T>* __restrict__ dst = vrep >= 0 && !WMEAN ? static_cast<cpx<T>*>(prm.rep_out) + (size_t)vslot * prm.ld_out
                                        : out + (size_t)mode * prm.ld_out;
   const T nrm = (T)prm.norm;
   const T kap = (T)prm.kappa;
@@ -281,11 +315,26 @@ __device__ __forceinline__ void depth_modes(const cpx<T>* __restrict__ in, cpx<T
 #pragma unroll
   for (int c = 0; c < 3; ++c) tr[c] = prm.has_t ? scl(src[prm.off_t + c], nrm / mu) : zero<T>();
 
+  auto keep = [&](cpx<T>* __restrict__ p, cpx<T> v, bool first) {
+    if constexpr (WMEAN) {
+      if (vrep >= 0) {
+        const T w = vslot < 4 ? T(0.25) : T(0.5);        // exact; the same for the whole wave
+        cpx<T> m = add(scl(sh_down<T, 64>(v, LPM), w), scl(v, w));
+        if (vslot < 4) {
+          m = add(scl(sh_down<T, 64>(v, 2 * LPM), w), m);
+          m = add(scl(sh_down<T, 64>(v, 3 * LPM), w), m);
+        }
+        if (vrep > 0) return;
+        v = m;
+      }
+    }
+    put(p, v, first);
+  };
   // strain e (original frame, 6 comps) of node i -> outputs (stress needs eps_p again)
   auto emit = [&](int i, const cpx<T> e[6], bool first, T wgt) {
     if (wantS) {
 #pragma unroll
-      for (int c = 0; c < 6; ++c) put(dst + prm.off_strain + (size_t)c * nz + i, scl(e[c], wgt), first);
+      for (int c = 0; c < 6; ++c) keep(dst + prm.off_strain + (size_t)c * nz + i, scl(e[c], wgt), first);
     }
     if (wantX) {
       cpx<T> ep[6];
@@ -297,7 +346,7 @@ __device__ __forceinline__ void depth_modes(const cpx<T>* __restrict__ in, cpx<T
       for (int c = 0; c < 6; ++c) {
         cpx<T> sc = scl(sub(e[c], ep[c]), T(2) * mu);
         if (c < 3) sc = axpy(sc, kap * mu, sub(tre, trp));
-        put(dst + prm.off_stress + (size_t)c * nz + i, scl(sc, wgt), first);
+        keep(dst + prm.off_stress + (size_t)c * nz + i, scl(sc, wgt), first);
       }
     }
   };
@@ -633,12 +682,32 @@ __device__ __forceinline__ void depth_modes(const cpx<T>* __restrict__ in, cpx<T
           cpx<T> V = scl(v, iq);
           cpx<T> W = scl(c, iq);
           if (prm.off_disp >= 0) {
-            put(dst + prm.off_disp + i, scl(sub(scl(U, n1), scl(V, n2)), wrep), rep == rep0);
-            put(dst + prm.off_disp + (size_t)nz + i, scl(add(scl(U, n2), scl(V, n1)), wrep), rep == rep0);
-            put(dst + prm.off_disp + (size_t)2 * nz + i, scl(W, wrep), rep == rep0);
+            keep(dst + prm.off_disp + i, scl(sub(scl(U, n1), scl(V, n2)), wrep), rep == rep0);
+            keep(dst + prm.off_disp + (size_t)nz + i, scl(add(scl(U, n2), scl(V, n1)), wrep), rep == rep0);
+            keep(dst + prm.off_disp + (size_t)2 * nz + i, scl(W, wrep), rep == rep0);
           }
-          if (prm.off_u3 >= 0 && i == 0) put(dst + prm.off_u3, scl(W, wrep), rep == rep0);
+          if (prm.off_u3 >= 0 && i == 0) keep(dst + prm.off_u3, scl(W, wrep), rep == rep0);
         }
+      }
+    }
+  }
+
+  if constexpr (MEAN && !WMEAN) {
+    if (vrep >= 0) {                    // the whole block
+      __syncthreads();
+      // by all lanes of the mode's groups, several loads in flight
+      const int n = vslot < 4 ? 4 : 2;
+      const T w = vslot < 4 ? T(0.25) : T(0.5);          // exact
+      const cpx<T>* __restrict__ r = dst - (size_t)vrep * prm.ld_out;
+      cpx<T>* __restrict__ to = out + (size_t)mode * prm.ld_out;
+#pragma unroll 4
+      for (int c = vrep * LPM + l; c < prm.np_out; c += n * LPM) {
+        cpx<T> v = add(scl(r[(size_t)prm.ld_out + c], w), scl(r[c], w));
+        if (n == 4) {
+          v = add(scl(r[(size_t)2 * prm.ld_out + c], w), v);
+          v = add(scl(r[(size_t)3 * prm.ld_out + c], w), v);
+        }
+        to[c] = v;
       }
     }
   }

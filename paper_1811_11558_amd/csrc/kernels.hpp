@@ -150,7 +150,8 @@ struct DepthParams {
   // Nyquist modes: NULL -> a second launch averages each mode's 2 or 4 sign
   // replicas in turn; else the main launch evaluates every replica as a
   // mode of its own into depth_replicas(ny, kxh) records of stride ld_out
-  // here, and the second launch averages them
+  // here, and averages them itself (float64) or leaves that to the second
+  // launch (float32)
   void* rep_out;
   int nt_in;              // the main launch reads the input with streaming loads
   const int* zact;        // if set: eigenstrain layers z >= *zact are zero and not read
@@ -174,9 +175,8 @@ struct alignas(16) ModeConst {
 // Depth pass over several grids in one launch per part: the host table lists
 // each grid's parameters (derived constants filled by depth_derive, rep_out
 // set: the Nyquist sign replicas are modes of the main launch), input and
-// output spectra, and prefix counts of blocks: first_main for the main launch
-// (modes and replicas, depth_groups_per_block(cfg) per block), first_nyq for
-// the averaging launch (one block per Nyquist mode).  dtab is a device copy
+// output spectra, and prefix counts of blocks (depth_blocks): first_main for the
+// main launch, first_nyq for the averaging launch (none in float64).  dtab is a device copy
 // target.  Every grid must request the same kinds of output and have nz <=
 // the configuration's capacity.
 constexpr int DEPTH_BATCH_MAX = 8;
@@ -206,21 +206,36 @@ hipError_t launch_operator_persistent(OpBatch& host, OpBatch* dev, int depth_cfg
                                       hipStream_t st);
 // Sign replicas of the Nyquist modes: 2 for each of the ny + kxh - 1 modes on
 // the kx = nx/2 column or the ky = ny/2 row, 2 more for the corner.
-inline int depth_replicas(int ny, int kxh) { return 2 * (ny + kxh); }
-int depth_groups_per_block(int cfg);
+__host__ __device__ inline int depth_replicas(int ny, int kxh) { return 2 * (ny + kxh); }
+// Whether the main launch forms the Nyquist modes from their sign replicas
+// itself (float64).  The launch that does it otherwise costs 4 of the 25 us of an
+// application at 32 x 32 x 16.  float32 keeps that launch: in the one-launch form
+// the compiler fuses other multiplies and adds of the recurrences (hardly two
+// layouts alike), which changes float32 results by 1e-7.
+template <typename T>
+__host__ __device__ constexpr bool mean_in_pass() { return sizeof(T) == 8; }
+// whether part 2 launches anything
+template <typename T>
+bool depth_nyq_launch(const DepthParams& p) { return !p.rep_out || !mean_in_pass<T>(); }
+
+// blocks of the main and of the averaging launch of a batched pass (rep_out set)
+template <typename T>
+void depth_blocks(int cfg, const DepthParams& p, int* main, int* nyq);
 template <typename T>
 hipError_t launch_depth_batch(const DepthBatch& host, DepthBatch* dtab, int cfg, hipStream_t st);
 
 template <typename T>
 hipError_t launch_mode_table(ModeConst<T>* tab, int nx, int ny, double lx, double ly, double h, hipStream_t st);
 
-// part: 0 = every mode (two launches), 1 = all but the Nyquist modes,
-// 2 = the Nyquist modes only.
+// part: 0 = every mode, 1 = the main launch, 2 = what the Nyquist modes need
+// after it or, without rep_out, beside it.
 template <typename T>
 hipError_t launch_depth(const cpx<T>* in, cpx<T>* out, const DepthParams& p, int cfg, hipStream_t st,
                         int part = 0);
 int depth_num_configs();
 bool depth_config_valid(int id, int nz);
+int depth_batch_config(int nz);
+template <typename T>
 int depth_default_config(int nz);
 
 // Mean-mode (k = 0) fields in float64 from the block sums of the input

@@ -2,10 +2,9 @@
 // application over several grids of different sizes in ONE cooperative
 // launch.  The grid of blocks (as many as the device holds at once) loops
 // over the blocks of each stage in turn -- forward row transforms, forward
-// column transforms, the depth pass with the Nyquist sign replicas, the
-// Nyquist averages, inverse column and inverse row transforms -- and meets
-// at a grid barrier between stages, so the stages need no launches of their
-// own and no block waits for a kernel boundary.  Every block runs the same
+// column transforms, the depth pass, inverse column and inverse row transforms
+// -- and meets at a grid barrier between stages, so the stages need no launches
+// of their own and no block waits for a kernel boundary.  Every block runs the same
 // device bodies as the batched launches (fft_dev.hpp, depth_dev.hpp), so the
 // results are bitwise those of the multi-launch batch.
 #include <hip/hip_cooperative_groups.h>
@@ -29,22 +28,33 @@ __global__ __launch_bounds__(NT) void k_op_persistent(const OpBatch* __restrict_
   cg::grid_group grid = cg::this_grid();
   const int G = (int)gridDim.x;
   const int b0 = (int)blockIdx.x;
+  // a block's LDS tiles are used again by its next item: the barrier after each
   const XformBatch& x0 = t->x[0];
-  for (int blk = b0; blk < x0.first[x0.n]; blk += G) x_r2c_batch_block<T>(x0, blk, red);
+  for (int blk = b0; blk < x0.first[x0.n]; blk += G) {
+    x_r2c_batch_block<T>(x0, blk, red);
+    __syncthreads();
+  }
   grid.sync();
   const XformBatch& x1 = t->x[1];
-  for (int blk = b0; blk < x1.first[x1.n]; blk += G) y_fwd_batch_block<T>(x1, blk);
+  for (int blk = b0; blk < x1.first[x1.n]; blk += G) {
+    y_fwd_batch_block<T>(x1, blk);
+    __syncthreads();
+  }
   grid.sync();
   const DepthBatch* d = &t->d;
   for (int blk = b0; blk < d->first_main[d->n]; blk += G) depth_batch_block<T, LPM, P, false, false, false>(d, blk);
   grid.sync();
-  for (int blk = b0; blk < d->first_nyq[d->n]; blk += G) nyq_batch_block<T>(d, blk);
-  grid.sync();
   const XformBatch& x2 = t->x[2];
-  for (int blk = b0; blk < x2.first[x2.n]; blk += G) y_inv_batch_block<T>(x2, blk);
+  for (int blk = b0; blk < x2.first[x2.n]; blk += G) {
+    y_inv_batch_block<T>(x2, blk);
+    __syncthreads();
+  }
   grid.sync();
   const XformBatch& x3 = t->x[3];
-  for (int blk = b0; blk < x3.first[x3.n]; blk += G) x_c2r_batch_block<T>(x3, blk, red);
+  for (int blk = b0; blk < x3.first[x3.n]; blk += G) {
+    x_c2r_batch_block<T>(x3, blk, red);
+    __syncthreads();
+  }
 }
 
 }  // namespace
@@ -54,7 +64,7 @@ hipError_t launch_operator_persistent(OpBatch& host, OpBatch* dev, int depth_cfg
                                       hipStream_t st) {
   if (disp || wx || !std::is_same<T, double>::value) return hipErrorNotSupported;
   const void* kern = nullptr;
-  switch (depth_cfg) {          // the default layouts of nz <= 16, 32, 64, 128
+  switch (depth_cfg) {          // depth_batch_config of nz <= 16, 32, 64, 128
     case 0: kern = (const void*)k_op_persistent<double, 16, 1>; break;
     case 1: kern = (const void*)k_op_persistent<double, 16, 2>; break;
     case 3: kern = (const void*)k_op_persistent<double, 32, 2>; break;
@@ -77,7 +87,7 @@ hipError_t launch_operator_persistent(OpBatch& host, OpBatch* dev, int depth_cfg
   }
   int items = 0;
   for (int k = 0; k < 4; ++k) items = std::max(items, host.x[k].first[host.x[k].n]);
-  items = std::max(items, std::max(host.d.first_main[host.d.n], host.d.first_nyq[host.d.n]));
+  items = std::max(items, host.d.first_main[host.d.n]);
   int device = 0, ncu = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);

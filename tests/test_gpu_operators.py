@@ -514,3 +514,30 @@ def test_batched_transforms_same_alone_and_in_a_batch():
             assert torch.equal(got[i][k], alone[k]), (shapes[i], k)
     for c in ctxs:
         c.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(4, 4, 7), (8, 16, 16), (32, 4, 24), (16, 8, 40), (4, 32, 64), (8, 4, 70),
+                                      (16, 16, 130)])
+def test_nyquist_modes_of_every_layout_and_last_block(nx, ny, nz):
+    """White noise (its Nyquist modes are as large as the others) through
+    each depth layout that serves nz, every output: the Nyquist modes are
+    means over sign replicas formed in the first blocks of the launch, whose
+    last one is partly idle at these sizes."""
+    g = grid_dict(nx, ny, nz, 1.0, 0.5, 0.3)
+    rng = np.random.default_rng(nx + 10 * ny + nz)
+    eps, t = rng.standard_normal((6, nz, ny, nx)), rng.standard_normal((3, ny, nx))
+    ref = ora.apply(g, E, NU, eps_p=eps, traction=t)
+    ctx = _ctx(g)
+    dev = torch.device("cuda")
+    for cfg, cap in enumerate((16, 32, 32, 64, 64, 128, 256, 512)):
+        if not nz <= cap < 4 * nz:
+            continue
+        ctx.set_option(ctx.OPT_DEPTH_CONFIG, cfg)
+        out = ctx.operator_apply(torch.from_numpy(eps).to(dev), torch.from_numpy(t).to(dev),
+                                 want=("strain", "stress", "disp", "surf_u3"))
+        torch.cuda.synchronize()
+        for k in ("strain", "stress", "disp", "surf_u3"):
+            err = _rel(out[k].cpu().numpy(), ref[k])
+            _say("nyquist", (nx, ny, nz), cfg, k, err)
+            assert err <= TOL, (cfg, k, err)
+    ctx.close()
