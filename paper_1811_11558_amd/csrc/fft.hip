@@ -37,42 +37,39 @@ template <typename T, int LOGN, int TILE>
 __host__ __device__ constexpr int c2r_lds_elems() {
   return c2r_seq<T>(1 << LOGN, TILE) * ((1 << LOGN) + 1);
 }
-template <typename T, int LOGN, int TILE>
-__host__ __device__ constexpr int col_lds_elems() {
-  return col_batch<T>(1 << LOGN, TILE) * ((1 << LOGN) + 1);
-}
-
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
-__global__ __launch_bounds__(NT) void k_x_r2c(InSegments seg, cpx<T>* __restrict__ out, int ny, int R,
+__global__ __launch_bounds__((r2c_threads<T>(1 << LOGN, TILE))) void k_x_r2c(InSegments seg, cpx<T>* __restrict__ out, int ny, int R,
                                              const cpx<T>* __restrict__ tw, double* __restrict__ bsum,
                                              LayerSkip skip) {
   __shared__ cpx<T> buf[r2c_lds_elems<T, LOGN, TILE>()];
-  __shared__ double red[NT / 64];
-  x_r2c_body<T, LOGN, NTL, TILE, RADIX>(buf, red, blockIdx.x, seg, out, ny, R, tw, bsum, skip);
+  constexpr int NTH = r2c_threads<T>(1 << LOGN, TILE);
+  __shared__ double red[NTH / 64];
+  x_r2c_body<T, LOGN, NTL, TILE, RADIX, NTH>(buf, red, blockIdx.x, seg, out, ny, R, tw, bsum, skip);
 }
 
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
-__global__ __launch_bounds__(NT) void k_y_fwd(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, int kxh,
-                                             int NP, int ldp, const cpx<T>* __restrict__ tw, LayerSkip skip) {
-  __shared__ cpx<T> buf[col_lds_elems<T, LOGN, TILE>()];
-  y_fwd_body<T, LOGN, NTL, TILE, RADIX>(buf, xcd_block(), in, out, kxh, NP, ldp, tw, skip);
+__global__ __launch_bounds__((col_threads<T>(1 << LOGN, TILE))) void k_y_fwd(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
+                                             int kxh, int NP, int ldp, const cpx<T>* __restrict__ tw, LayerSkip skip) {
+  __shared__ __align__(16) char tile[col_lds_bytes<T>(1 << LOGN, TILE)];
+  y_fwd_body<T, LOGN, NTL, TILE, RADIX>(tile, threadIdx.x, xcd_block(), true, in, out, kxh, NP, ldp, tw, skip);
 }
 
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
-__global__ __launch_bounds__(NT) void k_y_inv(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, int kxh,
-                                             int NP, int ldp, const cpx<T>* __restrict__ tw) {
-  __shared__ cpx<T> buf[col_lds_elems<T, LOGN, TILE>()];
-  y_inv_body<T, LOGN, NTL, TILE, RADIX>(buf, xcd_block(), in, out, kxh, NP, ldp, tw);
+__global__ __launch_bounds__((col_threads<T>(1 << LOGN, TILE))) void k_y_inv(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
+                                             int kxh, int NP, int ldp, const cpx<T>* __restrict__ tw) {
+  __shared__ __align__(16) char tile[col_lds_bytes<T>(1 << LOGN, TILE)];
+  y_inv_body<T, LOGN, NTL, TILE, RADIX>(tile, threadIdx.x, xcd_block(), true, in, out, kxh, NP, ldp, tw);
 }
 
 template <typename T, int LOGN, int TILE, int RADIX>
-__global__ __launch_bounds__(NT) void k_x_c2r(const cpx<T>* __restrict__ in, OutSegments seg, int ny, int R,
+__global__ __launch_bounds__((c2r_threads<T>(1 << LOGN, TILE))) void k_x_c2r(const cpx<T>* __restrict__ in, OutSegments seg, int ny, int R,
                                              double scale, const cpx<T>* __restrict__ tw,
                                              const double* __restrict__ padd, ResidEpilogue ep, int nts) {
   __shared__ cpx<T> buf[c2r_lds_elems<T, LOGN, TILE>()];
-  __shared__ double red[NT / 64];
+  constexpr int NTH = c2r_threads<T>(1 << LOGN, TILE);
+  __shared__ double red[NTH / 64];
   // the last planes first: the inverse column transform wrote them last
-  x_c2r_body<T, LOGN, TILE, RADIX>(buf, red, (int)(gridDim.x - 1 - blockIdx.x), in, seg, ny, R, scale, tw, padd, ep,
+  x_c2r_body<T, LOGN, TILE, RADIX, NTH>(buf, red, (int)(gridDim.x - 1 - blockIdx.x), in, seg, ny, R, scale, tw, padd, ep,
                                    nts != 0);
 }
 
@@ -163,11 +160,11 @@ struct R2CLaunch {
   template <int L, int TILE, int RADIX>
   hipError_t go() {
     const int R = rows_per_block(r2c_seq<T>(1 << L, TILE), ny);
-    const dim3 grid((unsigned)(nplanes * (size_t)ny / R));
+    const dim3 grid((unsigned)(nplanes * (size_t)ny / R)), blk(r2c_threads<T>(1 << L, TILE));
     if (stream_in)
-      hipLaunchKernelGGL((k_x_r2c<T, L, true, TILE, RADIX>), grid, dim3(NT), 0, st, seg, out, ny, R, tw, bsum, skip);
+      hipLaunchKernelGGL((k_x_r2c<T, L, true, TILE, RADIX>), grid, blk, 0, st, seg, out, ny, R, tw, bsum, skip);
     else
-      hipLaunchKernelGGL((k_x_r2c<T, L, false, TILE, RADIX>), grid, dim3(NT), 0, st, seg, out, ny, R, tw, bsum, skip);
+      hipLaunchKernelGGL((k_x_r2c<T, L, false, TILE, RADIX>), grid, blk, 0, st, seg, out, ny, R, tw, bsum, skip);
     return hipGetLastError();
   }
 };
@@ -184,18 +181,18 @@ struct ColLaunch {
   template <int L, int TILE, int RADIX>
   hipError_t go() {
     constexpr int B = col_batch<T>(1 << L, TILE);
-    const dim3 grid((unsigned)(kxh * ((NP + B - 1) / B)));
+    const dim3 grid((unsigned)(kxh * ((NP + B - 1) / B))), blk(col_threads<T>(1 << L, TILE));
     if (FWD) {
       if (stream_in)
-        hipLaunchKernelGGL((k_y_fwd<T, L, true, TILE, RADIX>), grid, dim3(NT), 0, st, in, out, kxh, NP, ldp, tw, skip);
+        hipLaunchKernelGGL((k_y_fwd<T, L, true, TILE, RADIX>), grid, blk, 0, st, in, out, kxh, NP, ldp, tw, skip);
       else
-        hipLaunchKernelGGL((k_y_fwd<T, L, false, TILE, RADIX>), grid, dim3(NT), 0, st, in, out, kxh, NP, ldp, tw,
+        hipLaunchKernelGGL((k_y_fwd<T, L, false, TILE, RADIX>), grid, blk, 0, st, in, out, kxh, NP, ldp, tw,
                            skip);
     } else {
       if (stream_in)
-        hipLaunchKernelGGL((k_y_inv<T, L, true, TILE, RADIX>), grid, dim3(NT), 0, st, in, out, kxh, NP, ldp, tw);
+        hipLaunchKernelGGL((k_y_inv<T, L, true, TILE, RADIX>), grid, blk, 0, st, in, out, kxh, NP, ldp, tw);
       else
-        hipLaunchKernelGGL((k_y_inv<T, L, false, TILE, RADIX>), grid, dim3(NT), 0, st, in, out, kxh, NP, ldp, tw);
+        hipLaunchKernelGGL((k_y_inv<T, L, false, TILE, RADIX>), grid, blk, 0, st, in, out, kxh, NP, ldp, tw);
     }
     return hipGetLastError();
   }
@@ -216,8 +213,8 @@ struct C2RLaunch {
   template <int L, int TILE, int RADIX>
   hipError_t go() {
     const int R = rows_per_block(c2r_seq<T>(1 << L, TILE), ny);
-    const dim3 grid((unsigned)(nplanes * (size_t)ny / R));
-    hipLaunchKernelGGL((k_x_c2r<T, L, TILE, RADIX>), grid, dim3(NT), 0, st, in, seg, ny, R, scale, tw, padd, ep,
+    const dim3 grid((unsigned)(nplanes * (size_t)ny / R)), blk(c2r_threads<T>(1 << L, TILE));
+    hipLaunchKernelGGL((k_x_c2r<T, L, TILE, RADIX>), grid, blk, 0, st, in, seg, ny, R, scale, tw, padd, ep,
                        stream_out ? 1 : 0);
     return hipGetLastError();
   }
@@ -242,7 +239,7 @@ int row_seq_of(int nx, FftChoice ch) {
 #undef CALL
     return hipErrorInvalidValue;
   };
-  run();
+  (void)run();
   return f.seq;
 }
 
@@ -361,9 +358,10 @@ template <typename T>
 BatchGeom<T> geom_col(int logn, int kxh, int NP) {
   BatchGeom<T> g;
   const int n = 1 << logn;
-  const int B = col_batch<T>(n, 1);
-  g.blocks = kxh * ((NP + B - 1) / B);
-  g.lds = (size_t)B * (n + 1) * sizeof(cpx<T>);
+  const int tile = col_shared_tile<T>(n);
+  const int B = col_batch<T>(n, tile), G = NT / col_threads<T>(n, tile);
+  g.blocks = (kxh * ((NP + B - 1) / B) + G - 1) / G;
+  g.lds = (size_t)G * col_lds_bytes<T>(n, tile);
   return g;
 }
 

@@ -541,3 +541,23 @@ def test_nyquist_modes_of_every_layout_and_last_block(nx, ny, nz):
             _say("nyquist", (nx, ny, nz), cfg, k, err)
             assert err <= TOL, (cfg, k, err)
     ctx.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(4, 256, 5), (8, 512, 3), (4, 2048, 3), (8, 4096, 2)])
+def test_column_passes_at_every_tile_and_precision(nx, ny, nz):
+    """Columns of two, three and four register passes with each tile choice,
+    plane counts that leave the last tile partly idle, both precisions."""
+    g = grid_dict(nx, ny, nz, 1.0, ny / 512, 0.25)     # (the oracle refuses elements thicker than |q h| = 1200)
+    e, t = filtered_eigenstrain(g, seed=nx + ny), filtered_traction(g, seed=nz + 9)
+    ref = ora.apply(g, E, NU, eps_p=e, traction=t)
+    dev = torch.device("cuda")
+    for prec, bound in (("fp64", TOL), ("fp32_refined", 2e-6)):
+        c = _ctx(g, precision=prec)
+        for ch in FFT_CHOICES:
+            c.set_fft_config([ch] * 4)
+            out = c.operator_apply(torch.from_numpy(e).to(dev), torch.from_numpy(t).to(dev), want=("strain", "surf_u3"))
+            torch.cuda.synchronize()
+            errs = [_rel(out[k].cpu().numpy(), ref[k]) for k in ("strain", "surf_u3")]
+            _say("columns", (nx, ny, nz), prec, ch, errs)
+            assert max(errs) <= bound, (prec, ch, errs)
+        c.close()
