@@ -44,6 +44,11 @@ __device__ __forceinline__ cpx<T> ld_in(const cpx<T>* p) {
   else return *p;
 }
 template <bool NT>
+__device__ __forceinline__ double ld_in(const double* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT>
 __device__ __forceinline__ double2 ld_in(const double2* p) {
   if constexpr (NT) {
     const cpx<double> v = ld_nt(reinterpret_cast<const cpx<double>*>(p));

@@ -29,22 +29,13 @@ namespace fvim {
 
 namespace {
 // ---------------------------------------------------- single-grid kernels
-template <typename T, int LOGN, int TILE>
-__host__ __device__ constexpr int r2c_lds_elems() {
-  return r2c_seq<T>(1 << LOGN, TILE) * ((1 << LOGN) + 1);
-}
-template <typename T, int LOGN, int TILE>
-__host__ __device__ constexpr int c2r_lds_elems() {
-  return c2r_seq<T>(1 << LOGN, TILE) * ((1 << LOGN) + 1);
-}
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
-__global__ __launch_bounds__((r2c_threads<T>(1 << LOGN, TILE))) void k_x_r2c(InSegments seg, cpx<T>* __restrict__ out, int ny, int R,
-                                             const cpx<T>* __restrict__ tw, double* __restrict__ bsum,
-                                             LayerSkip skip) {
-  __shared__ cpx<T> buf[r2c_lds_elems<T, LOGN, TILE>()];
-  constexpr int NTH = r2c_threads<T>(1 << LOGN, TILE);
-  __shared__ double red[NTH / 64];
-  x_r2c_body<T, LOGN, NTL, TILE, RADIX, NTH>(buf, red, blockIdx.x, seg, out, ny, R, tw, bsum, skip);
+__global__ __launch_bounds__((row_threads<T>(1 << LOGN, TILE)))
+void k_x_r2c(InSegments seg, cpx<T>* __restrict__ out, int ny, int R, const cpx<T>* __restrict__ tw,
+             double* __restrict__ bsum, LayerSkip skip) {
+  __shared__ __align__(16) char tile[row_lds_bytes<T>(1 << LOGN, TILE)];
+  __shared__ double red[row_threads<T>(1 << LOGN, TILE) / 64];
+  x_r2c_body<T, LOGN, NTL, TILE, RADIX>(tile, red, blockIdx.x, seg, out, ny, R, tw, bsum, skip);
 }
 
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
@@ -62,15 +53,14 @@ __global__ __launch_bounds__((col_threads<T>(1 << LOGN, TILE))) void k_y_inv(con
 }
 
 template <typename T, int LOGN, int TILE, int RADIX>
-__global__ __launch_bounds__((c2r_threads<T>(1 << LOGN, TILE))) void k_x_c2r(const cpx<T>* __restrict__ in, OutSegments seg, int ny, int R,
-                                             double scale, const cpx<T>* __restrict__ tw,
-                                             const double* __restrict__ padd, ResidEpilogue ep, int nts) {
-  __shared__ cpx<T> buf[c2r_lds_elems<T, LOGN, TILE>()];
-  constexpr int NTH = c2r_threads<T>(1 << LOGN, TILE);
-  __shared__ double red[NTH / 64];
+__global__ __launch_bounds__((row_threads<T>(1 << LOGN, TILE)))
+void k_x_c2r(const cpx<T>* __restrict__ in, OutSegments seg, int ny, int R, double scale,
+             const cpx<T>* __restrict__ tw, const double* __restrict__ padd, ResidEpilogue ep, int nts) {
+  __shared__ __align__(16) char tile[row_lds_bytes<T>(1 << LOGN, TILE)];
+  __shared__ double red[row_threads<T>(1 << LOGN, TILE) / 64];
   // the last planes first: the inverse column transform wrote them last
-  x_c2r_body<T, LOGN, TILE, RADIX, NTH>(buf, red, (int)(gridDim.x - 1 - blockIdx.x), in, seg, ny, R, scale, tw, padd, ep,
-                                   nts != 0);
+  x_c2r_body<T, LOGN, TILE, RADIX>(tile, red, (int)(gridDim.x - 1 - blockIdx.x), in, seg, ny, R, scale, tw, padd,
+                                   ep, nts != 0);
 }
 
 template <typename T>
@@ -102,17 +92,6 @@ int rows_per_block(int seq, int ny) { return 2 * seq < ny ? 2 * seq : ny; }
 int ilog2(int n) { return 31 - __builtin_clz((unsigned)n); }
 
 bool fft_tunable(int logn) { return logn >= FFT_TUNE_MIN_LOGN && logn <= FFT_TUNE_MAX_LOGN; }
-
-// Runtime tile -> compile-time tile of a row kernel's SEQ (or a column
-// kernel's B) for a length 2^L.
-template <typename T, int L>
-int r2c_seq_rt(int tile) {
-  return tile == 0 ? r2c_seq<T>(1 << L, 0) : (tile == 2 ? r2c_seq<T>(1 << L, 2) : r2c_seq<T>(1 << L, 1));
-}
-template <typename T, int L>
-int c2r_seq_rt(int tile) {
-  return tile == 0 ? c2r_seq<T>(1 << L, 0) : (tile == 2 ? c2r_seq<T>(1 << L, 2) : c2r_seq<T>(1 << L, 1));
-}
 
 #define FVIM_LOGN_SWITCH(logn, CALL) \
   switch (logn) {                    \
@@ -159,8 +138,8 @@ struct R2CLaunch {
   const LayerSkip& skip;
   template <int L, int TILE, int RADIX>
   hipError_t go() {
-    const int R = rows_per_block(r2c_seq<T>(1 << L, TILE), ny);
-    const dim3 grid((unsigned)(nplanes * (size_t)ny / R)), blk(r2c_threads<T>(1 << L, TILE));
+    const int R = rows_per_block(row_seq<T>(1 << L, TILE), ny);
+    const dim3 grid((unsigned)(nplanes * (size_t)ny / R)), blk(row_threads<T>(1 << L, TILE));
     if (stream_in)
       hipLaunchKernelGGL((k_x_r2c<T, L, true, TILE, RADIX>), grid, blk, 0, st, seg, out, ny, R, tw, bsum, skip);
     else
@@ -212,36 +191,13 @@ struct C2RLaunch {
   bool stream_out;
   template <int L, int TILE, int RADIX>
   hipError_t go() {
-    const int R = rows_per_block(c2r_seq<T>(1 << L, TILE), ny);
-    const dim3 grid((unsigned)(nplanes * (size_t)ny / R)), blk(c2r_threads<T>(1 << L, TILE));
+    const int R = rows_per_block(row_seq<T>(1 << L, TILE), ny);
+    const dim3 grid((unsigned)(nplanes * (size_t)ny / R)), blk(row_threads<T>(1 << L, TILE));
     hipLaunchKernelGGL((k_x_c2r<T, L, TILE, RADIX>), grid, blk, 0, st, in, seg, ny, R, scale, tw, padd, ep,
                        stream_out ? 1 : 0);
     return hipGetLastError();
   }
 };
-
-template <typename T, bool R2C>
-struct SeqOf {
-  template <int L, int TILE, int RADIX>
-  hipError_t go() {
-    seq = R2C ? r2c_seq<T>(1 << L, TILE) : c2r_seq<T>(1 << L, TILE);
-    return hipSuccess;
-  }
-  int seq = 0;
-};
-
-template <typename T, bool R2C>
-int row_seq_of(int nx, FftChoice ch) {
-  SeqOf<T, R2C> f;
-  auto run = [&]() -> hipError_t {
-#define CALL(L) return with_choice<L>(ch, f)
-    FVIM_LOGN_SWITCH(ilog2(nx), CALL)
-#undef CALL
-    return hipErrorInvalidValue;
-  };
-  (void)run();
-  return f.seq;
-}
 
 }  // namespace
 
@@ -252,7 +208,7 @@ FftChoice fft_effective(int logn, FftChoice ch) {
 
 template <typename T>
 int x_r2c_blocks_per_plane(int nx, int ny, FftChoice ch) {
-  return ny / rows_per_block(row_seq_of<T, true>(nx, fft_effective(ilog2(nx), ch)), ny);
+  return ny / rows_per_block(row_seq<T>(nx, fft_effective(ilog2(nx), ch).tile), ny);
 }
 
 template <typename T>
@@ -313,7 +269,7 @@ hipError_t launch_x_c2r(const cpx<T>* in, const OutSegments& seg, int nx, int ny
 
 template <typename T>
 int x_c2r_blocks(int nx, int ny, size_t nplanes, FftChoice ch) {
-  return (int)(nplanes * (size_t)ny / rows_per_block(row_seq_of<T, false>(nx, fft_effective(ilog2(nx), ch)), ny));
+  return (int)(nplanes * (size_t)ny / rows_per_block(row_seq<T>(nx, fft_effective(ilog2(nx), ch).tile), ny));
 }
 
 template <typename T>
@@ -335,23 +291,12 @@ struct BatchGeom {
 };
 
 template <typename T>
-BatchGeom<T> geom_r2c(int logn, int ny, int nplanes) {
+BatchGeom<T> geom_row(int logn, int ny, int nplanes) {
   BatchGeom<T> g;
   const int n = 1 << logn;
-  const int seq = r2c_seq<T>(n, 1);
-  g.R = rows_per_block(seq, ny);
+  g.R = rows_per_block(row_seq<T>(n, 3), ny);
   g.blocks = nplanes * ny / g.R;
-  g.lds = (size_t)seq * (n + 1) * sizeof(cpx<T>);
-  return g;
-}
-template <typename T>
-BatchGeom<T> geom_c2r(int logn, int ny, int nplanes) {
-  BatchGeom<T> g;
-  const int n = 1 << logn;
-  const int seq = c2r_seq<T>(n, 1);
-  g.R = rows_per_block(seq, ny);
-  g.blocks = nplanes * ny / g.R;
-  g.lds = (size_t)seq * (n + 1) * sizeof(cpx<T>);
+  g.lds = (size_t)row_lds_bytes<T>(n, 3);
   return g;
 }
 template <typename T>
@@ -377,9 +322,8 @@ size_t xform_batch_prepare(int kind, XformBatch& b) {
   b.first[0] = 0;
   for (int c = 0; c < b.n; ++c) {
     if (b.logn[c] < 2 || b.logn[c] > XFORM_BATCH_MAX_LOGN) return 0;
-    BatchGeom<T> g = kind == 0 ? geom_r2c<T>(b.logn[c], b.ny[c], b.NP[c])
-                     : kind == 3 ? geom_c2r<T>(b.logn[c], b.ny[c], b.NP[c])
-                                 : geom_col<T>(b.logn[c], b.kxh[c], b.NP[c]);
+    BatchGeom<T> g = kind == 0 || kind == 3 ? geom_row<T>(b.logn[c], b.ny[c], b.NP[c])
+                                            : geom_col<T>(b.logn[c], b.kxh[c], b.NP[c]);
     b.R[c] = g.R;
     b.first[c + 1] = b.first[c] + g.blocks;
     lds = std::max(lds, g.lds);
@@ -394,9 +338,8 @@ hipError_t launch_xform_batch(int kind, XformBatch& b, hipStream_t st) {
   b.first[0] = 0;
   for (int c = 0; c < b.n; ++c) {
     if (b.logn[c] < 2 || b.logn[c] > XFORM_BATCH_MAX_LOGN) return hipErrorInvalidValue;
-    BatchGeom<T> g = kind == 0 ? geom_r2c<T>(b.logn[c], b.ny[c], b.NP[c])
-                     : kind == 3 ? geom_c2r<T>(b.logn[c], b.ny[c], b.NP[c])
-                                 : geom_col<T>(b.logn[c], b.kxh[c], b.NP[c]);
+    BatchGeom<T> g = kind == 0 || kind == 3 ? geom_row<T>(b.logn[c], b.ny[c], b.NP[c])
+                                            : geom_col<T>(b.logn[c], b.kxh[c], b.NP[c]);
     b.R[c] = g.R;
     b.first[c + 1] = b.first[c] + g.blocks;
     lds = std::max(lds, g.lds);
@@ -415,7 +358,7 @@ hipError_t launch_xform_batch(int kind, XformBatch& b, hipStream_t st) {
 // blocks per plane of the batched x_r2c (the float32 mean-mode sums)
 template <typename T>
 int x_r2c_batch_blocks_per_plane(int nx, int ny) {
-  return ny / rows_per_block(r2c_seq<T>(nx, 1), ny);
+  return ny / rows_per_block(row_seq<T>(nx, 3), ny);
 }
 
 #define FVIM_INST(T)                                                                                            \

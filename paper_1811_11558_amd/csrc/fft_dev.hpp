@@ -1,5 +1,5 @@
-// Device code of the in-plane transforms (constants, LDS Stockham stages and
-// the row/column bodies, single-grid and batched).  Included by fft.hip and
+// Device code of the in-plane transforms (constants, register passes and the
+// row/column bodies, single-grid and batched).  Included by fft.hip and
 // persist.hip; everything is in an anonymous namespace (one copy per
 // translation unit).
 #pragma once
@@ -14,7 +14,7 @@ namespace {
 
 #ifndef FVIM_NT_DEFINED
 #define FVIM_NT_DEFINED
-constexpr int NT = 256;   // threads per block (the transforms of one grid: tile_threads)
+constexpr int NT = 256;   // threads per block of the launches over several grids
 #endif
 
 // a times the twiddle w (its conjugate for INV), with its fused operations
@@ -29,51 +29,26 @@ __device__ __forceinline__ cpx<T> turn(cpx<T> a, cpx<T> w) {
   return mk(fma_t(a.x, w.x, INV ? p : -p), fma_t(a.y, w.x, INV ? -q : q));
 }
 
-// Complex elements of one block's LDS tile in the row kernels.  TILE picks
-// half (0), the default (1) or twice (2) the default, which was chosen per
-// kernel and precision by measurement on 256^2 x 64: a smaller tile lets
-// more blocks share a CU (the forward transform gains: 16 KiB in float64),
-// a larger one gives the inverse transform's strided reads longer runs
-// (32 KiB in float64; 16 KiB in float32).  The tuner times the three.
+// TILE picks half (0), the default (1) or twice (2) the default run of a
+// transform kernel on its strided side; the tuner times the three.
 __host__ __device__ constexpr int tile_scale(int base, int tile) {
   return tile == 0 ? base / 2 : (tile == 2 ? base * 2 : base);
 }
-template <typename T>
-__host__ __device__ constexpr int r2c_tile_elems(int tile) { return tile_scale(sizeof(T) == 8 ? 1024 : 2048, tile); }
-template <typename T>
-__host__ __device__ constexpr int c2r_tile_elems(int tile) { return tile_scale(2048, tile); }
-// Row pairs per block of a row kernel (R = 2 SEQ rows of length n).  The
-// X[p][kx][y] side is touched in runs of R elements of one kx, so SEQ is the
-// tile's share but at least what gives runs of ROW_RUN bytes, as far as the
-// 160 KiB of LDS a block may use and a tile of 8192 elements (the loads of a
-// whole tile are staged in registers) allow.  (At nx = 1024 in float64 a 16 KiB
-// tile alone gives 2-row blocks, 32-byte runs and 1.5 TB/s.)
-constexpr int ROW_RUN = 128;
-__host__ __device__ constexpr int row_seq(int n, int csize, int tile) {
-  int seq = tile / n;
-  if (seq < 1) seq = 1;
-  const int minseq = ROW_RUN / (2 * csize);
-  if (seq < minseq) seq = minseq;
-  while (seq > 1 && (seq * (n + 1) * csize > 160 * 1024 || seq * n > 8192)) seq /= 2;
-  return seq;
+// Elements of a transform per thread.  16: 64 registers of float64 values.  8 up
+// to length 128: short grids are bound by the chain of one thread's loads, passes
+// and stores (64 x 64 x 16 float64 27.6 -> 25.4 us, 32 x 32 x 16 21.6 -> 19.8 us; at
+// 256 no gain).  In the columns 32 in float32 from length 1024 on (512 threads per
+// tile instead of 1024: y_fwd 833 -> 787 us at 1024^2 x 64), but not below (at 256 and
+// 512 the passes take 150 to 170 registers, two waves per SIMD: y_inv 541 against
+// 460 us at 512^2 x 128), and not in the rows (the packing has as many values again:
+// 165 to 212 registers).
+__host__ __device__ constexpr int row_elems(int n) {
+  const int v = n <= 128 ? 8 : 16;
+  return n < v ? n : v;
 }
-template <typename T>
-__host__ __device__ constexpr int r2c_seq(int n, int tile) {
-  return row_seq(n, (int)sizeof(cpx<T>), r2c_tile_elems<T>(tile));
-}
-template <typename T>
-__host__ __device__ constexpr int c2r_seq(int n, int tile) {
-  return row_seq(n, (int)sizeof(cpx<T>), c2r_tile_elems<T>(tile));
-}
-// Elements of a transform per thread of a column kernel: 64 registers of
-// float64 values.  In float32 32 values from length 1024 on (512 threads per
-// tile instead of 1024: y_fwd 833 -> 787 us at 1024^2 x 64) and 16 below (with 32
-// the passes of length 256 and 512 take 150 to 170 registers, two waves per SIMD:
-// y_inv 541 against 460 us at 512^2 x 128).
 template <typename T>
 __host__ __device__ constexpr int reg_elems(int n) {
-  const int v = sizeof(T) == 4 && n >= 1024 ? 32 : 16;
-  return n < v ? n : v;
+  return sizeof(T) == 4 && n >= 1024 ? 32 : row_elems(n);
 }
 
 // Columns (planes) per block of the column (y) kernels.  The mode-major side
@@ -105,19 +80,41 @@ __host__ __device__ constexpr int col_lds_bytes(int n, int tile) {
   return col_batch<T>(n, tile) * n * (int)sizeof(cpx<T>) / (col_split<T>(n, tile) ? 2 : 1);
 }
 
-// Threads per block of a tile of `bytes` of LDS: 8 float64 elements per thread
-// up to 1024 threads, so that a larger tile does not mean fewer waves per CU
-// (64 KiB tiles on 256 threads left 8 waves per CU and ran at 3 to 3.7 TB/s).
-__host__ __device__ constexpr int tile_threads(int bytes) {
-  return bytes > 64 * 1024 ? 1024 : (bytes > 32 * 1024 ? 512 : 256);
+// Row pairs (two rows of reals are one complex transform) per block of the row
+// (x) kernels.  The X[p][kx][y] side is touched in runs of 2 row_seq elements
+// of one kx: 128 bytes by default, as far as a block of 1024 threads allows (half
+// that: 1662 / 1619 us against 1364 / 1381 for x_fwd / x_inv at 1024^2 x 64 float64).
+// TILE 3: a block of the launches over several grids, NT threads.
+template <typename T>
+__host__ __device__ constexpr int row_seq(int n, int tile) {
+  const int m = n / row_elems(n);
+  if (tile == 3) return NT / m;
+  int s = tile_scale(128, tile) / (2 * (int)sizeof(cpx<T>));
+  while (s > 1 && s * m > 1024) s /= 2;
+  while (s * m < 64) s *= 2;            // at least one wave
+  return s;
 }
 template <typename T>
-__host__ __device__ constexpr int r2c_threads(int n, int tile) {
-  return tile_threads(r2c_seq<T>(n, tile) * n * (int)sizeof(cpx<T>));
+__host__ __device__ constexpr int row_threads(int n, int tile) {
+  return row_seq<T>(n, tile) * (n / row_elems(n));
 }
 template <typename T>
-__host__ __device__ constexpr int c2r_threads(int n, int tile) {
-  return tile_threads(c2r_seq<T>(n, tile) * n * (int)sizeof(cpx<T>));
+__host__ __device__ constexpr bool row_split(int n, int tile) {
+  return row_seq<T>(n, tile) * n * (int)sizeof(cpx<T>) > 32 * 1024;
+}
+// Row of the exchange tile: element pos at pos + pos / 16, so that the first
+// pass's writes (16 apart) spread over the banks, and row pairs so far apart that
+// the unpacking, rows fastest, does too (w elements are 256 bytes).
+template <typename T>
+__host__ __device__ constexpr int row_ld(int n, int tile) {
+  const int esz = row_split<T>(n, tile) ? (int)sizeof(T) : (int)sizeof(cpx<T>);
+  const int w = 256 / esz, len = n + n / 16, s = row_seq<T>(n, tile);
+  if (n < 4 * w) return len | 1;
+  return (len + w - 1) / w * w + (s < w ? w / s : 1);
+}
+template <typename T>
+__host__ __device__ constexpr int row_lds_bytes(int n, int tile) {
+  return row_seq<T>(n, tile) * row_ld<T>(n, tile) * (int)(row_split<T>(n, tile) ? sizeof(T) : sizeof(cpx<T>));
 }
 __host__ __device__ constexpr int ilog2c(int n) { return n <= 1 ? 0 : 1 + ilog2c(n / 2); }
 
@@ -167,88 +164,6 @@ __device__ __forceinline__ void butterfly(cpx<T>* a) {
   }
 }
 
-// One self-sorting (Stockham) radix-R stage of NB transforms of length
-// N = 2^LOGN held at buf[b * ld + k] (NB <= NBMAX), for sub-transforms of
-// length ns = 2^LS: butterfly j of a transform takes elements j + m N/R,
-// turned by w^(m k N/(R ns)) with k = j mod ns, and writes them to
-// (j / ns) ns R + k + m ns.  Called by all NTH threads.
-template <typename T, int LOGN, int NBMAX, bool INV, int R, int LS, int NTH>
-__device__ __forceinline__ void stockham_stage(cpx<T>* buf, int ld, int NB, const cpx<T>* __restrict__ tw) {
-  constexpr int N = 1 << LOGN;
-  constexpr int LR = ilog2c(R);
-  constexpr int M = N / R;
-  constexpr int ns = 1 << LS;
-  constexpr int tstep = M >> LS;
-  constexpr int MB = (NBMAX * M + NTH - 1) / NTH;
-  const int tid = threadIdx.x;
-  const int nb = NB * M;
-  cpx<T> v[MB][R];
-#pragma unroll
-  for (int u = 0; u < MB; ++u) {
-    const int j = tid + u * NTH;
-    if (j < nb) {
-      const int b = j >> (LOGN - LR), jj = j & (M - 1);
-      const cpx<T>* src = buf + b * ld + jj;
-#pragma unroll
-      for (int m = 0; m < R; ++m) v[u][m] = src[m * M];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < MB; ++u) {
-    const int j = tid + u * NTH;
-    if (j < nb) {
-      const int b = j >> (LOGN - LR), jj = j & (M - 1);
-      const int k = jj & (ns - 1);
-      if constexpr (LS > 0) {
-#pragma unroll
-        for (int m = 1; m < R; ++m) v[u][m] = turn<INV>(v[u][m], tw[m * k * tstep]);
-      }
-      butterfly<T, R, INV>(v[u]);
-      const int o = b * ld + ((jj >> LS) << (LS + LR)) + k;
-#pragma unroll
-      for (int m = 0; m < R; ++m) buf[o + m * ns] = v[u][m];
-    }
-  }
-  __syncthreads();
-}
-
-template <typename T, int LOGN, int NBMAX, bool INV, int R, int LS, int NTH>
-__device__ __forceinline__ void stockham_from(cpx<T>* buf, int ld, int NB, const cpx<T>* __restrict__ tw) {
-  if constexpr (LS < LOGN) {
-    stockham_stage<T, LOGN, NBMAX, INV, R, LS, NTH>(buf, ld, NB, tw);
-    stockham_from<T, LOGN, NBMAX, INV, R, LS + ilog2c(R), NTH>(buf, ld, NB, tw);
-  }
-}
-
-// NB transforms of length N = 2^LOGN held at buf[b * ld + k] (NB <= NBMAX),
-// Stockham autosort.  RADIX 4: one radix-2 stage first when LOGN is odd,
-// then radix-4 stages; RADIX 8: one radix-2 or radix-4 stage first when
-// LOGN mod 3 is 1 or 2, then radix-8 stages.  All index arithmetic is shifts
-// and masks.  Called by all NTH threads.
-template <typename T, int LOGN, int NBMAX, bool INV, int RADIX, int NTH>
-__device__ __forceinline__ void lds_fft(cpx<T>* buf, int ld, int NB, const cpx<T>* __restrict__ tw) {
-  if constexpr (RADIX == 4) {
-    if constexpr (LOGN & 1) {
-      stockham_stage<T, LOGN, NBMAX, INV, 2, 0, NTH>(buf, ld, NB, tw);
-      stockham_from<T, LOGN, NBMAX, INV, 4, 1, NTH>(buf, ld, NB, tw);
-    } else {
-      stockham_from<T, LOGN, NBMAX, INV, 4, 0, NTH>(buf, ld, NB, tw);
-    }
-  } else {
-    static_assert(RADIX == 8, "radix 4 or 8");
-    if constexpr (LOGN % 3 == 1) {
-      stockham_stage<T, LOGN, NBMAX, INV, 2, 0, NTH>(buf, ld, NB, tw);
-      stockham_from<T, LOGN, NBMAX, INV, 8, 1, NTH>(buf, ld, NB, tw);
-    } else if constexpr (LOGN % 3 == 2) {
-      stockham_stage<T, LOGN, NBMAX, INV, 4, 0, NTH>(buf, ld, NB, tw);
-      stockham_from<T, LOGN, NBMAX, INV, 8, 2, NTH>(buf, ld, NB, tw);
-    } else {
-      stockham_from<T, LOGN, NBMAX, INV, 8, 0, NTH>(buf, ld, NB, tw);
-    }
-  }
-}
-
 // Sum of v over the block (fixed order: waves by shuffles, then the waves in
 // turn); red: NTH / 64 doubles of LDS.  Every thread gets the total.
 template <int NTH>
@@ -268,10 +183,11 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // A transform as few passes over registers: a thread holds V elements of its
 // sequence, positions t + e M (M = N / V threads per sequence), and runs as many
 // consecutive Stockham stages on them as their radices' product (at most V)
-// allows, so that only the passes, not the stages, exchange through LDS.  Each
-// stage does the same operations on the same values as stockham_stage.
+// allows, so that only the passes, not the stages, exchange through LDS.
 //
-// Stages of radices R1, Rest... from sub-transforms of length 2^LS on: the Rg
+// A Stockham stage of radix R for sub-transforms of length ns takes elements
+// j + m N/R (m < R), turned by w^(m k N/(R ns)) with k = j mod ns, and writes its
+// butterfly's results to (j / ns) ns R + k + m ns.  Stages of radices R1, Rest... from sub-transforms of length 2^LS on: the Rg
 // values at positions tt + c N / Rg give outputs idx at positions
 // (tt / ns) Rg ns + k + idx ns, k = tt mod ns, ns = 2^LS.  The first stage's
 // butterfly over m of v[m2 + m S] (S = Rg / R1) yields the inputs of R1
@@ -317,8 +233,9 @@ __host__ __device__ constexpr int group_index(int reg, Radices<R1, Rest...>) {
   else return reg / S + R1 * group_index(reg % S, Radices<Rest...>{});
 }
 
-// The stages of a length-2^LOGN transform in lds_fft's order, from the one at
-// sub-length 2^LS on.
+// The stages of a length-2^LOGN transform from sub-length 2^LS on.  RADIX 4: one
+// radix-2 stage first when LOGN is odd, then radix 4; RADIX 8: one radix-2 or
+// radix-4 stage first when LOGN mod 3 is 1 or 2, then radix 8.
 template <int LOGN, int RADIX>
 __host__ __device__ constexpr int stage_radix(int ls) {
   if (ls > 0) return RADIX;
@@ -410,15 +327,16 @@ __device__ __forceinline__ void reg_fft(cpx<T> (&v)[V], int t0, L0 lds0, int t1,
 // X[(plane * kxh + k) * ny + y].
 // If bsum is not NULL, block lb also writes the float64 sum of its R rows to
 // bsum[lb] (the plane means of the mean mode are then formed in float64).
-template <typename T, int LOGN, bool NTL, int TILE, int RADIX, int NTH>
-__device__ __forceinline__ void x_r2c_body(cpx<T>* buf, double* red, int lb, const InSegments& seg,
+template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
+__device__ __forceinline__ void x_r2c_body(char* tile, double* red, int lb, const InSegments& seg,
                                            cpx<T>* __restrict__ out, int ny, int R,
                                            const cpx<T>* __restrict__ tw, double* __restrict__ bsum,
                                            const LayerSkip& skip) {
-  constexpr int N = 1 << LOGN;
-  constexpr int SEQ = r2c_seq<T>(N, TILE);
-  constexpr int ld = N + 1;
+  constexpr int N = 1 << LOGN, V = row_elems(N), M = N / V;
+  constexpr int SEQ = row_seq<T>(N, TILE), NTH = row_threads<T>(N, TILE), ld = row_ld<T>(N, TILE);
+  constexpr bool SPLIT = row_split<T>(N, TILE);
   constexpr int kxh = N / 2 + 1;
+  using E = std::conditional_t<SPLIT, T, cpx<T>>;
   const size_t row0 = (size_t)lb * R;
   const size_t plane = row0 / ny;
   const int y0 = (int)(row0 - plane * ny);
@@ -429,48 +347,71 @@ __device__ __forceinline__ void x_r2c_body(cpx<T>* buf, double* red, int lb, con
   }
   const int sg = (seg.n > 1 && (int)plane >= seg.first[1]) ? 1 : 0;
   const double* in = seg.ptr[sg] + ((plane - seg.first[sg]) * ny + y0) * (size_t)N;
-  // 16-byte loads: two consecutive x of one row
-  constexpr int MV = (2 * SEQ * N / 2 + NTH - 1) / NTH;
-  const int tot = R * N / 2;
-  const double2* src = reinterpret_cast<const double2*>(in);
-  double2 v[MV];
+  // threads of a row pair in x order; those past the last pair repeat it (never
+  // stored), so every load is unconditional
+  const int s = (int)threadIdx.x / M, t = (int)threadIdx.x % M, hp = R / 2;
+  const double* r0 = in + (size_t)(2 * min(s, hp - 1)) * N + t;
+  double a[V], b[V];
 #pragma unroll
-  for (int u = 0; u < MV; ++u) {
-    int i = threadIdx.x + u * NTH;
-    if (i < tot) v[u] = ld_in<NTL>(src + i);
+  for (int e = 0; e < V; ++e) {
+    a[e] = ld_in<NTL>(r0 + e * M);
+    b[e] = ld_in<NTL>(r0 + N + e * M);
   }
+  cpx<T> v[V];
 #pragma unroll
-  for (int u = 0; u < MV; ++u) {
-    int i = threadIdx.x + u * NTH;
-    if (i < tot) {
-      int r = (2 * i) >> LOGN, x = (2 * i) & (N - 1);
-      cpx<T>* d = buf + (r >> 1) * ld + x;
-      if (r & 1) { d[0].y = (T)v[u].x; d[1].y = (T)v[u].y; }
-      else { d[0].x = (T)v[u].x; d[1].x = (T)v[u].y; }
-    }
-  }
+  for (int e = 0; e < V; ++e) v[e] = mk((T)a[e], (T)b[e]);
   if (bsum) {
     double acc = 0.0;
 #pragma unroll
-    for (int u = 0; u < MV; ++u) {
-      int i = threadIdx.x + u * NTH;
-      if (i < tot) acc += v[u].x + v[u].y;
-    }
-    acc = block_sum<NTH>(acc, red);
+    for (int e = 0; e < V; ++e) acc += a[e] + b[e];
+    acc = block_sum<NTH>(s < hp ? acc : 0.0, red);
     if (threadIdx.x == 0) bsum[lb] = acc;
   }
-  __syncthreads();
-  lds_fft<T, LOGN, SEQ, false, RADIX, NTH>(buf, ld, R / 2, tw);
-  const int tot2 = kxh * R;
-  for (int i = threadIdx.x; i < tot2; i += NTH) {
-    int k = i / R, yl = i - k * R;
-    int p = yl >> 1;
-    cpx<T> Z = buf[p * ld + k];
-    cpx<T> Zc = buf[p * ld + ((N - k) & (N - 1))];
-    cpx<T> X;
-    if ((yl & 1) == 0) X = mk(T(0.5) * (Z.x + Zc.x), T(0.5) * (Z.y - Zc.y));
-    else X = mk(T(0.5) * (Z.y + Zc.y), T(0.5) * (Zc.x - Z.x));
-    out[(plane * kxh + k) * ny + y0 + yl] = X;
+  E* lds = reinterpret_cast<E*>(tile);
+  auto at = [lds](int q, int pos) { return lds + q * ld + pos + (pos >> 4); };
+  auto mine = [at, s](int pos) { return at(s, pos); };
+  reg_fft<T, LOGN, false, RADIX, V, 0, SPLIT>(v, t, mine, t, mine, tw);
+  // X of the two rows from Z[k] and Z[N - k], rows fastest
+  const int lr = __builtin_ctz(R), tot = kxh * R;
+  cpx<T>* dst = out + plane * kxh * ny + y0;
+  constexpr int MO = (kxh * 2 * SEQ + NTH - 1) / NTH;
+  if constexpr (M > 1) __syncthreads();              // the last exchange has been read
+  if constexpr (SPLIT) {
+    T zx[MO], cx[MO];
+#pragma unroll
+    for (int e = 0; e < V; ++e) *mine(t + e * M) = v[e].x;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < MO; ++u) {
+      const int i = min((int)threadIdx.x + u * NTH, tot - 1);
+      const int k = i >> lr, p = (i & (R - 1)) >> 1;
+      zx[u] = *at(p, k);
+      cx[u] = *at(p, (N - k) & (N - 1));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < V; ++e) *mine(t + e * M) = v[e].y;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < MO; ++u) {
+      const int i = (int)threadIdx.x + u * NTH;
+      if (i < tot) {
+        const int k = i >> lr, y = i & (R - 1);
+        const T zy = *at(y >> 1, k), cy = *at(y >> 1, (N - k) & (N - 1));
+        dst[(size_t)k * ny + y] = (y & 1) == 0 ? mk(T(0.5) * (zx[u] + cx[u]), T(0.5) * (zy - cy))
+                                               : mk(T(0.5) * (zy + cy), T(0.5) * (cx[u] - zx[u]));
+      }
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < V; ++e) *mine(t + e * M) = v[e];
+    __syncthreads();
+    for (int i = threadIdx.x; i < tot; i += NTH) {
+      const int k = i >> lr, y = i & (R - 1);
+      const cpx<T> Z = *at(y >> 1, k), Zc = *at(y >> 1, (N - k) & (N - 1));
+      dst[(size_t)k * ny + y] = (y & 1) == 0 ? mk(T(0.5) * (Z.x + Zc.x), T(0.5) * (Z.y - Zc.y))
+                                             : mk(T(0.5) * (Z.y + Zc.y), T(0.5) * (Zc.x - Z.x));
+    }
   }
 }
 
@@ -576,16 +517,17 @@ __device__ __forceinline__ void y_inv_body(char* tile, int tid, int lb, bool liv
 // If padd is not NULL, padd[plane] (float64) is added to every output value
 // of that plane (the mean mode computed in float64).  nts: the outputs
 // (without the epilogue) are stored as streaming writes.
-template <typename T, int LOGN, int TILE, int RADIX, int NTH>
-__device__ __forceinline__ void x_c2r_body(cpx<T>* buf, double* red, int lb, const cpx<T>* __restrict__ in,
+template <typename T, int LOGN, int TILE, int RADIX>
+__device__ __forceinline__ void x_c2r_body(char* tile, double* red, int lb, const cpx<T>* __restrict__ in,
                                            const OutSegments& seg, int ny, int R, double scale,
                                            const cpx<T>* __restrict__ tw, const double* __restrict__ padd,
                                            const ResidEpilogue& ep, bool nts) {
-  constexpr int N = 1 << LOGN;
-  constexpr int SEQ = c2r_seq<T>(N, TILE);
-  constexpr int ld = N + 1;
+  constexpr int N = 1 << LOGN, V = row_elems(N), M = N / V;
+  constexpr int SEQ = row_seq<T>(N, TILE), NTH = row_threads<T>(N, TILE), ld = row_ld<T>(N, TILE);
+  constexpr bool SPLIT = row_split<T>(N, TILE);
   constexpr int kxh = N / 2 + 1;
   constexpr int nyq = N / 2;
+  using E = std::conditional_t<SPLIT, T, cpx<T>>;
   const int hp = R / 2;                  // a power of two (R = ny or 2 SEQ)
   const int lr = __builtin_ctz(R);
   // one element per lane, consecutive lanes on consecutive rows y of one kx
@@ -599,96 +541,107 @@ __device__ __forceinline__ void x_c2r_body(cpx<T>* buf, double* red, int lb, con
   const size_t row0 = (size_t)lb * R;
   const int plane = (int)(row0 / ny);
   const int y0 = (int)(row0 - (size_t)plane * ny);
-  cpx<T> v[MV];
+  cpx<T> w[MV];
   {
     const cpx<T>* src = in + (size_t)plane * kxh * ny + y0;
 #pragma unroll
     for (int u = 0; u < MV; ++u) {
       const int i = min((int)threadIdx.x + u * NTH, last);
       const int k = i >> lr, y = i & (R - 1);
-      v[u] = src[(size_t)k * ny + y];
+      w[u] = src[(size_t)k * ny + y];
     }
   }
-  {
+  E* lds = reinterpret_cast<E*>(tile);
+  auto at = [lds](int q, int pos) { return lds + q * ld + pos + (pos >> 4); };
+  const int s = (int)threadIdx.x / M, t = (int)threadIdx.x % M;
+  auto mine = [at, s](int pos) { return at(s, pos); };
+  // Z = X0 + i X1 at k (even lanes) and N - k (odd lanes)
 #pragma unroll
-    for (int u = 0; u < MV; ++u) {
-      const int i = min((int)threadIdx.x + u * NTH, last);
-      const int k = i >> lr, pr = (i & (R - 1)) >> 1;
-      const cpx<T> o = dpp_move<DPP_SWAP1>(v[u]);
-      const cpx<T> X0 = odd ? o : v[u], X1 = odd ? v[u] : o;
-      if (k == 0 || k == nyq) {
-        if (!odd) buf[pr * ld + k] = mk(X0.x, X1.x);
-      } else if (!odd) {
-        buf[pr * ld + k] = mk(X0.x - X1.y, X0.y + X1.x);
-      } else {
-        buf[pr * ld + N - k] = mk(X0.x + X1.y, X1.x - X0.y);
+  for (int u = 0; u < MV; ++u) {
+    const int k = min((int)threadIdx.x + u * NTH, last) >> lr;
+    const cpx<T> o = dpp_move<DPP_SWAP1>(w[u]);
+    const cpx<T> X0 = odd ? o : w[u], X1 = odd ? w[u] : o;
+    if (k == 0 || k == nyq) w[u] = mk(X0.x, X1.x);
+    else if (!odd) w[u] = mk(X0.x - X1.y, X0.y + X1.x);
+    else w[u] = mk(X0.x + X1.y, X1.x - X0.y);
+  }
+  auto place = [&](int u) {              // (both lanes write a pair's k = 0, nx/2: the same value)
+    const int i = min((int)threadIdx.x + u * NTH, last);
+    const int k = i >> lr;
+    return at((i & (R - 1)) >> 1, odd ? (N - k) & (N - 1) : k);
+  };
+  cpx<T> v[V];
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int u = 0; u < MV; ++u) *place(u) = w[u].x;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e].x = *mine(t + e * M);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < MV; ++u) *place(u) = w[u].y;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e].y = *mine(t + e * M);
+  } else {
+#pragma unroll
+    for (int u = 0; u < MV; ++u) *place(u) = w[u];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = *mine(t + e * M);
+  }
+  if constexpr (M > 1) __syncthreads();
+  reg_fft<T, LOGN, true, RADIX, V, 0, SPLIT>(v, t, mine, t, mine, tw);
+  int sg = 0;
+  while (sg + 1 < seg.n && plane >= seg.first[sg + 1]) ++sg;
+  const bool live = s < hp;
+  const size_t at0 = (size_t)(2 * min(s, hp - 1)) * N + t;
+  double* dst = seg.ptr[sg] + ((size_t)(plane - seg.first[sg]) * ny + y0) * N + at0;
+  const double add = padd ? padd[plane] : 0.0;
+  if (!ep.x) {
+    // the real parts are row 2 s, the imaginary parts row 2 s + 1.  The
+    // operator's outputs are not read again by the operator, so they are stored
+    // as streaming (non-temporal) writes, which do not displace the spectrum
+    // buffers from the last-level cache -- where a wave writes whole lines.
+    if (live) {
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const double o0 = (double)v[e].x * scale + add, o1 = (double)v[e].y * scale + add;
+        if (M >= 16 && nts) {
+          __builtin_nontemporal_store(o0, dst + e * M);
+          __builtin_nontemporal_store(o1, dst + N + e * M);
+        } else {
+          dst[e * M] = o0;
+          dst[N + e * M] = o1;
+        }
       }
     }
-    __syncthreads();
-    lds_fft<T, LOGN, SEQ, true, RADIX, NTH>(buf, ld, hp, tw);
-    int s = 0;
-    while (s + 1 < seg.n && plane >= seg.first[s + 1]) ++s;
-    double* dst = seg.ptr[s] + ((size_t)(plane - seg.first[s]) * ny + y0) * N;
-    const double add = padd ? padd[plane] : 0.0;
-    typedef double v2d __attribute__((ext_vector_type(2)));
-    if (!ep.x) {
-      // Each thread stores one x pair of a row pair: the real parts of the
-      // two LDS elements it reads go to row 2 pr, their imaginary parts to
-      // row 2 pr + 1.  The operator's outputs are not read again by the
-      // operator, so they are stored as streaming (non-temporal) writes,
-      // which do not displace the spectrum buffers from the last-level
-      // cache.
-      const int tot4 = hp * (N / 2);
-      for (int i = threadIdx.x; i < tot4; i += NTH) {
-        const int pr = (2 * i) >> LOGN, x = (2 * i) & (N - 1);
-        const cpx<T>* b = buf + pr * ld + x;
-        const cpx<T> b0 = b[0], b1 = b[1];
-        v2d o0, o1;
-        o0.x = (double)b0.x * scale + add;
-        o0.y = (double)b1.x * scale + add;
-        o1.x = (double)b0.y * scale + add;
-        o1.y = (double)b1.y * scale + add;
-        v2d* q0 = reinterpret_cast<v2d*>(dst) + (size_t)(2 * pr) * (N / 2) + (x >> 1);
-        v2d* q1 = q0 + (N / 2);
-        if (nts) {
-          __builtin_nontemporal_store(o0, q0);
-          __builtin_nontemporal_store(o1, q1);
-        } else {
-          *q0 = o0;
-          *q1 = o1;
+  } else {
+    // residual epilogue (the residual is the first and only segment)
+    const size_t off = ((size_t)plane * ny + y0) * N + at0;
+    double s0 = 0.0, s1 = 0.0;
+    if (live) {
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const size_t i0 = off + e * M, i1 = i0 + N;
+        const double ra = ep.x[i0] - ((double)v[e].x * scale + add);
+        const double rb = ep.x[i1] - ((double)v[e].y * scale + add);
+        dst[e * M] = ra;
+        dst[N + e * M] = rb;
+        s0 += ra * ra + rb * rb;
+        if (ep.Fo) {
+          const double fa = ep.Fo[i0], fb = ep.Fo[i1];
+          s1 += fa * (ra - fa) + fb * (rb - fb);
         }
       }
-    } else {
-      // residual epilogue (the residual is the first and only segment)
-      const int tot2 = R * N / 2;
-      double2* d2 = reinterpret_cast<double2*>(dst);
-      const size_t off = ((size_t)plane * ny + y0) * N;
-      const double2* x2 = reinterpret_cast<const double2*>(ep.x + off);
-      const double2* f2 = ep.Fo ? reinterpret_cast<const double2*>(ep.Fo + off) : nullptr;
-      double s0 = 0.0, s1 = 0.0;
-      for (int i = threadIdx.x; i < tot2; i += NTH) {
-        int r = (2 * i) >> LOGN, x = (2 * i) & (N - 1);
-        const cpx<T>* b = buf + (r >> 1) * ld + x;
-        double2 o;
-        if (r & 1) { o.x = (double)b[0].y * scale + add; o.y = (double)b[1].y * scale + add; }
-        else { o.x = (double)b[0].x * scale + add; o.y = (double)b[1].x * scale + add; }
-        const double2 xv = x2[i];
-        const double2 rr = make_double2(xv.x - o.x, xv.y - o.y);
-        d2[i] = rr;
-        s0 += rr.x * rr.x + rr.y * rr.y;
-        if (f2) {
-          const double2 f = f2[i];
-          s1 += f.x * (rr.x - f.x) + f.y * (rr.y - f.y);
-        }
-      }
-      const double a = block_sum<NTH>(s0, red);
-      const double c = block_sum<NTH>(s1, red);
-      if (threadIdx.x == 0) {
-        const int cp = plane / ep.nz, z = plane - cp * ep.nz;
-        const double wt = (cp < 3 ? 1.0 : 2.0) * (ep.wz ? ep.wz[z] : ((z == 0 || z == ep.nz - 1) ? 0.5 : 1.0));
-        ep.part[2 * lb] = wt * a;
-        ep.part[2 * lb + 1] = wt * c;
-      }
+    }
+    const double a = block_sum<NTH>(s0, red);
+    const double c = block_sum<NTH>(s1, red);
+    if (threadIdx.x == 0) {
+      const int cp = plane / ep.nz, z = plane - cp * ep.nz;
+      const double wt = (cp < 3 ? 1.0 : 2.0) * (ep.wz ? ep.wz[z] : ((z == 0 || z == ep.nz - 1) ? 0.5 : 1.0));
+      ep.part[2 * lb] = wt * a;
+      ep.part[2 * lb + 1] = wt * c;
     }
   }
 }
@@ -750,10 +703,10 @@ template <typename T>
 __device__ __forceinline__ void x_r2c_batch_block(const XformBatch& b, int blk, double* red) {
   const int c = batch_grid(b, blk);
   const int lb = blk - b.first[c];
-  cpx<T>* buf = reinterpret_cast<cpx<T>*>(fvim_dyn_lds);
+  char* tile = reinterpret_cast<char*>(fvim_dyn_lds);
   cpx<T>* out = static_cast<cpx<T>*>(b.out[c]);
   const cpx<T>* tw = static_cast<const cpx<T>*>(b.tw[c]);
-#define CALL(L) x_r2c_body<T, L, false, 1, 4, NT>(buf, red, lb, b.iseg[c], out, b.ny[c], b.R[c], tw, b.bsum[c], LayerSkip{})
+#define CALL(L) x_r2c_body<T, L, false, 3, 4>(tile, red, lb, b.iseg[c], out, b.ny[c], b.R[c], tw, b.bsum[c], LayerSkip{})
   FVIM_BATCH_LOGN_SWITCH(b.logn[c], CALL)
 #undef CALL
 }
@@ -796,11 +749,11 @@ template <typename T>
 __device__ __forceinline__ void x_c2r_batch_block(const XformBatch& b, int blk, double* red) {
   const int c = batch_grid(b, blk);
   const int lb = blk - b.first[c];
-  cpx<T>* buf = reinterpret_cast<cpx<T>*>(fvim_dyn_lds);
+  char* tile = reinterpret_cast<char*>(fvim_dyn_lds);
   const cpx<T>* in = static_cast<const cpx<T>*>(b.in[c]);
   const cpx<T>* tw = static_cast<const cpx<T>*>(b.tw[c]);
 #define CALL(L) \
-  x_c2r_body<T, L, 1, 4, NT>(buf, red, lb, in, b.oseg[c], b.ny[c], b.R[c], 1.0, tw, b.padd[c], ResidEpilogue{}, \
+  x_c2r_body<T, L, 3, 4>(tile, red, lb, in, b.oseg[c], b.ny[c], b.R[c], 1.0, tw, b.padd[c], ResidEpilogue{}, \
                          b.nts[c] != 0)
   FVIM_BATCH_LOGN_SWITCH(b.logn[c], CALL)
 #undef CALL
