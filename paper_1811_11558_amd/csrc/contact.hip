@@ -454,6 +454,216 @@ __global__ __launch_bounds__(GT) void k_pk_err(const double* __restrict__ part, 
   }
 }
 
+// ---------------------------------------------------- one-workgroup iteration
+// Small surfaces (16 to 64 points a side) by one workgroup: every thread keeps its
+// row pair's p, g, t and h in registers and the half spectrum X is in LDS (34 KiB
+// at 64 x 64), so an iteration has barriers where the launches above have kernel
+// boundaries, and the convergence test is in the loop.  Bound by that chain of
+// barriers (about 45 per iteration) and, at 64 x 64, by one CU's LDS.  us per
+// iteration of a solve to 1e-12, launches with a test on the host after each
+// iteration -> one workgroup: 16^2 39.5 -> 6.2, 64 x 16 40.5 -> 8.9, 32^2 41.0 -> 10.9,
+// 64^2 42.2 -> 20.9.  (128^2 does not fit the LDS; its launches take 28.6.)
+template <int LX, int LY>
+struct Solo {
+  static constexpr int NX = 1 << LX, NY = 1 << LY, KXH = NX / 2 + 1;
+  static constexpr int NTH = NX * NY / 8 < 64 ? 64 : NX * NY / 8, NW = NTH / 64;
+  static constexpr int WT = 2 * (Surf<LX>::TILE > Surf<LY>::TILE ? Surf<LX>::TILE : Surf<LY>::TILE);
+  static constexpr int COLS = NW * Surf<LY>::SEQ;    // columns transformed at a time
+  static constexpr int PASSES = (KXH + COLS - 1) / COLS;
+};
+
+template <int LX, int LY>
+__global__ __launch_bounds__((Solo<LX, LY>::NTH)) void k_pk_solo(PkBufs a, int count, double tol, int first,
+                                                              int last) {
+  using C = Solo<LX, LY>;
+  using SX = Surf<LX>;
+  using SY = Surf<LY>;
+  constexpr int NW = C::NW, KXH = C::KXH;
+  __shared__ cpx<double> X[C::NY * KXH];
+  __shared__ cpx<double> tiles[NW * C::WT];
+  __shared__ double sh[4 * NW];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  cpx<double>* buf = tiles + wave * C::WT;           // each wave's sequences have tiles of their own
+  Pair q;
+  q.b = lane / SX::M;
+  q.jj = lane & (SX::M - 1);
+  q.s = wave * SX::SEQ + q.b;
+  q.on = 2 * q.s < C::NY;
+  q.off = (size_t)2 * q.s * C::NX;
+  cpx<double>* Xa = X + (q.on ? 2 * q.s * KXH : 0);
+  cpx<double>* Xb = Xa + KXH;
+  const int cb = lane / SY::M, cj = lane & (SY::M - 1);
+  SurfTw<LX> tx;
+  SurfTw<LY> ty;
+  surf_load_tw<LX>(a.twx, q.jj, tx);
+  surf_load_tw<LY>(a.twy, cj, ty);
+  double mult[C::PASSES][4];
+  {
+    const double twopi = 6.283185307179586476925286766559;
+    const double fac = 2.0 / a.estar / ((double)C::NX * C::NY);
+#pragma unroll
+    for (int u = 0; u < C::PASSES; ++u) {
+      const int kx = u * C::COLS + wave * SY::SEQ + cb;
+      const double q1 = twopi * kx / a.lx;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int ky = cj + m * SY::M;
+        const int k2 = (ky * 2 <= C::NY) ? ky : ky - C::NY;
+        const double q2 = twopi * k2 / a.ly;
+        mult[u][m] = (kx == 0 && ky == 0) ? 0.0 : fac / sqrt(q1 * q1 + q2 * q2);
+      }
+    }
+  }
+  // v <- M[v]
+  auto comply = [&](cpx<double> (&v)[1][4]) {
+    __syncthreads();                                 // the last call's tiles have been read
+    surf_fft<LX, false, 1>(v, buf, 0, q.b, q.jj, tx);
+    surf_store_spectra<LX>(v[0], buf + (surf_last<LX>(0) ^ 1) * SX::TILE, q.b, q.jj, q.on, Xa, Xb);
+#pragma unroll
+    for (int u = 0; u < C::PASSES; ++u) {
+      __syncthreads();
+      const int kx = u * C::COLS + wave * SY::SEQ + cb;
+      const bool on = kx < KXH;
+      cpx<double> z[1][4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) z[0][m] = on ? X[(cj + m * SY::M) * KXH + kx] : zero<double>();
+      surf_fft<LY, false, 1>(z, buf, 0, cb, cj, ty);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) z[0][m] = scl(z[0][m], mult[u][m]);
+      surf_fft<LY, true, 1>(z, buf, surf_last<LY>(0) ^ 1, cb, cj, ty);
+      if (on) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) X[(cj + m * SY::M) * KXH + kx] = z[0][m];
+      }
+    }
+    __syncthreads();
+    surf_load_inverse<LX>(v, buf, q.b, q.jj, q.on, Xa, Xb, tx);
+  };
+  cpx<double> p[4], g[4], t[4], h[4], v[1][4];
+  load_pair<LX>(a.p, q, p);
+  load_pair<LX>(a.h, q, h);
+  double dp = 0.0, o[3];
+  // the sums over the contact set of the gap: sum |p - p_old|, sum g, points
+  auto gap_sums = [&]() {
+    double s[3] = {dp, 0.0, 0.0};
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      if (p[m].x > 0.0) { s[1] += g[m].x; s[2] += 1.0; }
+      if (p[m].y > 0.0) { s[1] += g[m].y; s[2] += 1.0; }
+    }
+    surf_sums<3, NW>(s, sh, o);
+  };
+  double delta = 0.0, gold = 1.0;
+  if (first) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      t[m] = zero<double>();
+      v[0][m] = p[m];
+    }
+    comply(v);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) g[m] = sub(v[0][m], h[m]);
+  } else {
+    load_pair<LX>(a.g, q, g);
+    load_pair<LX>(a.t, q, t);
+    delta = a.sc[S_DELTA];
+    gold = a.sc[S_GOLD];
+  }
+  const double W = a.sc[S_W], dA = a.sc[S_DA], tau0 = a.sc[S_TAU0];
+  gap_sums();
+  double err = 0.0;
+  int it = 0;
+  bool stop = false;
+  while (it < count && !stop) {                      // (uniform: every thread has the same sums)
+    ++it;
+    // direction (k_pk_dir)
+    const double cnt = o[2], gbar = cnt > 0.0 ? o[1] / cnt : 0.0;
+    double c2[2] = {0.0, 0.0}, e[2];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const double dx = g[m].x - gbar, dy = g[m].y - gbar;
+      if (p[m].x > 0.0) { c2[0] += dx * dx; c2[1] += dx; }
+      if (p[m].y > 0.0) { c2[0] += dy * dy; c2[1] += dy; }
+    }
+    surf_sums<2, NW>(c2, sh, e);
+    const double glo = cnt > 0.0 ? e[1] / cnt : 0.0;
+    const double G = e[0] - e[1] * glo;
+    const double beta = gold > 0.0 ? delta * G / gold : 0.0;
+    gold = G;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      t[m].x = p[m].x > 0.0 ? g[m].x - gbar - glo + (beta != 0.0 ? beta * t[m].x : 0.0) : 0.0;
+      t[m].y = p[m].y > 0.0 ? g[m].y - gbar - glo + (beta != 0.0 ? beta * t[m].y : 0.0) : 0.0;
+      v[0][m] = t[m];
+    }
+    comply(v);
+    // step (k_pk_curv, k_pk_update)
+    double s4[4] = {0.0, 0.0, 0.0, 0.0}, r[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      if (p[m].x > 0.0) { s4[0] += (g[m].x - gbar - glo) * t[m].x; s4[1] += v[0][m].x; s4[2] += t[m].x; }
+      if (p[m].y > 0.0) { s4[0] += (g[m].y - gbar - glo) * t[m].y; s4[1] += v[0][m].y; s4[2] += t[m].y; }
+    }
+    surf_sums<4, NW>(s4, sh, r);
+    const double rbar = cnt > 0.0 ? r[1] / cnt : 0.0, tbar = cnt > 0.0 ? r[2] / cnt : 0.0;
+    double c1[1] = {0.0}, den[1];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      if (p[m].x > 0.0) c1[0] += (v[0][m].x - rbar) * (t[m].x - tbar);
+      if (p[m].y > 0.0) c1[0] += (v[0][m].y - rbar) * (t[m].y - tbar);
+    }
+    surf_sums<1, NW>(c1, sh, den);
+    const double tau = den[0] != 0.0 ? r[0] / den[0] : 0.0;
+    const double tre = tau != 0.0 ? tau : tau0;
+    double s2[2] = {0.0, 0.0}, n[2];
+    cpx<double> pn[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) pn[m] = p[m];
+    if (q.on) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        pn[m].x = pk_step(p[m].x, g[m].x - gbar - glo, t[m].x, tau, tre, s2[1]);
+        pn[m].y = pk_step(p[m].y, g[m].y - gbar - glo, t[m].y, tau, tre, s2[1]);
+        s2[0] += pn[m].x + pn[m].y;
+      }
+    }
+    surf_sums<2, NW>(s2, sh, n);
+    // load renormalised, a restart after re-admission, new gap (k_pk_gap)
+    const double scale = n[0] > 0.0 ? W / (dA * n[0]) : 1.0;
+    delta = n[1] > 0.0 ? 0.0 : 1.0;
+    dp = 0.0;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      pn[m] = scl(pn[m], scale);
+      dp += fabs(pn[m].x - p[m].x) + fabs(pn[m].y - p[m].y);
+      p[m] = pn[m];
+      v[0][m] = pn[m];
+    }
+    comply(v);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) g[m] = sub(v[0][m], h[m]);
+    gap_sums();
+    err = dA * o[0] / W;
+    stop = !(err >= tol && err <= 1.7976931348623157e308);     // converged or not finite
+  }
+  const double gbar = o[2] > 0.0 ? o[1] / o[2] : 0.0;
+  if (stop || last) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) g[m] = mk(g[m].x - gbar, g[m].y - gbar);
+  }
+  store_pair<LX>(a.p, q, p);
+  store_pair<LX>(a.g, q, g);
+  store_pair<LX>(a.t, q, t);
+  if (threadIdx.x == 0) {
+    a.sc[S_DELTA] = delta;
+    a.sc[S_GOLD] = gold;
+    a.sc[S_GBAR] = gbar;
+    a.sc[S_CNT] = o[2];
+    a.sc[S_ERR] = a.mirror[S_ERR] = err;
+    a.mirror[S_IT] = (double)it;
+  }
+}
+
 hipError_t launch_columns(int nx, int ny, double lx, double ly, double estar, const cpx<double>* twy,
                           cpx<double>* X, const double* part, int ldp, int nb, const double* sc, hipStream_t st) {
   const double fac = 2.0 / estar / ((double)nx * ny);
@@ -541,6 +751,22 @@ hipError_t launch_pk_iteration(const PkBufs& b, hipStream_t st) {
                      b.ny, b.twx, b.part, ldp, nbr, b.sc)
   FVIM_SURF_SWITCH(surf_log2(b.nx), CALL)
 #undef CALL
+  return hipGetLastError();
+}
+
+// 16: the threads of a shorter side would not fill a wave; 64: see k_pk_solo
+bool pk_solo_fits(int nx, int ny) { return nx >= 16 && nx <= 64 && ny >= 16 && ny <= 64; }
+
+hipError_t launch_pk_solo(const PkBufs& b, int count, double tol, bool first, bool last, hipStream_t st) {
+#define CASE(LX, LY)                                                                                            \
+  case LX * 16 + LY:                                                                                            \
+    hipLaunchKernelGGL((k_pk_solo<LX, LY>), dim3(1), dim3(Solo<LX, LY>::NTH), 0, st, b, count, tol, first, last); \
+    break;
+  switch (surf_log2(b.nx) * 16 + surf_log2(b.ny)) {
+    CASE(4, 4) CASE(4, 5) CASE(4, 6) CASE(5, 4) CASE(5, 5) CASE(5, 6) CASE(6, 4) CASE(6, 5) CASE(6, 6)
+    default: return hipErrorInvalidValue;
+  }
+#undef CASE
   return hipGetLastError();
 }
 

@@ -7,7 +7,7 @@ namespace fvim {
 // device scalar slots of the solvers
 enum {
   S_GBAR = 0, S_G, S_GOLD, S_DELTA, S_ERR, S_CNT, S_W, S_DA,
-  S_DOT0, S_DOT1, S_DOT2, S_KKT, S_TAU0, S_GLO, NSCAL = 32
+  S_DOT0, S_DOT1, S_DOT2, S_KKT, S_TAU0, S_GLO, S_IT, NSCAL = 32
 };
 
 // One contact problem on an nx x ny surface: device fields of nx ny doubles
@@ -45,6 +45,17 @@ hipError_t launch_pk_first(const PkBufs& b, hipStream_t st);
 // One Polonsky-Keer iteration from the state launch_pk_first or the previous
 // iteration left: p is the new pressure, g = M[p] - h.
 hipError_t launch_pk_iteration(const PkBufs& b, hipStream_t st);
+
+// Whether an nx x ny surface is iterated by one workgroup (launch_pk_solo).
+bool pk_solo_fits(int nx, int ny);
+
+// Up to `count` iterations in one launch, fewer when sum |p - p_old| falls below
+// tol or is not finite.  first: from the start pressure (launch_pk_first's g,
+// no direction), else from the state the previous launch left.  mirror[S_ERR],
+// mirror[S_IT]: the last iteration's measure and how many ran; after the last
+// one (converged, or `last` and count done) g is left minus its mean on the contact
+// set, with sc[S_GBAR] and sc[S_CNT].
+hipError_t launch_pk_solo(const PkBufs& b, int count, double tol, bool first, bool last, hipStream_t st);
 
 // sc[S_ERR] (and its mirror) = dA sum |p - p_old| / W of the last iteration.
 hipError_t launch_pk_err(const PkBufs& b, hipStream_t st);

@@ -646,6 +646,8 @@ static int compliance(fvim_ctx* c, const double* p, double* u, hipStream_t st) {
 
 // Contact iterations between two reads of the convergence measure.
 static int pk_check_period(size_t n) { return n <= 4096 ? 1 : 4; }
+// and most iterations of a one-workgroup launch (a few ms)
+constexpr int PK_SOLO_ITERS = 256;
 
 // The iterations up to the next check and their convergence measure, as a
 // fixed sequence of launches on st (no host dependency: every scalar lives in
@@ -697,17 +699,18 @@ int pk_solve(fvim_ctx* c, const double* h, double W, double tol, int max_iter, d
   w->hsc[S_TAU0] = 1.0 / w->mdiag;
   hipError_t e = hipMemcpyAsync(w->sc, w->hsc, sizeof(double) * NSCAL, hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return fail_hip(e, "scalar upload");
+  const bool solo = pk_solo_fits(pk.nx, pk.ny);
   // no previous conjugate direction
-  hipLaunchKernelGGL(k_fill, G, Bk, 0, st, t, n, 0.0);
+  if (!solo) hipLaunchKernelGGL(k_fill, G, Bk, 0, st, t, n, 0.0);
   // initial pressure: warm start renormalised to W, or uniform
   hipLaunchKernelGGL(k_sum_abs, G, Bk, 0, st, p, n, w->part);
   hipLaunchKernelGGL(k_pk_final<false>, dim3(1), Bk, 0, st, w->part, nb, w->sc, w->dmap);
   hipLaunchKernelGGL(k_pk_start, G, Bk, 0, st, p, n, w->sc);
-  if ((e = launch_pk_first(pk, st)) != hipSuccess) return fail_hip(e, "contact start");
+  if (!solo && (e = launch_pk_first(pk, st)) != hipSuccess) return fail_hip(e, "contact start");
   int it = 0;
   double err = INFINITY;
   const int check = pk_check_period(n);
-  bool graph = c->use_graphs && w->cap_fail < CAP_TRIES;
+  bool graph = !solo && c->use_graphs && w->cap_fail < CAP_TRIES;
   if (graph && (!w->pk_exec || w->g_h != h || w->g_p != p)) {
     if ((rc = cap_ensure(w))) return rc;
     if (w->pk_exec) { hipGraphExecDestroy(w->pk_exec); w->pk_exec = nullptr; }
@@ -729,22 +732,27 @@ int pk_solve(fvim_ctx* c, const double* h, double W, double tol, int max_iter, d
       w->g_p = p;
     }
   }
-  while (it < max_iter) {
-    const int count = std::min(check, max_iter - it);
-    if (graph && count == check) {
+  // (solo: the first launch also forms the gap, so there is one at max_iter = 0 too)
+  for (bool first = true; it < max_iter || (solo && first); first = false) {
+    const int count = std::max(std::min(solo ? PK_SOLO_ITERS : check, max_iter - it), 0);
+    if (solo) {
+      if ((e = launch_pk_solo(pk, count, tol, first, it + count >= max_iter, st)) != hipSuccess)
+        return fail_hip(e, "contact iteration");
+    } else if (graph && count == check) {
       if ((e = hipGraphLaunch(w->pk_exec, st)) != hipSuccess) return fail_hip(e, "graph launch");
     } else {
       if ((rc = pk_iterations(pk, count, st))) return rc;
     }
-    it += count;
     if ((rc = read_scalars(c, S_ERR, 1))) return rc;
+    it += solo ? (int)w->hmap[S_IT] : count;
+    if (it == 0) break;
     err = w->hsc[S_ERR];
     if (!std::isfinite(err)) return fail(FVIM_EINVAL, "contact_solve: non-finite iterate (check h and W)");
     if (err < tol) break;
   }
   const bool conv = err < tol;
   // final gap (g = M[p] - h is that of the last iterate) and certificate
-  if ((e = launch_pk_gap_mean(pk, st)) != hipSuccess) return fail_hip(e, "contact gap");
+  if (!solo && (e = launch_pk_gap_mean(pk, st)) != hipSuccess) return fail_hip(e, "contact gap");
   hipLaunchKernelGGL(k_pk_kkt, G, Bk, 0, st, p, g, h, n, w->part);
   hipLaunchKernelGGL(k_pk_final<true>, dim3(1), Bk, 0, st, w->part, nb, w->sc, w->dmap);
   if (gap) {

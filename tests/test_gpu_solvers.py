@@ -81,6 +81,37 @@ def test_contact_matches_oracle_at_the_transform_lengths(nx, ny):
     ctx.close()
 
 
+@pytest.mark.parametrize("nx,ny", [(16, 16), (16, 32), (16, 64), (32, 16), (32, 32), (32, 64), (64, 16), (64, 32),
+                                   (64, 64)])
+def test_contact_of_one_workgroup_matches_oracle(nx, ny):
+    """Surfaces small enough for one workgroup, on non-square cells: the
+    minimiser and its gap (bound of the square cases), and with a tolerance
+    below rounding the same minimiser after 300 iterations, more than one launch runs."""
+    ly = ny / nx
+    g = grid_dict(nx, ny, 2, 1.0, ly)
+    h = rough_surface(nx, ny, hurst=0.8, k_roll=1, k_cut=max(1, max(nx, ny) // 16), rms_slope=0.1, seed=nx + ny,
+                      ly=ly)
+    _say("contact", nx, ny)
+    ref, rgap, rinfo = oc.contact_solve(h, 0.02 * ly, g, E, NU, tol=1e-14, max_iter=20000)
+    ctx = _ctx(g)
+    hd = torch.from_numpy(h).cuda()
+    p, gap, info = ctx.contact_solve(hd, 0.02 * ly, tol=1e-14, max_iter=20000, want_gap=True)
+    torch.cuda.synchronize()
+    err, gerr = _rel(p.cpu().numpy(), ref), _rel(gap.cpu().numpy(), rgap)
+    _say("iters gpu/oracle", info["iters"], rinfo["iters"], "rel err p", err, "gap", gerr)
+    assert err < 1e-11 and gerr < 1e-11
+    p = torch.zeros_like(p)
+    try:
+        ctx.contact_solve(hd, 0.02 * ly, tol=1e-300, max_iter=300, p=p)
+    except RuntimeError as exc:                    # (an iterate that repeats exactly has converged)
+        assert "iteration limit" in str(exc), exc
+    torch.cuda.synchronize()
+    err = _rel(p.cpu().numpy(), ref)
+    _say("after 300 iterations", err)
+    assert err < 1e-11
+    ctx.close()
+
+
 def test_contact_matches_oracle_rough_1024():
     """The rough-surface workload's contact solve at its full size: 1024^2,
     Hurst 0.8, PSD plateau for 1 <= |k| < 4, cut-off |k| = 256, rms slope
