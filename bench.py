@@ -123,11 +123,11 @@ def stage_bytes(nx, ny, nz, csize=16, rsize=8, replicas=True, pin=None):
     the 6 nz eigenstrain planes and the 3 traction planes are transformed
     together (pin = 6 nz + 3 planes in), 6 nz strain planes come out.  With
     replicas (the default launch), the main depth launch also reads the
-    Nyquist modes' spectra once and writes one record per sign replica, and
-    depth_nyq averages those records into the Nyquist modes; without (side
-    stream), depth_nyq evaluates the Nyquist modes itself.  pin: input
-    planes when not both operators (6 nz for Mindlin alone, 3 for
-    Boussinesq alone)."""
+    Nyquist modes' spectra once, writes one record per sign replica and
+    averages those records into the Nyquist modes (in float32, csize 8,
+    depth_nyq does the last); without (side stream), depth_nyq evaluates the
+    Nyquist modes itself.  pin: input planes when not both operators (6 nz for
+    Mindlin alone, 3 for Boussinesq alone)."""
     kxh = nx // 2 + 1
     nm = kxh * ny
     nnyq = ny + kxh - 1                    # modes with kx = nx/2 or ky = ny/2
@@ -137,6 +137,8 @@ def stage_bytes(nx, ny, nz, csize=16, rsize=8, replicas=True, pin=None):
     if replicas:
         depth = (nm - nnyq) * per_mode + nnyq * pin * csize + nrep * pout * csize
         nyq = nrep * pout * csize + nnyq * pout * csize
+        if csize == 16:
+            depth, nyq = depth + nyq, 0
     else:
         depth = (nm - nnyq) * per_mode
         nyq = nnyq * per_mode
@@ -287,7 +289,7 @@ def bench_batch(a):
 SOLVER_NAMES = {0: "dfsane", 1: "picard", 2: "newton_krylov"}
 # (tile, radix) of the forward row, forward column, inverse column and
 # inverse row transforms for the 256^2 x 64 float64 operator
-HEADLINE_FFT_CONFIG = [(0, 4), (1, 8), (1, 8), (1, 8)]
+HEADLINE_FFT_CONFIG = [(2, 4), (2, 4), (2, 4), (2, 4)]
 
 
 def friction_opts(a):
@@ -709,9 +711,8 @@ def main():
         eps = None
     if (a.nx, a.ny, a.nz, a.precision, a.graded, a.op) == (256, 256, 64, "fp64", 0.0, "fused") and not a.tune:
         # the headline workload runs the launch choices measured fastest for
-        # it on MI355X (depth layout 64 lanes x 1 node; transforms: forward
-        # rows half tiles radix 4, the other three default tiles radix 8),
-        # pinned so that every run and its profile time the same kernels
+        # it on MI355X (depth layout 64 lanes x 1 node; transforms: double
+        # runs, radix 4), pinned so that every run and its profile time the same kernels
         # (the tuner's timings of near-equal candidates vary from run to run)
         ctx.set_option(ctx.OPT_DEPTH_CONFIG, 4 if a.depth_config is None else a.depth_config)
         ctx.set_fft_config(a.fft_config or HEADLINE_FFT_CONFIG)

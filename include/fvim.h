@@ -166,14 +166,14 @@ int fvim_operator_apply_noalloc(fvim_ctx* ctx, const double* eps_p, const double
  * operator of fvim_operator_apply for n contexts at once, ordered on the
  * stream of ctxs[0].  Contexts whose transform lengths nx and ny are both at
  * most 512 share one launch per in-plane transform stage (up to 8 grids per
- * launch, each with its length's default transform choice); longer ones run
- * their own transform launches with their own choices.  The depth pass of
- * up to 8 contexts runs as one launch for their regular modes and one for
- * their Nyquist modes, a table mapping each block to its grid (the layout is
- * the default one for the largest nz).  A context's results are therefore
- * the same in any batch (bitwise), and agree with its separate application
- * up to the summation order of the depth layout and transform choices
- * (bitwise when both are the defaults).  The arrays hold one device pointer
+ * launch, each with its length's default transform choice), and the depth
+ * pass of up to 8 contexts is one launch (in float32 two: the second
+ * averages the Nyquist modes' sign replicas), a table mapping each block to
+ * its grid, in one layout for the largest nz among them.  Longer ones run
+ * their own application, with their own choices.  A context's results are
+ * therefore the same in any batch (bitwise), and agree with its separate
+ * application up to the summation order of the depth layout and transform
+ * choices.  The arrays hold one device pointer
  * per context (eps_p[i] [6][nz][ny][nx], ...); an array that is NULL is not
  * requested for any context, and every requested pointer must be non-NULL.
  * All contexts must share the device and the precision.  Asynchronous.
@@ -444,13 +444,14 @@ enum {
   FVIM_STAGE_YFWD = 1,   /* y transform of the same planes               */
   FVIM_STAGE_XFWD_T = 2, /* unused (the traction planes are part of XFWD) */
   FVIM_STAGE_YFWD_T = 3, /* unused (part of YFWD)                        */
-  FVIM_STAGE_DEPTH = 4,  /* per-mode depth pass (with the sign replicas   */
-                         /* of the Nyquist modes unless the side stream  */
-                         /* is on)                                       */
+  FVIM_STAGE_DEPTH = 4,  /* per-mode depth pass (with the Nyquist modes,  */
+                         /* in float32 their sign replicas, unless the   */
+                         /* side stream is on)                           */
   FVIM_STAGE_YINV = 5,   /* inverse y transform of the output planes     */
   FVIM_STAGE_XINV = 6,   /* inverse x transform of the output planes     */
   FVIM_STAGE_DEPTH_NYQ = 7, /* Nyquist modes: average of their sign      */
-                            /* replicas (side stream: their depth pass)  */
+                            /* replicas (float32), or their depth pass   */
+                            /* (side stream)                             */
   FVIM_NSTAGES = 8
 };
 int fvim_set_timing(fvim_ctx* ctx, int on);
@@ -464,7 +465,8 @@ int fvim_set_timing(fvim_ctx* ctx, int on);
  * Callers that need run-to-run identical results store the chosen id and
  * set it explicitly.  FVIM_OPT_GRAPHS (default 1): the contact iteration is
  * captured once as a HIP graph and replayed (same kernels, same results; 0
- * launches the kernels one by one).  FVIM_OPT_SIDE_STREAM (default 0): 1 runs
+ * launches the kernels one by one; surfaces of 16 to 64 points a side need
+ * neither, one launch runs all iterations).  FVIM_OPT_SIDE_STREAM (default 0): 1 runs
  * the Nyquist-mode depth launch on a second library stream beside the main
  * depth launch (same results).  FVIM_OPT_STREAMING (default 2): each operator
  * launch reads its input spectrum for the last time; 1 does so with streaming
@@ -475,8 +477,8 @@ int fvim_set_timing(fvim_ctx* ctx, int on);
  * either way).  FVIM_OPT_FFT_CONFIG: launch choices of the four in-plane
  * transform kernels for the context's operator precision, 3 bits each
  * (bits 3k .. 3k+2 for k = 0 forward row, 1 forward column, 2 inverse
- * column, 3 inverse row transform): tile (0: half the default LDS tile,
- * 1: default, 2: twice) | 4 for radix-8 stages (else radix 4); 0x249 is
+ * column, 3 inverse row transform): tile (0: half the default run of
+ * elements on the strided side, 1: default, 2: twice) | 4 for radix-8 stages (else radix 4); 0x249 is
  * the default.  Alternatives exist for transform lengths 32 .. 1024; other
  * lengths run the default.  FVIM_OPT_TUNE also times these (6 choices per
  * kernel, on the next operator call's own data) and keeps the fastest; the

@@ -158,7 +158,7 @@ def report(a):
             ks = [k for k in depth_keys if k[0] == best]
             if ks:
                 st[stage] = ks[0]
-    # the Nyquist stage of the default launch averages the sign replicas
+    # the Nyquist stage of the float32 default launch averages the sign replicas
     avg = [k for k in keys if k[0].startswith("k_nyq_average")]
     if avg:
         st["depth_nyq"] = avg[0]
