@@ -169,8 +169,8 @@ int fvim_operator_apply_noalloc(fvim_ctx* ctx, const double* eps_p, const double
  * launch, each with its length's default transform choice), and the depth
  * pass of up to 8 contexts is one launch (in float32 two: the second
  * averages the Nyquist modes' sign replicas), a table mapping each block to
- * its grid, in one layout for the largest nz among them.  Longer ones run
- * their own application, with their own choices.  A context's results are
+ * its grid; the layout is the largest nz's, in float64 narrowed to the grid's
+ * own.  Longer ones run their own application, with their own choices.  A context's results are
  * therefore the same in any batch (bitwise), and agree with its separate
  * application up to the summation order of the depth layout and transform
  * choices.  The arrays hold one device pointer

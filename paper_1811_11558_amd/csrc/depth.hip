@@ -235,9 +235,17 @@ void depth_derive(DepthParams& p) {
   p.ik2 = 1.0 / (2.0 * kap + 2.0);
 }
 
+// Layout a grid of nz nodes runs in within a batched launch of layout cfg (as
+// depth_batch_block decides)
+template <typename T>
+int depth_batch_own(int cfg, int nz) {
+  if (sizeof(T) != 8 || (cfg != 3 && cfg != 5)) return cfg;
+  return nz <= 32 ? 1 : (nz <= 64 ? 3 : cfg);
+}
+
 template <typename T>
 void depth_blocks(int cfg, const DepthParams& p, int* main, int* nyq) {
-  *main = main_blocks<T>(NT / kCfgs[cfg].lpm, p);
+  *main = main_blocks<T>(NT / kCfgs[depth_batch_own<T>(cfg, p.nz)].lpm, p);
   *nyq = mean_in_pass<T>() ? 0 : p.ny + p.kxh - 1;
 }
 

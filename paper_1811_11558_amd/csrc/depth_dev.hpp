@@ -742,14 +742,26 @@ __device__ __forceinline__ void nyq_average(cpx<T>* __restrict__ out, const cpx<
 
 // One block of a batched depth launch (main modes or, NYQ, the Nyquist
 // averages) over the grids of the table b: block blk belongs to the grid c
-// with first[c] <= blk < first[c + 1].
+// with first[c] <= blk < first[c + 1].  In float64 the layouts of two nodes per
+// lane hold the narrower ones too, and a grid runs in the narrowest that serves its
+// nz (depth_batch_own): half the lanes or more idle otherwise (57.5 -> 49.5 us for 8 grids
+// of 8 to 64 nodes, 1.6M voxels).  float32 keeps one layout for all: see mean_in_pass.
 template <typename T, int LPM, int P, bool DISP, bool WANTX, bool NYQ>
 __device__ __forceinline__ void depth_batch_block(const DepthBatch* __restrict__ b, int blk) {
   const int* first = NYQ ? b->first_nyq : b->first_main;
   int c = 0;
   while (c + 1 < b->n && blk >= first[c + 1]) ++c;
-  depth_modes<T, LPM, P, DISP, WANTX, NYQ>(static_cast<const cpx<T>*>(b->in[c]), static_cast<cpx<T>*>(b->out[c]),
-                                           b->prm[c], blk - first[c]);
+  const cpx<T>* in = static_cast<const cpx<T>*>(b->in[c]);
+  cpx<T>* out = static_cast<cpx<T>*>(b->out[c]);
+  const DepthParams& prm = b->prm[c];
+  blk -= first[c];
+  if constexpr (sizeof(T) == 8 && !NYQ && P == 2 && LPM > 16) {
+    if (prm.nz <= 32) return depth_modes<T, 16, 2, DISP, WANTX, NYQ>(in, out, prm, blk);
+    if constexpr (LPM > 32) {
+      if (prm.nz <= 64) return depth_modes<T, 32, 2, DISP, WANTX, NYQ>(in, out, prm, blk);
+    }
+  }
+  depth_modes<T, LPM, P, DISP, WANTX, NYQ>(in, out, prm, blk);
 }
 
 template <typename T>

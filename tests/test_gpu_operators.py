@@ -561,3 +561,33 @@ def test_column_passes_at_every_tile_and_precision(nx, ny, nz):
             _say("columns", (nx, ny, nz), prec, ch, errs)
             assert max(errs) <= bound, (prec, ch, errs)
         c.close()
+
+
+@pytest.mark.parametrize("shapes", [[(16, 16, 20), (32, 16, 40), (16, 32, 33)],
+                                    [(16, 16, 10), (32, 16, 32), (16, 16, 64), (16, 32, 100), (64, 16, 65)]])
+def test_batched_grids_run_in_their_own_depth_layout(shapes):
+    """Grids whose depth counts ask for different layouts in one batch: the
+    oracle's fields, and (more than 16 nodes) bitwise those of the grid batched
+    alone."""
+    from paper_1811_11558_amd import operator_apply_batch
+    dev = torch.device("cuda")
+    want = ("strain", "surf_u3")
+    ctxs, eps, ts, refs = [], [], [], []
+    for i, (nx, ny, nz) in enumerate(shapes):
+        g = grid_dict(nx, ny, nz, 1.0, 1.0, 0.25)
+        e, t = filtered_eigenstrain(g, seed=70 + i), filtered_traction(g, seed=80 + i)
+        refs.append(ora.apply(g, E, NU, eps_p=e, traction=t))
+        ctxs.append(_ctx(g))
+        eps.append(torch.from_numpy(e).to(dev))
+        ts.append(torch.from_numpy(t).to(dev))
+    got = operator_apply_batch(ctxs, eps, ts, want=want)
+    for i, sh in enumerate(shapes):
+        alone = operator_apply_batch(ctxs[i:i + 1], eps[i:i + 1], ts[i:i + 1], want=want)[0]
+        torch.cuda.synchronize()
+        for k in want:
+            err = _rel(got[i][k].cpu().numpy(), refs[i][k])
+            _say("batch layouts", sh, k, err)
+            assert err <= TOL, (sh, k, err)
+            assert sh[2] <= 16 or torch.equal(got[i][k], alone[k]), (sh, k)
+    for c in ctxs:
+        c.close()
