@@ -78,7 +78,7 @@ def trace_table(path):
         acc[k].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
         meta[k] = (r["VGPR_Count"], r["Scratch_Size"], r["LDS_Block_Size"])
     out = ["VGPRs: the trace's VGPR_Count, which on gfx950 is half the register count of the code object "
-           "(the depth pass's 84 is 168 registers, 3 waves per SIMD).", "",
+           "(a float64 depth pass's 80 is 160 registers, 3 waves per SIMD).", "",
            "| kernel | grid (threads) | launches | average (us) | VGPRs | scratch (B) | LDS (B) |",
            "|---|---|---|---|---|---|---|"]
     for k in sorted(acc, key=lambda k: -sum(acc[k])):
