@@ -1,7 +1,8 @@
 // In-plane transforms of the layered fields (the DFT of Sec. 3.1, eqn dft),
-// written for gfx950: every kernel stages a batch of 1D transforms through
-// LDS and runs a self-sorting (Stockham) FFT of radix 4 (one radix-2 stage
-// when log2(n) is odd) or radix 8 (one radix-2 or radix-4 stage first).
+// written for gfx950: every kernel holds a batch of 1D transforms in registers
+// and runs a self-sorting (Stockham) FFT of radix 4 (one radix-2 stage when
+// log2(n) is odd) or radix 8 (one radix-2 or radix-4 stage first), exchanging
+// through LDS between passes of several stages.
 // Global memory is touched once on the way in and once on the way out, with
 // the layouts chosen so both sides are contiguous runs:
 //
@@ -15,8 +16,8 @@
 // done two rows at a time as one complex transform (z = a + i b).
 // Forward transforms are unnormalised; the depth pass applies 1/(nx ny).
 //
-// The LDS tile (half, default or twice the default) and the radix are
-// choices of each launch (FftChoice), timed by the context's tuner for
+// The tile (runs of half, default or twice the default length on the strided
+// side) and the radix are choices of each launch (FftChoice), timed by the context's tuner for
 // lengths 2^5 .. 2^10; other lengths use the default.  Kernels over several
 // grids (XformBatch) run the default choice of each grid's length.
 #include <algorithm>
@@ -39,15 +40,17 @@ void k_x_r2c(InSegments seg, cpx<T>* __restrict__ out, int ny, int R, const cpx<
 }
 
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
-__global__ __launch_bounds__((col_threads<T>(1 << LOGN, TILE))) void k_y_fwd(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
-                                             int kxh, int NP, int ldp, const cpx<T>* __restrict__ tw, LayerSkip skip) {
+__global__ __launch_bounds__((col_threads<T>(1 << LOGN, TILE)))
+void k_y_fwd(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, int kxh, int NP, int ldp,
+             const cpx<T>* __restrict__ tw, LayerSkip skip) {
   __shared__ __align__(16) char tile[col_lds_bytes<T>(1 << LOGN, TILE)];
   y_fwd_body<T, LOGN, NTL, TILE, RADIX>(tile, threadIdx.x, xcd_block(), true, in, out, kxh, NP, ldp, tw, skip);
 }
 
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
-__global__ __launch_bounds__((col_threads<T>(1 << LOGN, TILE))) void k_y_inv(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
-                                             int kxh, int NP, int ldp, const cpx<T>* __restrict__ tw) {
+__global__ __launch_bounds__((col_threads<T>(1 << LOGN, TILE)))
+void k_y_inv(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, int kxh, int NP, int ldp,
+             const cpx<T>* __restrict__ tw) {
   __shared__ __align__(16) char tile[col_lds_bytes<T>(1 << LOGN, TILE)];
   y_inv_body<T, LOGN, NTL, TILE, RADIX>(tile, threadIdx.x, xcd_block(), true, in, out, kxh, NP, ldp, tw);
 }

@@ -187,7 +187,9 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 //
 // A Stockham stage of radix R for sub-transforms of length ns takes elements
 // j + m N/R (m < R), turned by w^(m k N/(R ns)) with k = j mod ns, and writes its
-// butterfly's results to (j / ns) ns R + k + m ns.  Stages of radices R1, Rest... from sub-transforms of length 2^LS on: the Rg
+// butterfly's results to (j / ns) ns R + k + m ns.
+//
+// Stages of radices R1, Rest... from sub-transforms of length 2^LS on: the Rg
 // values at positions tt + c N / Rg give outputs idx at positions
 // (tt / ns) Rg ns + k + idx ns, k = tt mod ns, ns = 2^LS.  The first stage's
 // butterfly over m of v[m2 + m S] (S = Rg / R1) yields the inputs of R1
@@ -318,7 +320,7 @@ __device__ __forceinline__ void reg_fft(cpx<T> (&v)[V], int t0, L0 lds0, int t1,
 
 // ------------------------------------------------------------------ bodies
 // Each transform is a device body over one block's tile (logical block lb of
-// one grid) using the LDS tile buf (and red, NTH/64 doubles), shared by the
+// one grid) using the LDS tile (and red, a double per wave), shared by the
 // single-grid kernels and by the kernels that serve several grids in one
 // launch.
 
@@ -706,7 +708,8 @@ __device__ __forceinline__ void x_r2c_batch_block(const XformBatch& b, int blk, 
   char* tile = reinterpret_cast<char*>(fvim_dyn_lds);
   cpx<T>* out = static_cast<cpx<T>*>(b.out[c]);
   const cpx<T>* tw = static_cast<const cpx<T>*>(b.tw[c]);
-#define CALL(L) x_r2c_body<T, L, false, 3, 4>(tile, red, lb, b.iseg[c], out, b.ny[c], b.R[c], tw, b.bsum[c], LayerSkip{})
+#define CALL(L) \
+  x_r2c_body<T, L, false, 3, 4>(tile, red, lb, b.iseg[c], out, b.ny[c], b.R[c], tw, b.bsum[c], LayerSkip{})
   FVIM_BATCH_LOGN_SWITCH(b.logn[c], CALL)
 #undef CALL
 }
@@ -721,8 +724,8 @@ __device__ __forceinline__ void y_fwd_batch_block(const XformBatch& b, int blk) 
 #define CALL(L)                                                                                                \
   {                                                                                                            \
     const ColTile q = col_tile<T, L>(lb, b.kxh[c], b.NP[c]);                                                   \
-    y_fwd_body<T, L, false, col_shared_tile<T>(1 << L), 4>(q.lds, q.tid, q.lb, q.live, in, out, b.kxh[c], b.NP[c],       \
-                                  b.ldp[c], tw, LayerSkip{});                                                  \
+    y_fwd_body<T, L, false, col_shared_tile<T>(1 << L), 4>(q.lds, q.tid, q.lb, q.live, in, out, b.kxh[c],  \
+                                                          b.NP[c], b.ldp[c], tw, LayerSkip{});                       \
   }
   FVIM_BATCH_LOGN_SWITCH(b.logn[c], CALL)
 #undef CALL
@@ -738,8 +741,8 @@ __device__ __forceinline__ void y_inv_batch_block(const XformBatch& b, int blk) 
 #define CALL(L)                                                                                                \
   {                                                                                                            \
     const ColTile q = col_tile<T, L>(lb, b.kxh[c], b.NP[c]);                                                   \
-    y_inv_body<T, L, false, col_shared_tile<T>(1 << L), 4>(q.lds, q.tid, q.lb, q.live, in, out, b.kxh[c], b.NP[c],       \
-                                  b.ldp[c], tw);                                                               \
+    y_inv_body<T, L, false, col_shared_tile<T>(1 << L), 4>(q.lds, q.tid, q.lb, q.live, in, out, b.kxh[c],  \
+                                                          b.NP[c], b.ldp[c], tw);                                    \
   }
   FVIM_BATCH_LOGN_SWITCH(b.logn[c], CALL)
 #undef CALL

@@ -28,7 +28,7 @@ struct LayerSkip {
   const int* zact;
   int nz, nw;
 };
-// Launch choice of a transform kernel: the LDS tile (0: half the default,
+// Launch choice of a transform kernel: the runs on its strided side (0: half the default,
 // 1: the default, 2: twice) and the radix of the Stockham stages (4 or 8).
 // Only lengths 2^FFT_TUNE_MIN_LOGN .. 2^FFT_TUNE_MAX_LOGN have the
 // alternatives; fft_effective gives what a launch of length 2^logn runs.

@@ -461,7 +461,7 @@ struct SolverWork {
   double* pkpart = nullptr;     // block sums of the contact iteration
   double* sc = nullptr;         // device scalars
   double* hsc = nullptr;        // pinned host copy
-  double* hmap = nullptr;       // mapped host memory written by k_pk_final (host view)
+  double* hmap = nullptr;       // mapped host memory the reductions write (host view)
   double* dmap = nullptr;       //   (device view)
   double* vol = nullptr;        // volume work arrays (allocated on first plasticity use)
   size_t vol_count = 0;
@@ -618,7 +618,7 @@ size_t solver_footprint(const fvim_grid* g, size_t V) {
 }
 
 // Host copy of device scalars [first, first + n) (synchronises the stream).
-// The slots k_pk_final mirrors (S_ERR, S_DOT0..S_DOT2) are taken from the
+// The slots kernels mirror (S_ERR, S_DOT0..S_DOT2) are taken from the
 // mapped mirror once the stream is idle; others are copied.
 static int read_scalars_on(fvim_ctx* c, hipStream_t st, int first, int n) {
   SolverWork* w = c->sw;
