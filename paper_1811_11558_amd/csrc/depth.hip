@@ -40,16 +40,11 @@
 
 namespace fvim {
 namespace {
-// Waves per SIMD a layout's registers are held to: the float64 one-wave layout
-// fits 3 (at most 168 registers; the batched form takes up to 170 otherwise).
-template <typename T, int LPM, int P>
-constexpr int depth_waves() { return sizeof(T) == 8 && LPM == 64 && P == 1 ? 3 : 1; }
-
 // NTL: the input spectrum is read with streaming loads (last use); NU:
 // non-uniform depth nodes (prm.hz)
 template <typename T, int LPM, int P, bool DISP, bool WANTX, bool NYQ, bool NTL, bool NU = false>
-__global__ __launch_bounds__(NT, (depth_waves<T, LPM, P>()))
-void k_depth(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, DepthParams prm) {
+__global__ __launch_bounds__(NT) void k_depth(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
+                                             DepthParams prm) {
   depth_modes<T, LPM, P, DISP, WANTX, NYQ, NTL, NU>(in, out, prm, blockIdx.x);
 }
 
@@ -57,8 +52,7 @@ void k_depth(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, DepthParam
 // first[c] <= b < first[c + 1] (main or Nyquist block counts); the table is
 // in device memory, so its fields are block-uniform loads.
 template <typename T, int LPM, int P, bool DISP, bool WANTX, bool NYQ>
-__global__ __launch_bounds__(NT, (depth_waves<T, LPM, P>()))
-void k_depth_batch(const DepthBatch* __restrict__ b) {
+__global__ __launch_bounds__(NT) void k_depth_batch(const DepthBatch* __restrict__ b) {
   depth_batch_block<T, LPM, P, DISP, WANTX, NYQ>(b, (int)blockIdx.x);
 }
 
