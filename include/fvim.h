@@ -166,14 +166,15 @@ int fvim_operator_apply_noalloc(fvim_ctx* ctx, const double* eps_p, const double
  * operator of fvim_operator_apply for n contexts at once, ordered on the
  * stream of ctxs[0].  Contexts whose transform lengths nx and ny are both at
  * most 512 share one launch per in-plane transform stage (up to 8 grids per
- * launch, each with its length's default transform choice), and the depth
- * pass of up to 8 contexts is one launch (in float32 two: the second
- * averages the Nyquist modes' sign replicas), a table mapping each block to
- * its grid; the layout is the largest nz's, in float64 narrowed to the grid's
- * own.  Longer ones run their own application, with their own choices.  A context's results are
- * therefore the same in any batch (bitwise), and agree with its separate
- * application up to the summation order of the depth layout and transform
- * choices.  The arrays hold one device pointer
+ * launch, each with its length's default transform choice); longer ones run
+ * their own applications with their own transform choices.  The depth pass of up
+ * to 8 others is one launch for those of at most 128 nodes, one for those of
+ * 129 to 256 and one for deeper ones (in float32 one more averages the Nyquist
+ * modes' sign replicas), a table mapping each block to its grid.  Each grid runs
+ * in the default depth layout of its own nz.  A context's results are therefore the same in any batch (bitwise),
+ * and agree with its separate application up to the summation order of the
+ * depth layout and transform choices (bitwise when both are the defaults).
+ * The arrays hold one device pointer
  * per context (eps_p[i] [6][nz][ny][nx], ...); an array that is NULL is not
  * requested for any context, and every requested pointer must be non-NULL.
  * All contexts must share the device and the precision.  Asynchronous.

@@ -450,10 +450,10 @@ int tune_operator(fvim_ctx* c, OpPlan<T>& P) {
 }
 
 // One application: forward transforms, depth pass, mean mode (float32 path) and
-// inverse transforms.  ss != st: the Nyquist modes' depth launch runs on ss
-// beside the other modes'.
+// inverse transforms, the depth pass in layout cfg.  ss != st: the Nyquist modes'
+// depth launch runs on ss beside the other modes'.
 template <typename T>
-int op_run(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, hipStream_t ss, StageTimer& tm) {
+int op_run(fvim_ctx* c, OpPlan<T>& P, int cfg, hipStream_t st, hipStream_t ss, StageTimer& tm) {
   hipError_t e;
   tm.begin(FVIM_STAGE_XFWD, st);
   if ((e = run_x_fwd<T>(c, P, st, P.ch[0])) != hipSuccess) return fail_hip(e, "x_r2c");
@@ -463,11 +463,11 @@ int op_run(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, hipStream_t ss, StageTimer
   tm.end();
   if (ss != st && (e = join(c->ev_spec, st, ss)) != hipSuccess) return fail_hip(e, "fork");
   tm.begin(FVIM_STAGE_DEPTH, st);
-  if ((e = launch_depth<T>(P.B, P.A, P.prm, c->depth_cfg, st, 1)) != hipSuccess) return fail_hip(e, "depth");
+  if ((e = launch_depth<T>(P.B, P.A, P.prm, cfg, st, 1)) != hipSuccess) return fail_hip(e, "depth");
   tm.end();
   if (depth_nyq_launch<T>(P.prm)) {
     tm.begin(FVIM_STAGE_DEPTH_NYQ, ss);
-    if ((e = launch_depth<T>(P.B, P.A, P.prm, c->depth_cfg, ss, 2)) != hipSuccess)
+    if ((e = launch_depth<T>(P.B, P.A, P.prm, cfg, ss, 2)) != hipSuccess)
       return fail_hip(e, "depth (Nyquist modes)");
     tm.end();
   }
@@ -555,7 +555,7 @@ int operator_apply_t(fvim_ctx* c, const double* eps_p, const double* traction, d
     c->tune_pending = 0;
     op_refresh_sums<T>(c, P);
   }
-  return op_run<T>(c, P, st, ss, tm);
+  return op_run<T>(c, P, c->depth_cfg, st, ss, tm);
 }
 
 // Several contexts (grids may differ) on the stream of the first.  Grids whose
@@ -575,7 +575,7 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     return r;
   };
   for (int i = 0; i < n; ++i) cs[i]->stream = st;   // one stream orders the whole batch
-  int rc = 0, maxnz = 0;
+  int rc = 0;
   fvim_ctx* c0 = cs[0];
   StageTimer tm(c0);
   std::vector<int> bat;
@@ -584,27 +584,36 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
                     stress ? stress[i] : nullptr, disp ? disp[i] : nullptr, surf_u3 ? surf_u3[i] : nullptr, P[i]);
     if (!rc && P[i].np == 0) rc = fail(FVIM_EINVAL, "batch: every context needs an output");
     if (rc) break;
+    // the Nyquist sign replicas join the main launch (records after the
+    // spectrum in A, reserved by op_plan), whatever the side-stream option
+    DepthParams& p = P[i].prm;
+    p.rep_out = (void*)(P[i].A + (size_t)p.kxh * p.ny * p.ld_out);
     if (ilog2i(cs[i]->grid.nx) <= XFORM_BATCH_MAX_LOGN && ilog2i(cs[i]->grid.ny) <= XFORM_BATCH_MAX_LOGN) {
       bat.push_back(i);
-      maxnz = std::max(maxnz, cs[i]->grid.nz);
       for (int k = 0; k < 4; ++k) P[i].ch[k] = FftChoice{};
       P[i].wbpp = x_r2c_batch_blocks_per_plane<T>(cs[i]->grid.nx, cs[i]->grid.ny);
       if (P[i].k0x) P[i].tsum = P[i].wsum + (size_t)P[i].prm.off_t * P[i].wbpp;
     }
   }
   if (rc) return restore(rc);
-  const int nb = (int)bat.size();
+  const bool all_shared = (int)bat.size() == n;
+  std::vector<char> shared(n, 0);
+  for (int i : bat) shared[i] = 1;
+  std::vector<int> ord;                              // grids of the shared depth pass, group by group
   for (int i = 0; i < n; ++i) {
-    if (std::find(bat.begin(), bat.end(), i) != bat.end()) continue;
-    if ((rc = op_run<T>(cs[i], P[i], st, st, tm))) return restore(rc);
+    if (shared[i]) ord.push_back(i);
+    else if ((rc = op_run<T>(cs[i], P[i], -1, st, st, tm))) return restore(rc);
   }
-  if (nb == 0) return restore(FVIM_OK);
+  if (ord.empty()) return restore(FVIM_OK);
+  std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) {
+    return depth_batch_group(cs[a]->grid.nz) < depth_batch_group(cs[b]->grid.nz);
+  });
   if ((rc = ctx_reserve(c0, &c0->dbatch, &c0->dbatch_bytes, sizeof(DepthBatch)))) return restore(rc);
   // the persistent single-launch form (FVIM_OPT_PERSISTENT): float64, strain
-  // only, every grid a shared one, one table each
-  bool persist = c0->persistent && std::is_same<T, double>::value && !stress && !disp && !surf_u3 && nb == n &&
+  // only, every grid's transforms and depth pass shared, one table each
+  bool persist = c0->persistent && std::is_same<T, double>::value && !stress && !disp && !surf_u3 && all_shared &&
                  n <= XFORM_BATCH_MAX && n <= DEPTH_BATCH_MAX;
-  for (int i = 0; i < n && persist; ++i) persist = !P[i].k0x;
+  for (int i = 0; i < n && persist; ++i) persist = !P[i].k0x && cs[i]->grid.nz <= DEPTH_MIX_NZ;
   // the table of one stage of the batched grids bat[i0 ..], at most
   // XFORM_BATCH_MAX of them
   auto fill_xform = [&](int kind, size_t i0, XformBatch& b) {
@@ -654,22 +663,18 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     }
     return FVIM_OK;
   };
-  const int cfg = depth_batch_config(maxnz);
-  // the depth table of the grids bat[i0 .. i0 + DEPTH_BATCH_MAX - 1]
-  auto fill_depth = [&](int i0, DepthBatch& b) {
+  // the depth table of the grids ord[i0 ..], at most DEPTH_BATCH_MAX of them
+  auto fill_depth = [&](size_t i0, DepthBatch& b) {
     b = DepthBatch{};
-    b.n = std::min(DEPTH_BATCH_MAX, nb - i0);
+    b.n = (int)std::min<size_t>(DEPTH_BATCH_MAX, ord.size() - i0);
     for (int k = 0; k < b.n; ++k) {
-      const OpPlan<T>& p = P[bat[i0 + k]];
+      const OpPlan<T>& p = P[ord[i0 + k]];
       b.prm[k] = p.prm;
-      // the Nyquist sign replicas join the main launch (records after the
-      // spectrum in A, reserved by op_plan), whatever the side-stream option
-      b.prm[k].rep_out = (void*)(p.A + (size_t)p.prm.kxh * p.prm.ny * p.prm.ld_out);
       depth_derive(b.prm[k]);
       b.in[k] = p.B;
       b.out[k] = p.A;
       int nm, nq;
-      depth_blocks<T>(cfg, b.prm[k], &nm, &nq);
+      depth_blocks<T>(b.prm[k], &nm, &nq);
       b.first_main[k + 1] = b.first_main[k] + nm;
       b.first_nyq[k + 1] = b.first_nyq[k] + nq;
     }
@@ -681,17 +686,17 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     OpBatch ob;
     for (int k = 0; k < 4; ++k) fill_xform(k, 0, ob.x[k]);
     fill_depth(0, ob.d);
-    hipError_t e = launch_operator_persistent<T>(ob, (OpBatch*)c0->pbatch, cfg, false, false, st);
+    hipError_t e = launch_operator_persistent<T>(ob, (OpBatch*)c0->pbatch, false, false, st);
     if (e == hipSuccess) return restore(FVIM_OK);
     if (e != hipErrorNotSupported) return restore(fail_hip(e, "persistent batched operator"));
     (void)hipGetLastError();
   }
   if ((rc = xform(0, FVIM_STAGE_XFWD)) || (rc = xform(1, FVIM_STAGE_YFWD))) return restore(rc);
-  for (int i0 = 0; i0 < nb; i0 += DEPTH_BATCH_MAX) {
+  for (size_t i0 = 0; i0 < ord.size(); i0 += DEPTH_BATCH_MAX) {
     DepthBatch b;
     fill_depth(i0, b);
     tm.begin(FVIM_STAGE_DEPTH, st);
-    hipError_t e = launch_depth_batch<T>(b, (DepthBatch*)c0->dbatch, cfg, st);
+    hipError_t e = launch_depth_batch<T>(b, (DepthBatch*)c0->dbatch, st);
     tm.end();
     if (e != hipSuccess) return restore(fail_hip(e, "batched depth pass"));
   }

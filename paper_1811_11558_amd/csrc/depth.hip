@@ -34,6 +34,8 @@
 // recurrences run sequentially inside a lane and as Kogge-Stone scans across
 // the LPM lanes (log2(LPM) shuffle steps).  Input and output are mode-major,
 // so the nz values of one component of one mode are contiguous.
+#include <algorithm>
+
 #include "common.hpp"
 #include "depth_dev.hpp"
 #include "kernels.hpp"
@@ -48,12 +50,11 @@ __global__ __launch_bounds__(NT) void k_depth(const cpx<T>* __restrict__ in, cpx
   depth_modes<T, LPM, P, DISP, WANTX, NYQ, NTL, NU>(in, out, prm, blockIdx.x);
 }
 
-// Several grids in one launch: block b belongs to the grid c with
-// first[c] <= b < first[c + 1] (main or Nyquist block counts); the table is
-// in device memory, so its fields are block-uniform loads.
-template <typename T, int LPM, int P, bool DISP, bool WANTX, bool NYQ>
-__global__ __launch_bounds__(NT) void k_depth_batch(const DepthBatch* __restrict__ b) {
-  depth_batch_block<T, LPM, P, DISP, WANTX, NYQ>(b, (int)blockIdx.x);
+// Several grids in one launch (depth_batch_block), from block blk0 of the table's
+// on; the table is in device memory, so its fields are block-uniform loads.
+template <typename T, int LPM, int P, bool MIX, bool DISP, bool WANTX>
+__global__ __launch_bounds__(NT) void k_depth_batch(const DepthBatch* __restrict__ b, int blk0) {
+  depth_batch_block<T, LPM, P, MIX, DISP, WANTX>(b, blk0 + (int)blockIdx.x);
 }
 
 template <typename T>
@@ -186,27 +187,21 @@ bool depth_config_valid(int id, int nz) {
   return nz <= cap && 4 * nz > cap;
 }
 
-// Layout of a batched pass over grids of at most nz nodes: the fewest nodes per
-// lane that keeps <= 64 lanes.  (Two nodes per lane up to 128 nodes: a grid's sums
-// then do not depend on which of these layouts the rest of the batch asks for.)
-int depth_batch_config(int nz) {
+// Default without tuning, alone and in a batch: two nodes per
+// lane from 17 on, more than 128 nodes four or eight, but for 32 < nz <= 64 in
+// float64 one node per lane of a wave (reads whole lines, mode
+// constants in scalar registers, DPP scans): against 32 lanes x 2 nodes 8.8 / 15.7 us
+// at 16^2 x 64, 23.8 / 29.5 at 128^2 x 64, 76.8 / 99.0 at 256^2 x 64, 1231 / 1373 at
+// 1024^2 x 64, 17.1 / 19.6 at 64 x 128 x 33 and 62.9 / 61.6 at 256^2 x 33.  In float32
+// it is the slower one (57.6 / 45.7 us at 256^2 x 64).
+template <typename T>
+int depth_default_config(int nz) {
   if (nz <= 16) return 0;
   if (nz <= 32) return 1;
-  if (nz <= 64) return 3;
+  if (nz <= 64) return sizeof(T) == 8 ? 4 : 3;
   if (nz <= 128) return 5;
   if (nz <= 256) return 6;
   return 7;
-}
-
-// Default of one grid's pass without tuning: the same, but for 32 < nz <= 64 in
-// float64 one node per lane of a wave (reads whole lines, mode constants in scalar
-// registers, DPP scans): against 32 lanes x 2 nodes 8.8 / 15.7 us at 16^2 x 64,
-// 23.8 / 29.5 at 128^2 x 64, 76.8 / 99.0 at 256^2 x 64, 1231 / 1373 at 1024^2 x 64,
-// 17.1 / 19.6 at 64 x 128 x 33 and 62.9 / 61.6 at 256^2 x 33.  In float32 it is the
-// slower one (57.6 / 45.7 us at 256^2 x 64).
-template <typename T>
-int depth_default_config(int nz) {
-  return sizeof(T) == 8 && nz > 32 && nz <= 64 ? 4 : depth_batch_config(nz);
 }
 template int depth_default_config<double>(int);
 template int depth_default_config<float>(int);
@@ -229,65 +224,89 @@ void depth_derive(DepthParams& p) {
   p.ik2 = 1.0 / (2.0 * kap + 2.0);
 }
 
-// Layout a grid of nz nodes runs in within a batched launch of layout cfg (as
-// depth_batch_block decides)
 template <typename T>
-int depth_batch_own(int cfg, int nz) {
-  if (sizeof(T) != 8 || (cfg != 3 && cfg != 5)) return cfg;
-  return nz <= 32 ? 1 : (nz <= 64 ? 3 : cfg);
-}
-
-template <typename T>
-void depth_blocks(int cfg, const DepthParams& p, int* main, int* nyq) {
-  *main = main_blocks<T>(NT / kCfgs[depth_batch_own<T>(cfg, p.nz)].lpm, p);
+void depth_blocks(const DepthParams& p, int* main, int* nyq) {
+  *main = main_blocks<T>(NT / kCfgs[depth_default_config<T>(p.nz)].lpm, p);
   *nyq = mean_in_pass<T>() ? 0 : p.ny + p.kxh - 1;
 }
 
-// main launch (every mode, and the Nyquist sign replicas as modes of their
-// own), then one block per Nyquist mode averaging its replicas
-template <typename T, int LPM, int P, bool DISP, bool WANTX>
-hipError_t launch_batch_two(const DepthBatch* dtab, int nb_main, int nb_nyq, hipStream_t st) {
-  if (nb_main > 0)
-    hipLaunchKernelGGL((k_depth_batch<T, LPM, P, DISP, WANTX, false>), dim3(nb_main), dim3(NT), 0, st, dtab);
-  if (nb_nyq > 0) hipLaunchKernelGGL(k_nyq_average_batch<T>, dim3(nb_nyq), dim3(NT), 0, st, dtab);
+// Grids of at most DEPTH_MIX_NZ nodes share launches; beyond, the four- and
+// eight-node layouts (one wave per SIMD in float64) each have their own.
+int depth_batch_group(int nz) { return nz <= DEPTH_MIX_NZ ? 0 : (nz <= 256 ? 1 : 2); }
+
+// The deepest layout of the grids c0 .. c1 - 1, one group; mixed: others run in
+// other layouts.
+template <typename T>
+int depth_batch_config(const DepthBatch& b, int c0, int c1, bool* mixed) {
+  int lo = kNCfg, hi = 0;
+  for (int c = c0; c < c1; ++c) {
+    const int id = depth_default_config<T>(b.prm[c].nz);
+    lo = std::min(lo, id);
+    hi = std::max(hi, id);
+  }
+  *mixed = lo != hi;
+  return hi;
+}
+
+template <typename T, int LPM, int P, bool MIX>
+hipError_t launch_batch_cfg(const DepthBatch* dtab, bool disp, bool wx, int blk0, int nb, hipStream_t st) {
+  const dim3 grid((unsigned)nb), blk(NT);
+  if (disp && wx) hipLaunchKernelGGL((k_depth_batch<T, LPM, P, MIX, true, true>), grid, blk, 0, st, dtab, blk0);
+  else if (disp) hipLaunchKernelGGL((k_depth_batch<T, LPM, P, MIX, true, false>), grid, blk, 0, st, dtab, blk0);
+  else if (wx) hipLaunchKernelGGL((k_depth_batch<T, LPM, P, MIX, false, true>), grid, blk, 0, st, dtab, blk0);
+  else hipLaunchKernelGGL((k_depth_batch<T, LPM, P, MIX, false, false>), grid, blk, 0, st, dtab, blk0);
   return hipGetLastError();
 }
 
-template <typename T, int LPM, int P>
-hipError_t launch_batch_cfg(const DepthBatch* dtab, bool disp, bool wx, int nb_main, int nb_nyq, hipStream_t st) {
-  if (disp) return wx ? launch_batch_two<T, LPM, P, true, true>(dtab, nb_main, nb_nyq, st)
-                      : launch_batch_two<T, LPM, P, true, false>(dtab, nb_main, nb_nyq, st);
-  return wx ? launch_batch_two<T, LPM, P, false, true>(dtab, nb_main, nb_nyq, st)
-            : launch_batch_two<T, LPM, P, false, false>(dtab, nb_main, nb_nyq, st);
+// the main pass of the grids c0 .. c1 - 1, one group
+template <typename T>
+hipError_t launch_batch_group(const DepthBatch& host, const DepthBatch* dtab, int c0, int c1, bool disp, bool wx,
+                              hipStream_t st) {
+  const int b0 = host.first_main[c0], nb = host.first_main[c1] - b0;
+  constexpr int L64 = sizeof(T) == 8 ? 64 : 32;         // layout of 33 to 64 nodes
+  bool mix = false;
+  switch (depth_batch_config<T>(host, c0, c1, &mix)) {
+    case 0: return launch_batch_cfg<T, 16, 1, false>(dtab, disp, wx, b0, nb, st);
+    case 1: return mix ? launch_batch_cfg<T, 16, 2, true>(dtab, disp, wx, b0, nb, st)
+                       : launch_batch_cfg<T, 16, 2, false>(dtab, disp, wx, b0, nb, st);
+    case 3:
+    case 4: return mix ? launch_batch_cfg<T, L64, 64 / L64, true>(dtab, disp, wx, b0, nb, st)
+                       : launch_batch_cfg<T, L64, 64 / L64, false>(dtab, disp, wx, b0, nb, st);
+    case 5: return mix ? launch_batch_cfg<T, 64, 2, true>(dtab, disp, wx, b0, nb, st)
+                       : launch_batch_cfg<T, 64, 2, false>(dtab, disp, wx, b0, nb, st);
+    case 6: return launch_batch_cfg<T, 64, 4, false>(dtab, disp, wx, b0, nb, st);
+    case 7: return launch_batch_cfg<T, 64, 8, false>(dtab, disp, wx, b0, nb, st);
+  }
+  return hipErrorInvalidValue;
 }
 
+// The main pass of each run of grids of one group (every mode, and the Nyquist sign
+// replicas as modes of their own), then in float32 one block per Nyquist mode
+// averaging its replicas.
 template <typename T>
-hipError_t launch_depth_batch(const DepthBatch& host, DepthBatch* dtab, int cfg, hipStream_t st) {
-  if (host.n < 1 || host.n > DEPTH_BATCH_MAX || cfg < 0 || cfg >= kNCfg) return hipErrorInvalidValue;
+hipError_t launch_depth_batch(const DepthBatch& host, DepthBatch* dtab, hipStream_t st) {
+  if (host.n < 1 || host.n > DEPTH_BATCH_MAX) return hipErrorInvalidValue;
   const DepthParams& p0 = host.prm[0];
   const bool disp = p0.off_disp >= 0 || p0.off_u3 >= 0;
   const bool wx = p0.off_stress >= 0;
   for (int c = 0; c < host.n; ++c) {
     const DepthParams& p = host.prm[c];
-    if (!p.mtab || !p.rep_out || p.hz || p.nz > kCfgs[cfg].lpm * kCfgs[cfg].p ||
-        (p.off_disp >= 0 || p.off_u3 >= 0) != disp || (p.off_stress >= 0) != wx)
+    if (!p.mtab || !p.rep_out || p.hz || p.nz > 512 || (p.off_disp >= 0 || p.off_u3 >= 0) != disp ||
+        (p.off_stress >= 0) != wx)
       return hipErrorInvalidValue;
   }
   // pageable source: the copy is staged before the call returns
   hipError_t e = hipMemcpyAsync(dtab, &host, sizeof(DepthBatch), hipMemcpyHostToDevice, st);
-  if (e != hipSuccess) return e;
-  const int nm = host.first_main[host.n], nq = host.first_nyq[host.n];
-  switch (cfg) {
-    case 0: return launch_batch_cfg<T, 16, 1>(dtab, disp, wx, nm, nq, st);
-    case 1: return launch_batch_cfg<T, 16, 2>(dtab, disp, wx, nm, nq, st);
-    case 2: return launch_batch_cfg<T, 32, 1>(dtab, disp, wx, nm, nq, st);
-    case 3: return launch_batch_cfg<T, 32, 2>(dtab, disp, wx, nm, nq, st);
-    case 4: return launch_batch_cfg<T, 64, 1>(dtab, disp, wx, nm, nq, st);
-    case 5: return launch_batch_cfg<T, 64, 2>(dtab, disp, wx, nm, nq, st);
-    case 6: return launch_batch_cfg<T, 64, 4>(dtab, disp, wx, nm, nq, st);
-    case 7: return launch_batch_cfg<T, 64, 8>(dtab, disp, wx, nm, nq, st);
+  for (int c0 = 0, c1; c0 < host.n && e == hipSuccess; c0 = c1) {
+    for (c1 = c0 + 1; c1 < host.n && depth_batch_group(host.prm[c1].nz) == depth_batch_group(host.prm[c0].nz);) ++c1;
+    e = launch_batch_group<T>(host, dtab, c0, c1, disp, wx, st);
   }
-  return hipErrorInvalidValue;
+  if constexpr (!mean_in_pass<T>()) {
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_nyq_average_batch<T>, dim3((unsigned)host.first_nyq[host.n]), dim3(NT), 0, st, dtab);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 template <typename T>
@@ -314,10 +333,11 @@ template hipError_t launch_depth<double>(const cpx<double>*, cpx<double>*, const
                                          int);
 template hipError_t launch_depth<float>(const cpx<float>*, cpx<float>*, const DepthParams&, int, hipStream_t, int);
 template hipError_t launch_mode_table<double>(ModeConst<double>*, int, int, double, double, double, hipStream_t);
-template void depth_blocks<double>(int, const DepthParams&, int*, int*);
-template void depth_blocks<float>(int, const DepthParams&, int*, int*);
-template hipError_t launch_depth_batch<double>(const DepthBatch&, DepthBatch*, int, hipStream_t);
-template hipError_t launch_depth_batch<float>(const DepthBatch&, DepthBatch*, int, hipStream_t);
+template void depth_blocks<double>(const DepthParams&, int*, int*);
+template int depth_batch_config<double>(const DepthBatch&, int, int, bool*);
+template void depth_blocks<float>(const DepthParams&, int*, int*);
+template hipError_t launch_depth_batch<double>(const DepthBatch&, DepthBatch*, hipStream_t);
+template hipError_t launch_depth_batch<float>(const DepthBatch&, DepthBatch*, hipStream_t);
 template hipError_t launch_mode_table<float>(ModeConst<float>*, int, int, double, double, double, hipStream_t);
 
 }  // namespace fvim

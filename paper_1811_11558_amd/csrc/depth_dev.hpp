@@ -740,28 +740,30 @@ __device__ __forceinline__ void nyq_average(cpx<T>* __restrict__ out, const cpx<
   }
 }
 
-// One block of a batched depth launch (main modes or, NYQ, the Nyquist
-// averages) over the grids of the table b: block blk belongs to the grid c
-// with first[c] <= blk < first[c + 1].  In float64 the layouts of two nodes per
-// lane hold the narrower ones too, and a grid runs in the narrowest that serves its
-// nz (depth_batch_own): half the lanes or more idle otherwise (57.5 -> 49.5 us for 8 grids
-// of 8 to 64 nodes, 1.6M voxels).  float32 keeps one layout for all: see mean_in_pass.
-template <typename T, int LPM, int P, bool DISP, bool WANTX, bool NYQ>
+// One block of a batched depth launch over grids of the table b: block blk of the
+// table's belongs to the grid c with first_main[c] <= blk < first_main[c + 1].  Each grid
+// runs in the layout of its own application (depth_default_config), whatever the
+// others ask for; MIX: the launch, named for its deepest grid, holds the shallower
+// ones' layouts too.
+template <typename T, int LPM, int P, bool MIX, bool DISP, bool WANTX>
 __device__ __forceinline__ void depth_batch_block(const DepthBatch* __restrict__ b, int blk) {
-  const int* first = NYQ ? b->first_nyq : b->first_main;
   int c = 0;
-  while (c + 1 < b->n && blk >= first[c + 1]) ++c;
+  while (c + 1 < b->n && blk >= b->first_main[c + 1]) ++c;
   const cpx<T>* in = static_cast<const cpx<T>*>(b->in[c]);
   cpx<T>* out = static_cast<cpx<T>*>(b->out[c]);
   const DepthParams& prm = b->prm[c];
-  blk -= first[c];
-  if constexpr (sizeof(T) == 8 && !NYQ && P == 2 && LPM > 16) {
-    if (prm.nz <= 32) return depth_modes<T, 16, 2, DISP, WANTX, NYQ>(in, out, prm, blk);
-    if constexpr (LPM > 32) {
-      if (prm.nz <= 64) return depth_modes<T, 32, 2, DISP, WANTX, NYQ>(in, out, prm, blk);
-    }
+  blk -= b->first_main[c];
+  if constexpr (MIX) {
+    constexpr int CAP = LPM * P, L64 = sizeof(T) == 8 ? 64 : 32;
+    static_assert(CAP <= DEPTH_MIX_NZ, "layouts of a mixed launch");
+    if constexpr (CAP > 16)
+      if (prm.nz <= 16) return depth_modes<T, 16, 1, DISP, WANTX, false>(in, out, prm, blk);
+    if constexpr (CAP > 32)
+      if (prm.nz <= 32) return depth_modes<T, 16, 2, DISP, WANTX, false>(in, out, prm, blk);
+    if constexpr (CAP > 64)
+      if (prm.nz <= 64) return depth_modes<T, L64, 64 / L64, DISP, WANTX, false>(in, out, prm, blk);
   }
-  depth_modes<T, LPM, P, DISP, WANTX, NYQ>(in, out, prm, blk);
+  depth_modes<T, LPM, P, DISP, WANTX, false>(in, out, prm, blk);
 }
 
 template <typename T>

@@ -172,14 +172,15 @@ struct alignas(16) ModeConst {
   T s, r, G0, G0p, H0, H0p, iq, pad;
 };
 
-// Depth pass over several grids in one launch per part: the host table lists
+// Depth pass over several grids in one launch per group of depths: the host table lists
 // each grid's parameters (derived constants filled by depth_derive, rep_out
 // set: the Nyquist sign replicas are modes of the main launch), input and
 // output spectra, and prefix counts of blocks (depth_blocks): first_main for the
 // main launch, first_nyq for the averaging launch (none in float64).  dtab is a device copy
-// target.  Every grid must request the same kinds of output and have nz <=
-// the configuration's capacity.
+// target.  Every grid must request the same kinds of output; grids of one group
+// (depth_batch_group) stand together.
 constexpr int DEPTH_BATCH_MAX = 8;
+constexpr int DEPTH_MIX_NZ = 128;
 struct DepthBatch {
   int n;
   int first_main[DEPTH_BATCH_MAX + 1];
@@ -198,12 +199,10 @@ struct OpBatch {
 };
 // One cooperative launch runs every stage of the batched application, the
 // blocks looping over each stage's blocks and meeting at a grid barrier
-// between stages (float64, strain output only, depth configurations of
-// nz <= 128).  dev: device copy of the table (sizeof(OpBatch)).  Returns
+// between stages (float64, strain output only, nz <= DEPTH_MIX_NZ).  dev: device copy of the table (sizeof(OpBatch)).  Returns
 // hipErrorNotSupported when the batch does not qualify.
 template <typename T>
-hipError_t launch_operator_persistent(OpBatch& host, OpBatch* dev, int depth_cfg, bool disp, bool wx,
-                                      hipStream_t st);
+hipError_t launch_operator_persistent(OpBatch& host, OpBatch* dev, bool disp, bool wx, hipStream_t st);
 // Sign replicas of the Nyquist modes: 2 for each of the ny + kxh - 1 modes on
 // the kx = nx/2 column or the ky = ny/2 row, 2 more for the corner.
 __host__ __device__ inline int depth_replicas(int ny, int kxh) { return 2 * (ny + kxh); }
@@ -218,11 +217,15 @@ __host__ __device__ constexpr bool mean_in_pass() { return sizeof(T) == 8; }
 template <typename T>
 bool depth_nyq_launch(const DepthParams& p) { return !p.rep_out || !mean_in_pass<T>(); }
 
-// blocks of the main and of the averaging launch of a batched pass (rep_out set)
+// blocks of one grid in the main and in the averaging launch of a batched pass
+// (rep_out set)
 template <typename T>
-void depth_blocks(int cfg, const DepthParams& p, int* main, int* nyq);
+void depth_blocks(const DepthParams& p, int* main, int* nyq);
+int depth_batch_group(int nz);
 template <typename T>
-hipError_t launch_depth_batch(const DepthBatch& host, DepthBatch* dtab, int cfg, hipStream_t st);
+int depth_batch_config(const DepthBatch& b, int c0, int c1, bool* mixed);
+template <typename T>
+hipError_t launch_depth_batch(const DepthBatch& host, DepthBatch* dtab, hipStream_t st);
 
 template <typename T>
 hipError_t launch_mode_table(ModeConst<T>* tab, int nx, int ny, double lx, double ly, double h, hipStream_t st);
@@ -234,7 +237,6 @@ hipError_t launch_depth(const cpx<T>* in, cpx<T>* out, const DepthParams& p, int
                         int part = 0);
 int depth_num_configs();
 bool depth_config_valid(int id, int nz);
-int depth_batch_config(int nz);
 template <typename T>
 int depth_default_config(int nz);
 

@@ -22,7 +22,7 @@ namespace {
 
 namespace cg = cooperative_groups;
 
-template <typename T, int LPM, int P>
+template <typename T, int LPM, int P, bool MIX>
 __global__ __launch_bounds__(NT) void k_op_persistent(const OpBatch* __restrict__ t) {
   __shared__ double red[NT / 64];
   cg::grid_group grid = cg::this_grid();
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(NT) void k_op_persistent(const OpBatch* __restrict_
   }
   grid.sync();
   const DepthBatch* d = &t->d;
-  for (int blk = b0; blk < d->first_main[d->n]; blk += G) depth_batch_block<T, LPM, P, false, false, false>(d, blk);
+  for (int blk = b0; blk < d->first_main[d->n]; blk += G) depth_batch_block<T, LPM, P, MIX, false, false>(d, blk);
   grid.sync();
   const XformBatch& x2 = t->x[2];
   for (int blk = b0; blk < x2.first[x2.n]; blk += G) {
@@ -60,23 +60,21 @@ __global__ __launch_bounds__(NT) void k_op_persistent(const OpBatch* __restrict_
 }  // namespace
 
 template <typename T>
-hipError_t launch_operator_persistent(OpBatch& host, OpBatch* dev, int depth_cfg, bool disp, bool wx,
-                                      hipStream_t st) {
+hipError_t launch_operator_persistent(OpBatch& host, OpBatch* dev, bool disp, bool wx, hipStream_t st) {
   if (disp || wx || !std::is_same<T, double>::value) return hipErrorNotSupported;
+  if (host.d.n < 1 || host.d.n > DEPTH_BATCH_MAX) return hipErrorInvalidValue;
   const void* kern = nullptr;
-  switch (depth_cfg) {          // depth_batch_config of nz <= 16, 32, 64, 128
-    case 0: kern = (const void*)k_op_persistent<double, 16, 1>; break;
-    case 1: kern = (const void*)k_op_persistent<double, 16, 2>; break;
-    case 3: kern = (const void*)k_op_persistent<double, 32, 2>; break;
-    case 5: kern = (const void*)k_op_persistent<double, 64, 2>; break;
+  bool mix = false;
+  switch (depth_batch_config<double>(host.d, 0, host.d.n, &mix)) {  // default layouts of nz <= 16, 32, 64, 128
+    case 0: kern = (const void*)k_op_persistent<double, 16, 1, false>; break;
+    case 1: kern = (const void*)k_op_persistent<double, 16, 2, true>; break;
+    case 4: kern = (const void*)k_op_persistent<double, 64, 1, true>; break;
+    case 5: kern = (const void*)k_op_persistent<double, 64, 2, true>; break;
     default: return hipErrorNotSupported;
   }
-  const int cap[] = {16, 32, 0, 64, 0, 128};      // nodes per mode of those layouts
-  if (host.d.n < 1 || host.d.n > DEPTH_BATCH_MAX) return hipErrorInvalidValue;
   for (int c = 0; c < host.d.n; ++c) {
     const DepthParams& q = host.d.prm[c];
-    if (!q.mtab || !q.rep_out || q.hz || q.nz > cap[depth_cfg] || q.off_disp >= 0 || q.off_u3 >= 0 ||
-        q.off_stress >= 0)
+    if (!q.mtab || !q.rep_out || q.hz || q.nz > DEPTH_MIX_NZ || q.off_disp >= 0 || q.off_u3 >= 0 || q.off_stress >= 0)
       return hipErrorInvalidValue;
   }
   size_t lds = 0;
@@ -103,7 +101,7 @@ hipError_t launch_operator_persistent(OpBatch& host, OpBatch* dev, int depth_cfg
   return hipLaunchCooperativeKernel(kern, dim3(grid), dim3(NT), args, (unsigned)lds, st);
 }
 
-template hipError_t launch_operator_persistent<double>(OpBatch&, OpBatch*, int, bool, bool, hipStream_t);
-template hipError_t launch_operator_persistent<float>(OpBatch&, OpBatch*, int, bool, bool, hipStream_t);
+template hipError_t launch_operator_persistent<double>(OpBatch&, OpBatch*, bool, bool, hipStream_t);
+template hipError_t launch_operator_persistent<float>(OpBatch&, OpBatch*, bool, bool, hipStream_t);
 
 }  // namespace fvim

@@ -591,3 +591,46 @@ def test_batched_grids_run_in_their_own_depth_layout(shapes):
             assert sh[2] <= 16 or torch.equal(got[i][k], alone[k]), (sh, k)
     for c in ctxs:
         c.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refined"])
+@pytest.mark.parametrize("shapes", [
+    [(16, 16, 5), (32, 16, 16)],
+    [(16, 16, 5), (32, 16, 17), (16, 16, 32)],
+    [(16, 32, 16), (16, 16, 20), (32, 16, 33), (16, 16, 64)],
+    [(16, 16, 8), (16, 16, 32), (16, 16, 40), (16, 8, 65), (16, 16, 128), (4, 8, 6), (8, 4, 64), (16, 4, 100),
+     (32, 8, 12), (16, 16, 63)],
+    [(16, 16, 7), (16, 16, 129), (16, 16, 64), (16, 8, 300), (8, 16, 256), (16, 16, 100)],
+    [(1024, 4, 5), (16, 16, 40), (4, 1024, 40), (8, 8, 130), (1024, 8, 20)],
+    [(1024, 8, 48), (8, 1024, 48)],
+    [(1024, 128, 12), (16, 16, 40), (1024, 128, 20)]])     # (spectra of the long ones over 256 MB)
+def test_batched_grids_have_the_bits_of_their_own_application(shapes, precision):
+    """Any mix of depths and side lengths in a batch: every field is bitwise
+    that of the grid batched alone and of its separate application (default
+    choices), whatever layout the deepest grid of the batch asks for, and
+    whatever depth layout and side-stream option its context holds."""
+    from paper_1811_11558_amd import operator_apply_batch
+    dev = torch.device("cuda")
+    rng = np.random.default_rng(sum(s[2] for s in shapes))
+    for want in (("strain",), ("strain", "stress", "disp", "surf_u3")):
+        ctxs = [_ctx(grid_dict(nx, ny, nz, 1.0, 1.0, 0.25), precision=precision) for nx, ny, nz in shapes]
+        eps = [torch.from_numpy(rng.standard_normal((6, nz, ny, nx))).to(dev) for nx, ny, nz in shapes]
+        ts = [torch.from_numpy(rng.standard_normal((3, ny, nx))).to(dev) for nx, ny, nz in shapes]
+        got = operator_apply_batch(ctxs, eps, ts, want=want)
+        for i, sh in enumerate(shapes):
+            alone = operator_apply_batch(ctxs[i:i + 1], eps[i:i + 1], ts[i:i + 1], want=want)[0]
+            own = ctxs[i].operator_apply(eps[i], ts[i], want=want)
+            torch.cuda.synchronize()
+            for k in want:
+                same = torch.equal(got[i][k], alone[k]), torch.equal(got[i][k], own[k])
+                _say("batch bits", precision, sh, k, same)
+                assert all(same), (precision, sh, k, same)
+        for c in ctxs:
+            c.set_option(c.OPT_SIDE_STREAM, 1)
+            c.set_option(c.OPT_DEPTH_CONFIG, max(i for i, cap in enumerate((16, 32, 32, 64, 64, 128, 256, 512))
+                                                 if c.nz <= cap < 4 * c.nz))
+        again = operator_apply_batch(ctxs, eps, ts, want=want)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a[k], b[k]) for a, b in zip(again, got) for k in want)
+        for c in ctxs:
+            c.close()
