@@ -167,11 +167,13 @@ int fvim_operator_apply_noalloc(fvim_ctx* ctx, const double* eps_p, const double
  * stream of ctxs[0].  Contexts whose transform lengths nx and ny are both at
  * most 512 share one launch per in-plane transform stage (up to 8 grids per
  * launch, each with its length's default transform choice); longer ones run
- * their own applications with their own transform choices.  The depth pass of up
- * to 8 others is one launch for those of at most 128 nodes, one for those of
+ * their own transform launches with their own choices.  The depth pass of up
+ * to 8 contexts is one launch for those of at most 128 nodes, one for those of
  * 129 to 256 and one for deeper ones (in float32 one more averages the Nyquist
- * modes' sign replicas), a table mapping each block to its grid.  Each grid runs
- * in the default depth layout of its own nz.  A context's results are therefore the same in any batch (bitwise),
+ * modes' sign replicas), a table mapping each block to its grid; longer contexts
+ * with spectra of more than 64 MB (or 256 MB together) run one after the other
+ * instead.  Each grid runs in the default depth layout of its
+ * own nz.  A context's results are therefore the same in any batch (bitwise),
  * and agree with its separate application up to the summation order of the
  * depth layout and transform choices (bitwise when both are the defaults).
  * The arrays hold one device pointer

@@ -449,11 +449,9 @@ int tune_operator(fvim_ctx* c, OpPlan<T>& P) {
   return time_choices(c, lx, [&](FftChoice ch) { return run_x_inv<T>(c, P, st, ch); }, &P.ch[3]);
 }
 
-// One application: forward transforms, depth pass, mean mode (float32 path) and
-// inverse transforms, the depth pass in layout cfg.  ss != st: the Nyquist modes'
-// depth launch runs on ss beside the other modes'.
+// Forward transforms of the input planes: real fields -> mode-major B.
 template <typename T>
-int op_run(fvim_ctx* c, OpPlan<T>& P, int cfg, hipStream_t st, hipStream_t ss, StageTimer& tm) {
+int op_forward(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, StageTimer& tm) {
   hipError_t e;
   tm.begin(FVIM_STAGE_XFWD, st);
   if ((e = run_x_fwd<T>(c, P, st, P.ch[0])) != hipSuccess) return fail_hip(e, "x_r2c");
@@ -461,6 +459,31 @@ int op_run(fvim_ctx* c, OpPlan<T>& P, int cfg, hipStream_t st, hipStream_t ss, S
   tm.begin(FVIM_STAGE_YFWD, st);
   if ((e = run_y_fwd<T>(c, P, st, P.ch[1])) != hipSuccess) return fail_hip(e, "y_fwd");
   tm.end();
+  return FVIM_OK;
+}
+
+// Mean mode (float32 path) and inverse transforms: mode-major A -> outputs.
+template <typename T>
+int op_inverse(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, StageTimer& tm) {
+  hipError_t e;
+  if (P.k0x && (e = launch_k0_fields(P.wsum, P.wbpp, P.tsum, P.wbpp, P.padd, P.prm, st)) != hipSuccess)
+    return fail_hip(e, "k0");
+  tm.begin(FVIM_STAGE_YINV, st);
+  if ((e = run_y_inv<T>(c, P, st, P.ch[2])) != hipSuccess) return fail_hip(e, "y_inv");
+  tm.end();
+  tm.begin(FVIM_STAGE_XINV, st);
+  if ((e = run_x_inv<T>(c, P, st, P.ch[3])) != hipSuccess) return fail_hip(e, "x_c2r");
+  tm.end();
+  return FVIM_OK;
+}
+
+// One application, the depth pass in layout cfg.  ss != st: the Nyquist modes'
+// depth launch runs on ss beside the other modes'.
+template <typename T>
+int op_run(fvim_ctx* c, OpPlan<T>& P, int cfg, hipStream_t st, hipStream_t ss, StageTimer& tm) {
+  hipError_t e;
+  int rc = op_forward<T>(c, P, st, tm);
+  if (rc) return rc;
   if (ss != st && (e = join(c->ev_spec, st, ss)) != hipSuccess) return fail_hip(e, "fork");
   tm.begin(FVIM_STAGE_DEPTH, st);
   if ((e = launch_depth<T>(P.B, P.A, P.prm, cfg, st, 1)) != hipSuccess) return fail_hip(e, "depth");
@@ -472,15 +495,7 @@ int op_run(fvim_ctx* c, OpPlan<T>& P, int cfg, hipStream_t st, hipStream_t ss, S
     tm.end();
   }
   if (ss != st && (e = join(c->ev_nyq, ss, st)) != hipSuccess) return fail_hip(e, "join");
-  if (P.k0x && (e = launch_k0_fields(P.wsum, P.wbpp, P.tsum, P.wbpp, P.padd, P.prm, st)) != hipSuccess)
-    return fail_hip(e, "k0");
-  tm.begin(FVIM_STAGE_YINV, st);
-  if ((e = run_y_inv<T>(c, P, st, P.ch[2])) != hipSuccess) return fail_hip(e, "y_inv");
-  tm.end();
-  tm.begin(FVIM_STAGE_XINV, st);
-  if ((e = run_x_inv<T>(c, P, st, P.ch[3])) != hipSuccess) return fail_hip(e, "x_c2r");
-  tm.end();
-  return FVIM_OK;
+  return op_inverse<T>(c, P, st, tm);
 }
 
 // u = M[t] + N[C : eps_p] with any subset of outputs (see fvim.h).  With
@@ -560,8 +575,15 @@ int operator_apply_t(fvim_ctx* c, const double* eps_p, const double* traction, d
 
 // Several contexts (grids may differ) on the stream of the first.  Grids whose
 // transform lengths are both at most 2^XFORM_BATCH_MAX_LOGN share one launch per
-// stage (up to XFORM_BATCH_MAX or DEPTH_BATCH_MAX grids each, the default
-// choices); longer ones run their own applications, with their own choices.
+// transform stage (up to XFORM_BATCH_MAX grids each, the default choices); longer
+// ones keep transform launches of their own, with their own choices.  The depth
+// pass is shared, up to DEPTH_BATCH_MAX grids of one group in a launch, also by the
+// longer ones while their spectra are small: at most 64 MB each, and together within
+// BATCH_JOIN_BYTES, the last-level cache (8 grids of 16 x 1024 x 8 float64, 119 MB:
+// 314 us, with depth launches of their own 381).  Others run one after the other,
+// each with its spectra in the cache from stage to stage: 8 of 1024 x 64 x 32 (1.6 GB)
+// 1605 us, 1730 stage by stage; 2 of 1024 x 128 x 16 float32 (210 MB) 309 and 328.
+constexpr size_t BATCH_JOIN_BYTES = (size_t)256 << 20;
 template <typename T>
 int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps, const double* const* tr,
                            double* const* strain, double* const* stress, double* const* disp,
@@ -599,9 +621,17 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
   const bool all_shared = (int)bat.size() == n;
   std::vector<char> shared(n, 0);
   for (int i : bat) shared[i] = 1;
+  auto spectra = [&](int i) {
+    const DepthParams& p = P[i].prm;
+    return (size_t)p.kxh * p.ny * (p.ld_in + p.ld_out) * sizeof(cpx<T>);
+  };
+  size_t sum = 0;
+  for (int i = 0; i < n; ++i)
+    if (!shared[i] && spectra(i) <= BATCH_JOIN_BYTES / 4) sum += spectra(i);
+  auto joins = [&](int i) { return shared[i] || (sum <= BATCH_JOIN_BYTES && spectra(i) <= BATCH_JOIN_BYTES / 4); };
   std::vector<int> ord;                              // grids of the shared depth pass, group by group
   for (int i = 0; i < n; ++i) {
-    if (shared[i]) ord.push_back(i);
+    if (joins(i)) ord.push_back(i);
     else if ((rc = op_run<T>(cs[i], P[i], -1, st, st, tm))) return restore(rc);
   }
   if (ord.empty()) return restore(FVIM_OK);
@@ -691,6 +721,8 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     if (e != hipErrorNotSupported) return restore(fail_hip(e, "persistent batched operator"));
     (void)hipGetLastError();
   }
+  for (int i : ord)
+    if (!shared[i] && (rc = op_forward<T>(cs[i], P[i], st, tm))) return restore(rc);
   if ((rc = xform(0, FVIM_STAGE_XFWD)) || (rc = xform(1, FVIM_STAGE_YFWD))) return restore(rc);
   for (size_t i0 = 0; i0 < ord.size(); i0 += DEPTH_BATCH_MAX) {
     DepthBatch b;
@@ -700,6 +732,8 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     tm.end();
     if (e != hipSuccess) return restore(fail_hip(e, "batched depth pass"));
   }
+  for (int i : ord)
+    if (!shared[i] && (rc = op_inverse<T>(cs[i], P[i], st, tm))) return restore(rc);
   for (int i : bat) {
     if (!P[i].k0x) continue;
     hipError_t e = launch_k0_fields(P[i].wsum, P[i].wbpp, P[i].tsum, P[i].wbpp, P[i].padd, P[i].prm, st);

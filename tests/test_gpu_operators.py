@@ -634,3 +634,25 @@ def test_batched_grids_have_the_bits_of_their_own_application(shapes, precision)
         assert all(torch.equal(a[k], b[k]) for a, b in zip(again, got) for k in want)
         for c in ctxs:
             c.close()
+
+
+def test_batched_depth_pass_is_shared_with_long_grids_of_small_spectra():
+    """Grids too long for the shared transform launches still share the depth
+    launch (one for all here), not one each; grids whose spectra exceed the
+    cache keep applications of their own."""
+    from paper_1811_11558_amd import operator_apply_batch
+    dev = torch.device("cuda")
+    for shapes, depth, x_fwd in (([(1024, 8, 6)] * 3 + [(16, 1024, 12), (32, 16, 40)], 1, 5),
+                                 ([(1024, 128, 12), (1024, 8, 6), (16, 16, 8)], 2, 3)):
+        ctxs = [_ctx(grid_dict(nx, ny, nz, 1.0, 1.0, 0.25)) for nx, ny, nz in shapes]
+        eps = [torch.zeros(c.tensor_shape, dtype=torch.float64, device=dev) for c in ctxs]
+        ts = [torch.ones((3, c.ny, c.nx), dtype=torch.float64, device=dev) for c in ctxs]
+        operator_apply_batch(ctxs, eps, ts)
+        ctxs[0].set_timing(True)
+        operator_apply_batch(ctxs, eps, ts)
+        times = ctxs[0].stage_times()
+        _say("depth launches", shapes, times)
+        assert times["depth"][1] == depth
+        assert times["x_fwd"][1] == x_fwd
+        for c in ctxs:
+            c.close()
