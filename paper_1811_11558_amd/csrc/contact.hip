@@ -206,13 +206,17 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_pk_gap(const cpx<double>* _
   const Pair q = row_pair<LOGN>(ny);
   SurfTw<LOGN> t;
   cpx<double> v[1][4], pv[4], hv[4], po[4];
-  load_pair<LOGN>(p, q, pv);
-  load_pair<LOGN>(h, q, hv);
-  if (!FIRST) load_pair<LOGN>(pold, q, po);
+  auto fields = [&]() {
+    load_pair<LOGN>(p, q, pv);
+    load_pair<LOGN>(h, q, hv);
+    if (!FIRST) load_pair<LOGN>(pold, q, po);
+  };
+  if (!S::TIGHT) fields();
   surf_load_tw<LOGN>(tw, q.jj, t);
   double scale = 1.0, ov = 0.0;
   if (!FIRST) scale = load_scale<S::NW>(part, ldp, nb, sc, sh, ov);
   rows_in<LOGN>(v, buf, q, t, X);
+  if (S::TIGHT) fields();
   double s[3] = {0.0, 0.0, 0.0}, o[3];
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
@@ -300,7 +304,7 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_pk_dir(const double* __rest
   load_pair<LOGN>(p, q, pv);
   load_pair<LOGN>(g, q, gv);
   load_pair<LOGN>(t, q, v[0]);
-  surf_load_tw<LOGN>(tw, q.jj, w);
+  if (!S::TIGHT) surf_load_tw<LOGN>(tw, q.jj, w);
   // The mean as gbar + glo: gbar alone is off by its rounding, which at the
   // gap's rounding floor is as large as the gap itself and, once in t, is
   // carried and amplified from direction to direction.
@@ -332,6 +336,7 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_pk_dir(const double* __rest
     v[0][m].y = pv[m].y > 0.0 ? gv[m].y - gbar - glo + (beta != 0.0 ? beta * v[0][m].y : 0.0) : 0.0;
   }
   store_pair<LOGN>(t, q, v[0]);
+  if (S::TIGHT) surf_load_tw<LOGN>(tw, q.jj, w);
   rows_out<LOGN>(v, buf, q, w, X);
 }
 
@@ -349,13 +354,17 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_pk_curv(const cpx<double>* 
   const Pair q = row_pair<LOGN>(ny);
   SurfTw<LOGN> w;
   cpx<double> v[1][4], pv[4], gv[4], tv[4];
-  load_pair<LOGN>(p, q, pv);
-  load_pair<LOGN>(g, q, gv);
-  load_pair<LOGN>(t, q, tv);
+  auto fields = [&]() {
+    load_pair<LOGN>(p, q, pv);
+    load_pair<LOGN>(g, q, gv);
+    load_pair<LOGN>(t, q, tv);
+  };
+  if (!S::TIGHT) fields();
   surf_load_tw<LOGN>(tw, q.jj, w);
   const double gbar = sc[S_GBAR], glo = sc[S_GLO];
   if (blockIdx.x == 0 && threadIdx.x == 0) sc[S_GOLD] = sc[S_G];
   rows_in<LOGN>(v, buf, q, w, X);
+  if (S::TIGHT) fields();
   double s[4] = {0.0, 0.0, 0.0, 0.0}, o[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
@@ -416,7 +425,7 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_pk_update(double* __restric
   load_pair<LOGN>(p, q, v[0]);
   load_pair<LOGN>(g, q, gv);
   load_pair<LOGN>(t, q, tv);
-  surf_load_tw<LOGN>(tw, q.jj, w);
+  if (!S::TIGHT) surf_load_tw<LOGN>(tw, q.jj, w);
   const double gbar = sc[S_GBAR], glo = sc[S_GLO];
   const double* pr = part + PR * ldp;
   double a[4], den[1];
@@ -444,6 +453,7 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_pk_update(double* __restric
   store_pair<LOGN>(p, q, v[0]);
   surf_sums<2, S::NW>(s, sh, o);
   surf_put<2>(part + PU * ldp, ldp, o);
+  if (S::TIGHT) surf_load_tw<LOGN>(tw, q.jj, w);
   rows_out<LOGN>(v, buf, q, w, X);
 }
 

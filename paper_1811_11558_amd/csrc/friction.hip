@@ -378,14 +378,18 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_f_grad(const cpx<double>* _
   SurfTw<LOGN> t;
   cpx<double> u[1][4], yv[4], uev[4];
   double r[4];
-  load_row<LOGN>(y, n, q, yv);
-  if (ue) load_row<LOGN>(ue, n, q, uev);
+  auto fields = [&]() {
+    load_row<LOGN>(y, n, q, yv);
+    if (ue) load_row<LOGN>(ue, n, q, uev);
 #pragma unroll
-  for (int m = 0; m < 4; ++m) r[m] = q.on ? rho[q.off + q.jj + m * S::M] : 0.0;
+    for (int m = 0; m < 4; ++m) r[m] = q.on ? rho[q.off + q.jj + m * S::M] : 0.0;
+  };
+  if (!S::TIGHT) fields();
   surf_load_tw<LOGN>(tw, q.jj, t);
   const double l0 = sc[F_LAMA], l1 = sc[F_LAMA + 1];
   if (blockIdx.x == 0 && threadIdx.x == 0) sc[F_T] = sc[F_TN];   // of the last k_f_momentum
   row_in<LOGN>(u, buf, q, ny, t, X);
+  if (S::TIGHT) fields();
   ProjSums p;
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
@@ -468,7 +472,7 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_f_momentum(double* __restri
   cpx<double> v[1][4], qv[4], nv[4];
   load_row<LOGN>(q, n, r, qv);
   load_row<LOGN>(qn, n, r, nv);
-  surf_load_tw<LOGN>(tw, r.jj, w);
+  if (!S::TIGHT) surf_load_tw<LOGN>(tw, r.jj, w);
   const double t = sc[F_T];
   double s[2];
   surf_totals<2, S::NW>(nb, sh, s, [&](int i, double (&x)[2]) {
@@ -488,6 +492,7 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_f_momentum(double* __restri
   for (int m = 0; m < 4; ++m) v[0][m] = axpy(nv[m], beta, sub(nv[m], qv[m]));
   store_row<LOGN>(y, n, r, v[0]);
   store_row<LOGN>(q, n, r, nv);
+  if (S::TIGHT) surf_load_tw<LOGN>(tw, r.jj, w);
   row_out<LOGN>(v, buf, r, ny, w, X);
 }
 

@@ -33,6 +33,13 @@ struct Surf {
   static constexpr int L0 = (LOGN & 1) ? 1 : 2;      // log2 of the first stage's radix
   static constexpr int NST = (LOGN - L0) / 2;        // radix-4 stages after it
   static constexpr int NW = NTH / 64;                // waves
+  // Blocks of 1024 threads (length 4096) have 128 registers a thread: with the
+  // twiddles (60) loaded beside the fields, or three fields beside a transform, 12
+  // to 468 bytes a thread lay in scratch memory.  They load the twiddles after the
+  // pointwise work that precedes a transform, the fields after a transform: us per
+  // iteration of the contact at 4096^2 1840 -> 1262 and 4096 x 64 128 -> 84, of the
+  // tangential contact 1765 -> 1479 and 66 -> 56.
+  static constexpr bool TIGHT = NTH >= 1024;
 };
 
 // twiddles of the thread's butterfly in the stages after the first
@@ -220,7 +227,7 @@ __device__ __forceinline__ void surf_sums(const double (&v)[K], double* sh, doub
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       double t = 0.0;
-#pragma unroll
+#pragma unroll(NW > 8 ? 4 : NW)        // (16 waves: not all K * NW values in registers)
       for (int i = 0; i < NW; ++i) t += sh[k * NW + i];
       out[k] = t;
     }

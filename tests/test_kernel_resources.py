@@ -42,7 +42,9 @@ def scratch(tmp_path_factory):
 
 
 # the depth pass in the layout of 33 to 64 float64 nodes, every variant
-KERNELS = [r"k_depth(_batch)?IdLi64ELi1E"]
+# the row and column kernels of the contact iterations, up to 4096 points a side
+KERNELS = [r"k_depth(_batch)?IdLi64ELi1E",
+           r"k_(rows_fwd|rows_inv|columns|pk_\w+|f_rows_fwd|f_rows_inv|f_grad|f_momentum)ILi"]
 
 
 @pytest.mark.parametrize("pattern", KERNELS)
