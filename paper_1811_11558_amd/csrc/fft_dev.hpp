@@ -83,14 +83,16 @@ __host__ __device__ constexpr int col_lds_bytes(int n, int tile) {
 // Row pairs (two rows of reals are one complex transform) per block of the row
 // (x) kernels.  The X[p][kx][y] side is touched in runs of 2 row_seq elements
 // of one kx: 128 bytes by default, as far as a block of 1024 threads allows (half
-// that: 1662 / 1619 us against 1364 / 1381 for x_fwd / x_inv at 1024^2 x 64 float64).
+// that: 1662 / 1619 us against 1364 / 1381 for x_fwd / x_inv at 1024^2 x 64 float64);
+// of 512 at 4096 in float64, where 1024 threads of 128 registers spill: x_fwd 91 -> 75
+// us at 4096 x 32 x 16, 332 -> 259 at 4096 x 256 x 8 (x_inv 81 -> 76, 306 -> 299).
 // TILE 3: a block of the launches over several grids, NT threads.
 template <typename T>
 __host__ __device__ constexpr int row_seq(int n, int tile) {
   const int m = n / row_elems(n);
   if (tile == 3) return NT / m;
   int s = tile_scale(128, tile) / (2 * (int)sizeof(cpx<T>));
-  while (s > 1 && s * m > 1024) s /= 2;
+  while (s > 1 && s * m > (sizeof(T) == 8 && n >= 4096 ? 512 : 1024)) s /= 2;
   while (s * m < 64) s *= 2;            // at least one wave
   return s;
 }
@@ -223,8 +225,13 @@ __device__ __forceinline__ void group_stages(cpx<T>* v, int k, const cpx<T>* __r
   }
   if constexpr (sizeof...(Rest) > 0) {
 #pragma unroll
-    for (int m1 = 0; m1 < R1; ++m1)
+    for (int m1 = 0; m1 < R1; ++m1) {
+      // Float64 columns of 4096, 1024 threads of 128 registers: the groups one after
+      // the other, or their twiddles, loaded all at once, spill (y_fwd / y_inv 275 / 368
+      // -> 256 / 317 us at 256 x 4096 x 8).
+      if constexpr (sizeof(T) == 8 && N >= 4096) __builtin_amdgcn_sched_barrier(0);
       group_stages<T, INV, N, LS + ilog2c(R1), ZERO>(v + m1 * S, k + (m1 << LS), tw, Radices<Rest...>{});
+    }
   }
 }
 // register index of a group's values -> its output index idx

@@ -563,6 +563,24 @@ def test_column_passes_at_every_tile_and_precision(nx, ny, nz):
         c.close()
 
 
+@pytest.mark.parametrize("nx,ny,nz", [(4096, 4, 3), (4096, 8, 2), (4096, 16, 2), (2048, 8, 2)])
+def test_row_passes_at_the_longest_lengths(nx, ny, nz):
+    """Rows of 2048 and 4096 in both precisions, planes of one, two and four
+    blocks of row pairs (bounds of the column test)."""
+    g = grid_dict(nx, ny, nz, nx / 512, 1.0, 0.25)     # (the oracle refuses elements thicker than |q h| = 1200)
+    e, t = filtered_eigenstrain(g, seed=nx + ny), filtered_traction(g, seed=nz + 9)
+    ref = ora.apply(g, E, NU, eps_p=e, traction=t)
+    dev = torch.device("cuda")
+    for prec, bound in (("fp64", TOL), ("fp32_refined", 2e-6)):
+        c = _ctx(g, precision=prec)
+        out = c.operator_apply(torch.from_numpy(e).to(dev), torch.from_numpy(t).to(dev), want=("strain", "surf_u3"))
+        torch.cuda.synchronize()
+        errs = [_rel(out[k].cpu().numpy(), ref[k]) for k in ("strain", "surf_u3")]
+        _say("rows", (nx, ny, nz), prec, errs)
+        assert max(errs) <= bound, (prec, errs)
+        c.close()
+
+
 @pytest.mark.parametrize("shapes", [[(16, 16, 20), (32, 16, 40), (16, 32, 33)],
                                     [(16, 16, 10), (32, 16, 32), (16, 16, 64), (16, 32, 100), (64, 16, 65)]])
 def test_batched_grids_run_in_their_own_depth_layout(shapes):

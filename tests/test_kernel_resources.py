@@ -42,8 +42,9 @@ def scratch(tmp_path_factory):
 
 
 # the depth pass in the layout of 33 to 64 float64 nodes, every variant
-# the row and column kernels of the contact iterations, up to 4096 points a side
-KERNELS = [r"k_depth(_batch)?IdLi64ELi1E",
+# the row and column kernels of the contact iterations, up to 4096 points a side;
+# the float64 row transforms, up to that length
+KERNELS = [r"k_depth(_batch)?IdLi64ELi1E", r"k_x_(r2c|c2r)Id",
            r"k_(rows_fwd|rows_inv|columns|pk_\w+|f_rows_fwd|f_rows_inv|f_grad|f_momentum)ILi"]
 
 
