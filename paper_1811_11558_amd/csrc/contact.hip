@@ -206,17 +206,20 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_pk_gap(const cpx<double>* _
   const Pair q = row_pair<LOGN>(ny);
   SurfTw<LOGN> t;
   cpx<double> v[1][4], pv[4], hv[4], po[4];
-  auto fields = [&]() {
+  if (!S::TIGHT) {
     load_pair<LOGN>(p, q, pv);
     load_pair<LOGN>(h, q, hv);
     if (!FIRST) load_pair<LOGN>(pold, q, po);
-  };
-  if (!S::TIGHT) fields();
+  }
   surf_load_tw<LOGN>(tw, q.jj, t);
   double scale = 1.0, ov = 0.0;
   if (!FIRST) scale = load_scale<S::NW>(part, ldp, nb, sc, sh, ov);
   rows_in<LOGN>(v, buf, q, t, X);
-  if (S::TIGHT) fields();
+  if (S::TIGHT) {
+    load_pair<LOGN>(p, q, pv);
+    load_pair<LOGN>(h, q, hv);
+    if (!FIRST) load_pair<LOGN>(pold, q, po);
+  }
   double s[3] = {0.0, 0.0, 0.0}, o[3];
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
@@ -354,17 +357,20 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_pk_curv(const cpx<double>* 
   const Pair q = row_pair<LOGN>(ny);
   SurfTw<LOGN> w;
   cpx<double> v[1][4], pv[4], gv[4], tv[4];
-  auto fields = [&]() {
+  if (!S::TIGHT) {
     load_pair<LOGN>(p, q, pv);
     load_pair<LOGN>(g, q, gv);
     load_pair<LOGN>(t, q, tv);
-  };
-  if (!S::TIGHT) fields();
+  }
   surf_load_tw<LOGN>(tw, q.jj, w);
   const double gbar = sc[S_GBAR], glo = sc[S_GLO];
   if (blockIdx.x == 0 && threadIdx.x == 0) sc[S_GOLD] = sc[S_G];
   rows_in<LOGN>(v, buf, q, w, X);
-  if (S::TIGHT) fields();
+  if (S::TIGHT) {
+    load_pair<LOGN>(p, q, pv);
+    load_pair<LOGN>(g, q, gv);
+    load_pair<LOGN>(t, q, tv);
+  }
   double s[4] = {0.0, 0.0, 0.0, 0.0}, o[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) {

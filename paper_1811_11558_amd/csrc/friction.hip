@@ -378,18 +378,22 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_f_grad(const cpx<double>* _
   SurfTw<LOGN> t;
   cpx<double> u[1][4], yv[4], uev[4];
   double r[4];
-  auto fields = [&]() {
+  if (!S::TIGHT) {
     load_row<LOGN>(y, n, q, yv);
     if (ue) load_row<LOGN>(ue, n, q, uev);
 #pragma unroll
     for (int m = 0; m < 4; ++m) r[m] = q.on ? rho[q.off + q.jj + m * S::M] : 0.0;
-  };
-  if (!S::TIGHT) fields();
+  }
   surf_load_tw<LOGN>(tw, q.jj, t);
   const double l0 = sc[F_LAMA], l1 = sc[F_LAMA + 1];
   if (blockIdx.x == 0 && threadIdx.x == 0) sc[F_T] = sc[F_TN];   // of the last k_f_momentum
   row_in<LOGN>(u, buf, q, ny, t, X);
-  if (S::TIGHT) fields();
+  if (S::TIGHT) {
+    load_row<LOGN>(y, n, q, yv);
+    if (ue) load_row<LOGN>(ue, n, q, uev);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) r[m] = q.on ? rho[q.off + q.jj + m * S::M] : 0.0;
+  }
   ProjSums p;
 #pragma unroll
   for (int m = 0; m < 4; ++m) {

@@ -227,7 +227,7 @@ __device__ __forceinline__ void surf_sums(const double (&v)[K], double* sh, doub
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       double t = 0.0;
-#pragma unroll(NW > 8 ? 4 : NW)        // (16 waves: not all K * NW values in registers)
+#pragma unroll NW > 8 ? 4 : NW         // (16 waves: not all K * NW values in registers)
       for (int i = 0; i < NW; ++i) t += sh[k * NW + i];
       out[k] = t;
     }
