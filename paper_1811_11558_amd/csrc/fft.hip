@@ -163,6 +163,8 @@ struct ColLaunch {
   template <int L, int TILE, int RADIX>
   hipError_t go() {
     constexpr int B = col_batch<T>(1 << L, TILE);
+    if constexpr (TILE == 1 && col_batch<T>(1 << L, THIN) < B)
+      if (NP <= 4) return go<L, THIN, RADIX>();
     const dim3 grid((unsigned)(kxh * ((NP + B - 1) / B))), blk(col_threads<T>(1 << L, TILE));
     if (FWD) {
       if (stream_in)

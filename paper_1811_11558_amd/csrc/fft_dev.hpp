@@ -55,10 +55,15 @@ __host__ __device__ constexpr int reg_elems(int n) {
 // S[kx][ky][p] is touched in runs of B consecutive planes: 128 bytes, whole
 // lines, by default (half or twice that with TILE 0 or 2), as far as a block of
 // 1024 threads with reg_elems values each allows.  64-byte runs: y_inv 104
-// against 71 us at 256^2 x 64 in float64, 1925 against 1360 at 1024^2 x 64.
+// against 71 us at 256^2 x 64 in float64, 1925 against 1360 at 1024^2 x 64.  THIN:
+// 4 planes, for a traction's 3 or the surface displacement's 1, where most of a
+// default tile's threads only repeat the others' loads (y_fwd of 3 planes 32.6 ->
+// 16.8 us at 1024^2 in float64, 40.5 -> 14.9 in float32, y_inv of 1 plane 31.7 -> 21.4
+// and 33.6 -> 18.7).
+constexpr int THIN = 3;
 template <typename T>
 __host__ __device__ constexpr int col_batch(int n, int tile) {
-  int b = tile_scale(128, tile) / (int)sizeof(cpx<T>);
+  int b = tile == THIN ? 4 : tile_scale(128, tile) / (int)sizeof(cpx<T>);
   const int m = n / reg_elems<T>(n);
   while (b > 1 && b * m > 1024) b /= 2;
   while (b * m < 64) b *= 2;            // at least one wave

@@ -674,3 +674,27 @@ def test_batched_depth_pass_is_shared_with_long_grids_of_small_spectra():
         assert times["x_fwd"][1] == x_fwd
         for c in ctxs:
             c.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(16, 16, 5), (8, 64, 20), (64, 512, 12), (8, 1024, 6), (4, 2048, 3), (4, 4096, 2)])
+def test_column_tiles_of_few_planes(nx, ny, nz):
+    """A traction's 3 planes in, the surface displacement's 1 out (tiles of 4
+    planes where the default is wider): the oracle's values, and the bits of
+    the other tile choices."""
+    g = grid_dict(nx, ny, nz, 1.0, max(1.0, ny / 512), 0.25)
+    t = filtered_traction(g, seed=ny)
+    ref = ora.apply(g, E, NU, traction=t)["surf_u3"]
+    td = torch.from_numpy(t).cuda()
+    for prec, bound in (("fp64", TOL), ("fp32_refined", 2e-6)):
+        c = _ctx(g, precision=prec)
+        u = c.boussinesq_apply(td, want=("surf_u3",))["surf_u3"]
+        torch.cuda.synchronize()
+        err = _rel(u.cpu().numpy(), ref)
+        _say("few planes", (nx, ny, nz), prec, err)
+        assert err <= bound
+        for tile in (0, 2):
+            c.set_fft_config([(1, 4), (tile, 4), (tile, 4), (1, 4)])
+            v = c.boussinesq_apply(td, want=("surf_u3",))["surf_u3"]
+            torch.cuda.synchronize()
+            assert torch.equal(u, v), (prec, tile)
+        c.close()
