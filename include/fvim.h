@@ -461,8 +461,9 @@ int fvim_set_timing(fvim_ctx* ctx, int on);
 
 /*
  * Tuning options.  FVIM_OPT_DEPTH_CONFIG: id of the depth-pass thread layout
- * (lanes per mode x nodes per lane; -1 = built-in default for nz); ids that
- * do not serve nz are rejected with FVIM_EINVAL.  FVIM_OPT_TUNE = 1: the next
+ * (lanes per mode x nodes per lane; -1 = built-in default for nz, in float64 of
+ * 33 to 64 nodes another one for the displacements of a traction alone than the
+ * one reported); ids that do not serve nz are rejected with FVIM_EINVAL.  FVIM_OPT_TUNE = 1: the next
  * operator call times every valid layout on its own data (blocking) and
  * keeps the fastest.  Different layouts change only the summation order.
  * Callers that need run-to-run identical results store the chosen id and

@@ -147,7 +147,7 @@ int tune_depth(fvim_ctx* c, const cpx<T>* in, cpx<T>* out, const DepthParams& pr
   hipEvent_t a, b;
   if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) return fail(FVIM_EHIP, "events");
   float best = 1e30f;
-  int best_id = depth_default_config<T>(prm.nz);
+  int best_id = depth_default_config<T>(prm.nz, depth_light(prm));
   for (int id = 0; id < depth_num_configs(); ++id) {
     if (!depth_config_valid(id, prm.nz)) continue;
     hipError_t e = launch_depth<T>(in, out, prm, id, st);

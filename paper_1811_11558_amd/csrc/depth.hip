@@ -193,18 +193,22 @@ bool depth_config_valid(int id, int nz) {
 // constants in scalar registers, DPP scans): against 32 lanes x 2 nodes 8.8 / 15.7 us
 // at 16^2 x 64, 23.8 / 29.5 at 128^2 x 64, 76.8 / 99.0 at 256^2 x 64, 1231 / 1373 at
 // 1024^2 x 64, 17.1 / 19.6 at 64 x 128 x 33 and 62.9 / 61.6 at 256^2 x 33.  In float32
-// it is the slower one (57.6 / 45.7 us at 256^2 x 64).
+// it is the slower one (57.6 / 45.7 us at 256^2 x 64), and without eigenstrain where
+// no tensor field is asked for (light): a mode is then little more than its constants,
+// and a wave holds two modes in 32 x 2 (surface displacement of a traction 52.3 / 45.5 us at
+// 256^2 x 64, 187.2 / 155.6 at 512^2 x 40; strain 67.7 / 67.1 and 228.1 / 214.9, strain and
+// stress 102 / 215 and 321 / 370).
 template <typename T>
-int depth_default_config(int nz) {
+int depth_default_config(int nz, bool light) {
   if (nz <= 16) return 0;
   if (nz <= 32) return 1;
-  if (nz <= 64) return sizeof(T) == 8 ? 4 : 3;
+  if (nz <= 64) return sizeof(T) == 8 && !light ? 4 : 3;
   if (nz <= 128) return 5;
   if (nz <= 256) return 6;
   return 7;
 }
-template int depth_default_config<double>(int);
-template int depth_default_config<float>(int);
+template int depth_default_config<double>(int, bool);
+template int depth_default_config<float>(int, bool);
 
 template <typename T>
 hipError_t launch_mode_table(ModeConst<T>* tab, int nx, int ny, double lx, double ly, double h, hipStream_t st) {
@@ -226,7 +230,7 @@ void depth_derive(DepthParams& p) {
 
 template <typename T>
 void depth_blocks(const DepthParams& p, int* main, int* nyq) {
-  *main = main_blocks<T>(NT / kCfgs[depth_default_config<T>(p.nz)].lpm, p);
+  *main = main_blocks<T>(NT / kCfgs[depth_default_config<T>(p.nz, depth_light(p))].lpm, p);
   *nyq = mean_in_pass<T>() ? 0 : p.ny + p.kxh - 1;
 }
 
@@ -240,7 +244,7 @@ template <typename T>
 int depth_batch_config(const DepthBatch& b, int c0, int c1, bool* mixed) {
   int lo = kNCfg, hi = 0;
   for (int c = c0; c < c1; ++c) {
-    const int id = depth_default_config<T>(b.prm[c].nz);
+    const int id = depth_default_config<T>(b.prm[c].nz, depth_light(b.prm[c]));
     lo = std::min(lo, id);
     hi = std::max(hi, id);
   }
@@ -263,15 +267,18 @@ template <typename T>
 hipError_t launch_batch_group(const DepthBatch& host, const DepthBatch* dtab, int c0, int c1, bool disp, bool wx,
                               hipStream_t st) {
   const int b0 = host.first_main[c0], nb = host.first_main[c1] - b0;
-  constexpr int L64 = sizeof(T) == 8 ? 64 : 32;         // layout of 33 to 64 nodes
   bool mix = false;
   switch (depth_batch_config<T>(host, c0, c1, &mix)) {
     case 0: return launch_batch_cfg<T, 16, 1, false>(dtab, disp, wx, b0, nb, st);
     case 1: return mix ? launch_batch_cfg<T, 16, 2, true>(dtab, disp, wx, b0, nb, st)
                        : launch_batch_cfg<T, 16, 2, false>(dtab, disp, wx, b0, nb, st);
-    case 3:
-    case 4: return mix ? launch_batch_cfg<T, L64, 64 / L64, true>(dtab, disp, wx, b0, nb, st)
-                       : launch_batch_cfg<T, L64, 64 / L64, false>(dtab, disp, wx, b0, nb, st);
+    case 3: return mix ? launch_batch_cfg<T, 32, 2, true>(dtab, disp, wx, b0, nb, st)
+                       : launch_batch_cfg<T, 32, 2, false>(dtab, disp, wx, b0, nb, st);
+    case 4:
+      if constexpr (sizeof(T) == 8)
+        return mix ? launch_batch_cfg<T, 64, 1, true>(dtab, disp, wx, b0, nb, st)
+                   : launch_batch_cfg<T, 64, 1, false>(dtab, disp, wx, b0, nb, st);
+      break;
     case 5: return mix ? launch_batch_cfg<T, 64, 2, true>(dtab, disp, wx, b0, nb, st)
                        : launch_batch_cfg<T, 64, 2, false>(dtab, disp, wx, b0, nb, st);
     case 6: return launch_batch_cfg<T, 64, 4, false>(dtab, disp, wx, b0, nb, st);
@@ -315,7 +322,7 @@ hipError_t launch_depth(const cpx<T>* in, cpx<T>* out, const DepthParams& prm, i
   if (!prm.mtab) return hipErrorInvalidValue;
   DepthParams p = prm;
   depth_derive(p);
-  if (!depth_config_valid(cfg, p.nz)) cfg = depth_default_config<T>(p.nz);
+  if (!depth_config_valid(cfg, p.nz)) cfg = depth_default_config<T>(p.nz, depth_light(p));
   switch (cfg) {
     case 0: return launch_cfg<T, 16, 1>(in, out, p, st, part);
     case 1: return launch_cfg<T, 16, 2>(in, out, p, st, part);

@@ -238,7 +238,11 @@ hipError_t launch_depth(const cpx<T>* in, cpx<T>* out, const DepthParams& p, int
 int depth_num_configs();
 bool depth_config_valid(int id, int nz);
 template <typename T>
-int depth_default_config(int nz);
+int depth_default_config(int nz, bool light = false);
+// no eigenstrain and no tensor field asked for
+__host__ __device__ inline bool depth_light(const DepthParams& p) {
+  return !p.has_w && p.off_strain < 0 && p.off_stress < 0;
+}
 
 // Mean-mode (k = 0) fields in float64 from the block sums of the input
 // planes: out[plane] for every output plane (strain, stress, displacement,

@@ -698,3 +698,39 @@ def test_column_tiles_of_few_planes(nx, ny, nz):
             torch.cuda.synchronize()
             assert torch.equal(u, v), (prec, tile)
         c.close()
+
+
+def test_depth_layout_of_a_traction_alone():
+    """33 to 64 float64 nodes: 32 lanes x 2 nodes for the displacements of a
+    traction alone, 64 x 1 for tensor fields or with eigenstrain; in batches of
+    mixed depths the same."""
+    from paper_1811_11558_amd import operator_apply_batch
+    g = grid_dict(32, 32, 40, 1.0, 1.0, 0.25)
+    rng = np.random.default_rng(3)
+    t = torch.from_numpy(rng.standard_normal((3, 32, 32))).cuda()
+    e = torch.from_numpy(rng.standard_normal((6, 40, 32, 32))).cuda()
+    c = _ctx(g)
+    for want, eps, cfg in ((("surf_u3",), None, 3), (("disp",), None, 3), (("strain", "disp"), None, 4),
+                           (("disp",), e, 4)):
+        c.set_option(c.OPT_DEPTH_CONFIG, -1)
+        a = c.operator_apply(eps, t, want=want)
+        c.set_option(c.OPT_DEPTH_CONFIG, cfg)
+        b = c.operator_apply(eps, t, want=want)
+        torch.cuda.synchronize()
+        for k in want:
+            _say("layout", want, eps is not None, k)
+            assert torch.equal(a[k], b[k]), (want, cfg, k)
+    c.close()
+    for shapes in ([(16, 16, 8), (32, 16, 20), (16, 16, 40)], [(16, 16, 64), (16, 8, 40)],
+                   [(16, 16, 8), (32, 16, 20), (16, 16, 40), (16, 16, 64), (16, 8, 100), (8, 8, 130)]):
+        for prec in ("fp64", "fp32_refined"):
+            ctxs = [_ctx(grid_dict(*s, 1.0, 1.0, 0.25), precision=prec) for s in shapes]
+            ts = [torch.from_numpy(rng.standard_normal((3, s[1], s[0]))).cuda() for s in shapes]
+            for want in (("surf_u3",), ("disp", "surf_u3"), ("strain",)):
+                got = operator_apply_batch(ctxs, None, ts, want=want)
+                for x, q, o in zip(ctxs, ts, got):
+                    own = x.boussinesq_apply(q, want=want)
+                    torch.cuda.synchronize()
+                    assert all(torch.equal(own[k], o[k]) for k in want), (prec, want, x.nz)
+            for x in ctxs:
+                x.close()
