@@ -187,17 +187,19 @@ bool depth_config_valid(int id, int nz) {
   return nz <= cap && 4 * nz > cap;
 }
 
-// Default without tuning, alone and in a batch: two nodes per
-// lane from 17 on, more than 128 nodes four or eight, but for 32 < nz <= 64 in
-// float64 one node per lane of a wave (reads whole lines, mode
-// constants in scalar registers, DPP scans): against 32 lanes x 2 nodes 8.8 / 15.7 us
-// at 16^2 x 64, 23.8 / 29.5 at 128^2 x 64, 76.8 / 99.0 at 256^2 x 64, 1231 / 1373 at
-// 1024^2 x 64, 17.1 / 19.6 at 64 x 128 x 33 and 62.9 / 61.6 at 256^2 x 33.  In float32
-// it is the slower one (57.6 / 45.7 us at 256^2 x 64), and without eigenstrain where
-// no tensor field is asked for (light): a mode is then little more than its constants,
-// and a wave holds two modes in 32 x 2 (surface displacement of a traction 52.3 / 45.5 us at
-// 256^2 x 64, 187.2 / 155.6 at 512^2 x 40; strain 67.7 / 67.1 and 228.1 / 214.9, strain and
-// stress 102 / 215 and 321 / 370).
+// Default without tuning, alone and in a batch: two nodes per lane from 17 on, more
+// than 128 nodes four or eight, but for 32 < nz <= 64 in float64 one node per lane of
+// a wave (reads whole lines, mode constants in scalar registers, DPP scans).  us, 64 x 1
+// against 32 x 2, fused strain: 8.8 / 15.7 at 16^2 x 64, 23.8 / 29.5 at 128^2 x 64,
+// 76.8 / 99.0 at 256^2 x 64, 1231 / 1373 at 1024^2 x 64, 17.1 / 19.6 at 64 x 128 x 33,
+// 62.9 / 61.6 at 256^2 x 33; every output 102 / 215 at 256^2 x 64.  Two modes per wave
+// are faster where little is moved per mode (light) over more modes than waves fit
+// the chip at once: surface displacement of a traction 52.3 / 45.5 at 256^2 x 64 (19.6
+// against 18.8 the other way at 128 x 32 x 64), with eigenstrain 54.0 / 48.9 at 256^2 x 40
+// but 55.1 / 55.7 at 256^2 x 64; on graded nodes, where the 64 x 1 scans take LDS
+// shuffles too, strain 98.5 / 85.6 at 256^2 x 40 and 103.7 / 109.6 at 256^2 x 64, of a
+// traction alone 95.6 / 83.7.  In float32 64 x 1 is the slower one (57.6 / 45.7 us at
+// 256^2 x 64).
 template <typename T>
 int depth_default_config(int nz, bool light) {
   if (nz <= 16) return 0;
@@ -268,17 +270,21 @@ hipError_t launch_batch_group(const DepthBatch& host, const DepthBatch* dtab, in
                               hipStream_t st) {
   const int b0 = host.first_main[c0], nb = host.first_main[c1] - b0;
   bool mix = false;
-  switch (depth_batch_config<T>(host, c0, c1, &mix)) {
+  const int cfg = depth_batch_config<T>(host, c0, c1, &mix);
+  switch (cfg) {
     case 0: return launch_batch_cfg<T, 16, 1, false>(dtab, disp, wx, b0, nb, st);
     case 1: return mix ? launch_batch_cfg<T, 16, 2, true>(dtab, disp, wx, b0, nb, st)
                        : launch_batch_cfg<T, 16, 2, false>(dtab, disp, wx, b0, nb, st);
-    case 3: return mix ? launch_batch_cfg<T, 32, 2, true>(dtab, disp, wx, b0, nb, st)
-                       : launch_batch_cfg<T, 32, 2, false>(dtab, disp, wx, b0, nb, st);
+    case 3:
     case 4:
-      if constexpr (sizeof(T) == 8)
-        return mix ? launch_batch_cfg<T, 64, 1, true>(dtab, disp, wx, b0, nb, st)
-                   : launch_batch_cfg<T, 64, 1, false>(dtab, disp, wx, b0, nb, st);
-      break;
+      if constexpr (sizeof(T) == 8) {                   // (a mixed launch holds both)
+        if (mix) return launch_batch_cfg<T, 64, 1, true>(dtab, disp, wx, b0, nb, st);
+        return cfg == 4 ? launch_batch_cfg<T, 64, 1, false>(dtab, disp, wx, b0, nb, st)
+                        : launch_batch_cfg<T, 32, 2, false>(dtab, disp, wx, b0, nb, st);
+      } else {
+        return mix ? launch_batch_cfg<T, 32, 2, true>(dtab, disp, wx, b0, nb, st)
+                   : launch_batch_cfg<T, 32, 2, false>(dtab, disp, wx, b0, nb, st);
+      }
     case 5: return mix ? launch_batch_cfg<T, 64, 2, true>(dtab, disp, wx, b0, nb, st)
                        : launch_batch_cfg<T, 64, 2, false>(dtab, disp, wx, b0, nb, st);
     case 6: return launch_batch_cfg<T, 64, 4, false>(dtab, disp, wx, b0, nb, st);

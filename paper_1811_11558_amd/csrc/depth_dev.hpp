@@ -754,21 +754,16 @@ __device__ __forceinline__ void depth_batch_block(const DepthBatch* __restrict__
   const DepthParams& prm = b->prm[c];
   blk -= b->first_main[c];
   if constexpr (MIX) {
-    constexpr int CAP = LPM * P;
+    constexpr int CAP = LPM * P, L64 = sizeof(T) == 8 ? 64 : 32;
     static_assert(CAP <= DEPTH_MIX_NZ, "layouts of a mixed launch");
     if constexpr (CAP > 16)
       if (prm.nz <= 16) return depth_modes<T, 16, 1, DISP, WANTX, false>(in, out, prm, blk);
     if constexpr (CAP > 32)
       if (prm.nz <= 32) return depth_modes<T, 16, 2, DISP, WANTX, false>(in, out, prm, blk);
-    if constexpr (CAP > 64) {
-      if (prm.nz <= 64) {
-        if constexpr (sizeof(T) == 8 && !(DISP && !WANTX))
-          return depth_modes<T, 64, 1, DISP, WANTX, false>(in, out, prm, blk);
-        if constexpr (sizeof(T) == 8)
-          if (!depth_light(prm)) return depth_modes<T, 64, 1, DISP, WANTX, false>(in, out, prm, blk);
-        return depth_modes<T, 32, 2, DISP, WANTX, false>(in, out, prm, blk);
-      }
-    }
+    if constexpr (CAP > 32 && sizeof(T) == 8 && DISP && !WANTX)
+      if (prm.nz <= 64 && depth_light(prm)) return depth_modes<T, 32, 2, DISP, WANTX, false>(in, out, prm, blk);
+    if constexpr (CAP > 64)
+      if (prm.nz <= 64) return depth_modes<T, L64, 64 / L64, DISP, WANTX, false>(in, out, prm, blk);
   }
   depth_modes<T, LPM, P, DISP, WANTX, false>(in, out, prm, blk);
 }

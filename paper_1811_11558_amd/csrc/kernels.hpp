@@ -239,9 +239,12 @@ int depth_num_configs();
 bool depth_config_valid(int id, int nz);
 template <typename T>
 int depth_default_config(int nz, bool light = false);
-// no eigenstrain and no tensor field asked for
+// An application that moves little per mode, over more modes than the chip holds
+// waves at once (3 per SIMD, 1024 SIMDs): see depth_default_config.
 __host__ __device__ inline bool depth_light(const DepthParams& p) {
-  return !p.has_w && p.off_strain < 0 && p.off_stress < 0;
+  const bool tensor = p.off_strain >= 0 || p.off_stress >= 0, shallow = !p.has_w || p.nz <= 48;
+  const bool light = p.hz ? p.off_stress < 0 && (shallow || !tensor) : shallow && !tensor;
+  return light && p.kxh * p.ny > 3072;
 }
 
 // Mean-mode (k = 0) fields in float64 from the block sums of the input

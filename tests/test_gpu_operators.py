@@ -700,29 +700,44 @@ def test_column_tiles_of_few_planes(nx, ny, nz):
         c.close()
 
 
-def test_depth_layout_of_a_traction_alone():
-    """33 to 64 float64 nodes: 32 lanes x 2 nodes for the displacements of a
-    traction alone, 64 x 1 for tensor fields or with eigenstrain; in batches of
-    mixed depths the same."""
-    from paper_1811_11558_amd import operator_apply_batch
-    g = grid_dict(32, 32, 40, 1.0, 1.0, 0.25)
-    rng = np.random.default_rng(3)
-    t = torch.from_numpy(rng.standard_normal((3, 32, 32))).cuda()
-    e = torch.from_numpy(rng.standard_normal((6, 40, 32, 32))).cuda()
-    c = _ctx(g)
-    for want, eps, cfg in ((("surf_u3",), None, 3), (("disp",), None, 3), (("strain", "disp"), None, 4),
-                           (("disp",), e, 4)):
-        c.set_option(c.OPT_DEPTH_CONFIG, -1)
-        a = c.operator_apply(eps, t, want=want)
-        c.set_option(c.OPT_DEPTH_CONFIG, cfg)
-        b = c.operator_apply(eps, t, want=want)
-        torch.cuda.synchronize()
-        for k in want:
-            _say("layout", want, eps is not None, k)
-            assert torch.equal(a[k], b[k]), (want, cfg, k)
+@pytest.mark.parametrize("nx,ny,nz,graded,eigenstrain,want,cfg", [
+    (128, 64, 40, False, False, ("disp",), 3), (128, 64, 64, False, False, ("disp",), 3),
+    (128, 64, 40, False, False, ("strain", "disp"), 4), (128, 64, 48, False, True, ("surf_u3",), 3),
+    (128, 64, 49, False, True, ("disp",), 4), (128, 64, 40, False, True, ("strain",), 4),
+    (64, 64, 40, False, False, ("disp",), 4),                         # 2112 modes
+    (128, 64, 48, True, True, ("strain",), 3), (128, 64, 49, True, True, ("strain",), 4),
+    (128, 64, 64, True, True, ("surf_u3",), 3), (128, 64, 64, True, False, ("strain",), 3),
+    (128, 64, 40, True, True, ("stress",), 4)])
+def test_default_depth_layout_of_33_to_64_nodes(nx, ny, nz, graded, eigenstrain, want, cfg):
+    """Float64: 64 lanes x 1 node, 32 x 2 where an application moves little per
+    mode over many modes, each side of every bound."""
+    c = _ctx(grid_dict(nx, ny, nz, 1.0, 1.0, 0.25))
+    if graded:
+        z = 0.25 * (np.arange(nz) / (nz - 1)) ** 1.5
+        z[-1] = 0.25
+        c.set_depth_nodes(z)
+    rng = np.random.default_rng(nz)
+    t = torch.from_numpy(rng.standard_normal((3, ny, nx))).cuda()
+    e = torch.from_numpy(rng.standard_normal((6, nz, ny, nx))).cuda() if eigenstrain else None
+    a = c.operator_apply(e, t, want=want)
+    got = {}
+    for k in (3, 4):
+        c.set_option(c.OPT_DEPTH_CONFIG, k)
+        got[k] = c.operator_apply(e, t, want=want)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a[k], got[cfg][k]) for k in want)
+    assert not all(torch.equal(got[3][k], got[4][k]) for k in want)   # (the layouts' last bits tell them apart)
     c.close()
+
+
+def test_batched_traction_alone_has_the_bits_of_its_own_application():
+    """Without eigenstrain, mixed depths and both layouts of 33 to 64 nodes in a
+    batch: bitwise the separate application."""
+    from paper_1811_11558_amd import operator_apply_batch
+    rng = np.random.default_rng(3)
     for shapes in ([(16, 16, 8), (32, 16, 20), (16, 16, 40)], [(16, 16, 64), (16, 8, 40)],
-                   [(16, 16, 8), (32, 16, 20), (16, 16, 40), (16, 16, 64), (16, 8, 100), (8, 8, 130)]):
+                   [(128, 64, 40), (16, 16, 64), (16, 16, 8)], [(128, 64, 40), (64, 128, 64)],
+                   [(16, 16, 8), (32, 16, 20), (128, 64, 40), (16, 16, 64), (16, 8, 100), (8, 8, 130)]):
         for prec in ("fp64", "fp32_refined"):
             ctxs = [_ctx(grid_dict(*s, 1.0, 1.0, 0.25), precision=prec) for s in shapes]
             ts = [torch.from_numpy(rng.standard_normal((3, s[1], s[0]))).cuda() for s in shapes]
