@@ -37,18 +37,21 @@ __host__ __device__ constexpr int tile_scale(int base, int tile) {
 // Elements of a transform per thread.  16: 64 registers of float64 values.  8 up
 // to length 128: short grids are bound by the chain of one thread's loads, passes
 // and stores (64 x 64 x 16 float64 27.6 -> 25.4 us, 32 x 32 x 16 21.6 -> 19.8 us; at
-// 256 no gain).  In the columns 32 in float32 from length 1024 on (512 threads per
+// 256 no gain).  In rows of 16 4: with 8 two threads share a row and a load touches
+// 16 bytes of every line (x_fwd / x_inv 48.6 / 29.6 -> 33.1 / 23.5 us at 16 x 2048 x 40).
+// In the columns 32 in float32 from length 1024 on (512 threads per
 // tile instead of 1024: y_fwd 833 -> 787 us at 1024^2 x 64), but not below (at 256 and
 // 512 the passes take 150 to 170 registers, two waves per SIMD: y_inv 541 against
 // 460 us at 512^2 x 128), and not in the rows (the packing has as many values again:
 // 165 to 212 registers).
 __host__ __device__ constexpr int row_elems(int n) {
-  const int v = n <= 128 ? 8 : 16;
+  const int v = n <= 16 ? 4 : (n <= 128 ? 8 : 16);
   return n < v ? n : v;
 }
 template <typename T>
 __host__ __device__ constexpr int reg_elems(int n) {
-  return sizeof(T) == 4 && n >= 1024 ? 32 : row_elems(n);
+  const int v = sizeof(T) == 4 && n >= 1024 ? 32 : (n <= 128 ? 8 : 16);
+  return n < v ? n : v;
 }
 
 // Columns (planes) per block of the column (y) kernels.  The mode-major side
