@@ -243,7 +243,7 @@ struct OpPlan {
   DepthParams prm{};
   OutSegments seg{};
   InSegments iseg{};
-  int np = 0, np_in = 0, wbpp = 0, wbmax = 0;
+  int np = 0, np_in = 0, nsum = 0;
   bool k0x = false;
   bool nt = false;              // launches read their input with streaming loads
   ResidEpilogue ep{};           // residual epilogue of the inverse x transform
@@ -332,11 +332,9 @@ int op_layout(fvim_ctx* c, const double* eps_p, const double* traction, double* 
   const size_t nrep = (size_t)depth_replicas(ny, kxh);
   sz.spec = (planes * nmodes + nrep * (size_t)prm.ld_out) * sizeof(cpx<T>);
   for (int k = 0; k < 4; ++k) P.ch[k] = c->fft[prec_index<T>()][k];
-  P.wbpp = x_r2c_blocks_per_plane<T>(nx, ny, P.ch[0]);
-  // block sums of every input plane for the most blocks any tile choice
-  // gives (the tuner runs them all), then the mean-mode constants
-  P.wbmax = x_r2c_max_blocks_per_plane<T>(nx, ny);
-  sz.k0 = P.k0x ? sizeof(double) * ((size_t)(6 * nz + 3) * P.wbmax + (size_t)np) : 0;
+  // partial sums of every input plane, then the mean-mode constants
+  P.nsum = x_r2c_sums_per_plane(nx, ny);
+  sz.k0 = P.k0x ? sizeof(double) * ((size_t)(6 * nz + 3) * P.nsum + (size_t)np) : 0;
   sz.mt = sizeof(ModeConst<T>) * nmodes;
   // Streaming loads pay off when one launch's output fits the 256 MiB
   // last-level cache, so the next launch can read it from there. Measured
@@ -356,9 +354,9 @@ int op_layout(fvim_ctx* c, const double* eps_p, const double* traction, double* 
 template <typename T>
 void op_bind(fvim_ctx* c, OpPlan<T>& P, void* bufA, void* bufB, double* k0buf, const void* mt, bool side) {
   if (P.k0x) {
-    P.wsum = k0buf;                                // block sums of every input plane
-    P.tsum = P.wsum + (size_t)P.prm.off_t * P.wbpp;
-    P.padd = P.wsum + (size_t)(6 * c->grid.nz + 3) * P.wbmax;
+    P.wsum = k0buf;                                // partial sums of every input plane
+    P.tsum = P.wsum + (size_t)P.prm.off_t * P.nsum;
+    P.padd = P.wsum + (size_t)(6 * c->grid.nz + 3) * P.nsum;
   }
   P.prm.mtab = mt;
   P.prm.hz = c->hz;
@@ -397,14 +395,6 @@ int op_plan(fvim_ctx* c, const double* eps_p, const double* traction, double* st
   return FVIM_OK;
 }
 
-// Block count of the forward row transform after a change of its choice:
-// the float64 plane sums of the float32 path follow it.
-template <typename T>
-void op_refresh_sums(fvim_ctx* c, OpPlan<T>& P) {
-  P.wbpp = x_r2c_blocks_per_plane<T>(c->grid.nx, c->grid.ny, P.ch[0]);
-  if (P.k0x) P.tsum = P.wsum + (size_t)P.prm.off_t * P.wbpp;
-}
-
 static int ilog2i(int n) { return 31 - __builtin_clz((unsigned)n); }
 
 // Launches of the transform stages: real fields -> A -> mode-major B; mode-major
@@ -437,12 +427,11 @@ int tune_operator(fvim_ctx* c, OpPlan<T>& P) {
   hipError_t e;
   int rc = time_choices(c, lx, [&](FftChoice ch) { return run_x_fwd<T>(c, P, st, ch); }, &P.ch[0]);
   if (rc) return rc;
-  op_refresh_sums<T>(c, P);
   if ((e = run_x_fwd<T>(c, P, st, P.ch[0])) != hipSuccess) return fail_hip(e, "x_r2c");
   if ((rc = time_choices(c, ly, [&](FftChoice ch) { return run_y_fwd<T>(c, P, st, ch); }, &P.ch[1]))) return rc;
   if ((e = run_y_fwd<T>(c, P, st, P.ch[1])) != hipSuccess) return fail_hip(e, "y_fwd");
   if ((rc = tune_depth<T>(c, P.B, P.A, P.prm))) return rc;
-  if (P.k0x && (e = launch_k0_fields(P.wsum, P.wbpp, P.tsum, P.wbpp, P.padd, P.prm, st)) != hipSuccess)
+  if (P.k0x && (e = launch_k0_fields(P.wsum, P.tsum, P.nsum, P.padd, P.prm, st)) != hipSuccess)
     return fail_hip(e, "k0");
   if ((rc = time_choices(c, ly, [&](FftChoice ch) { return run_y_inv<T>(c, P, st, ch); }, &P.ch[2]))) return rc;
   if ((e = run_y_inv<T>(c, P, st, P.ch[2])) != hipSuccess) return fail_hip(e, "y_inv");
@@ -462,12 +451,10 @@ int op_forward(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, StageTimer& tm) {
   return FVIM_OK;
 }
 
-// Mean mode (float32 path) and inverse transforms: mode-major A -> outputs.
+// Inverse transforms: mode-major A -> outputs.
 template <typename T>
 int op_inverse(fvim_ctx* c, OpPlan<T>& P, hipStream_t st, StageTimer& tm) {
   hipError_t e;
-  if (P.k0x && (e = launch_k0_fields(P.wsum, P.wbpp, P.tsum, P.wbpp, P.padd, P.prm, st)) != hipSuccess)
-    return fail_hip(e, "k0");
   tm.begin(FVIM_STAGE_YINV, st);
   if ((e = run_y_inv<T>(c, P, st, P.ch[2])) != hipSuccess) return fail_hip(e, "y_inv");
   tm.end();
@@ -495,6 +482,8 @@ int op_run(fvim_ctx* c, OpPlan<T>& P, int cfg, hipStream_t st, hipStream_t ss, S
     tm.end();
   }
   if (ss != st && (e = join(c->ev_nyq, ss, st)) != hipSuccess) return fail_hip(e, "join");
+  if (P.k0x && (e = launch_k0_fields(P.wsum, P.tsum, P.nsum, P.padd, P.prm, st)) != hipSuccess)
+    return fail_hip(e, "k0");
   return op_inverse<T>(c, P, st, tm);
 }
 
@@ -568,7 +557,6 @@ int operator_apply_t(fvim_ctx* c, const double* eps_p, const double* traction, d
     for (int k = 0; k < 4; ++k) P.ch[k] = c->fft[prec_index<T>()][k] = rec.ch[k];
     c->depth_cfg = rec.depth_cfg;
     c->tune_pending = 0;
-    op_refresh_sums<T>(c, P);
   }
   return op_run<T>(c, P, c->depth_cfg, st, ss, tm);
 }
@@ -613,8 +601,6 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     if (ilog2i(cs[i]->grid.nx) <= XFORM_BATCH_MAX_LOGN && ilog2i(cs[i]->grid.ny) <= XFORM_BATCH_MAX_LOGN) {
       bat.push_back(i);
       for (int k = 0; k < 4; ++k) P[i].ch[k] = FftChoice{};
-      P[i].wbpp = x_r2c_batch_blocks_per_plane<T>(cs[i]->grid.nx, cs[i]->grid.ny);
-      if (P[i].k0x) P[i].tsum = P[i].wsum + (size_t)P[i].prm.off_t * P[i].wbpp;
     }
   }
   if (rc) return restore(rc);
@@ -731,14 +717,20 @@ int operator_apply_batch_t(fvim_ctx* const* cs, int n, const double* const* eps,
     hipError_t e = launch_depth_batch<T>(b, (DepthBatch*)c0->dbatch, st);
     tm.end();
     if (e != hipSuccess) return restore(fail_hip(e, "batched depth pass"));
+    if (sizeof(T) == 4) {                            // mean mode
+      K0Batch k{};
+      for (int j = 0; j < b.n; ++j) {
+        const OpPlan<T>& p = P[ord[i0 + j]];
+        k.wsum[j] = p.wsum;
+        k.tsum[j] = p.tsum;
+        k.nsum[j] = p.nsum;
+        k.out[j] = p.padd;
+      }
+      if ((e = launch_k0_batch(b, (const DepthBatch*)c0->dbatch, k, st)) != hipSuccess) return restore(fail_hip(e, "k0"));
+    }
   }
   for (int i : ord)
     if (!shared[i] && (rc = op_inverse<T>(cs[i], P[i], st, tm))) return restore(rc);
-  for (int i : bat) {
-    if (!P[i].k0x) continue;
-    hipError_t e = launch_k0_fields(P[i].wsum, P[i].wbpp, P[i].tsum, P[i].wbpp, P[i].padd, P[i].prm, st);
-    if (e != hipSuccess) return restore(fail_hip(e, "k0"));
-  }
   if ((rc = xform(2, FVIM_STAGE_YINV)) || (rc = xform(3, FVIM_STAGE_XINV))) return restore(rc);
   return restore(FVIM_OK);
 }

@@ -35,8 +35,7 @@ __global__ __launch_bounds__((row_threads<T>(1 << LOGN, TILE)))
 void k_x_r2c(InSegments seg, cpx<T>* __restrict__ out, int ny, int R, const cpx<T>* __restrict__ tw,
              double* __restrict__ bsum, LayerSkip skip) {
   __shared__ __align__(16) char tile[row_lds_bytes<T>(1 << LOGN, TILE)];
-  __shared__ double red[row_threads<T>(1 << LOGN, TILE) / 64];
-  x_r2c_body<T, LOGN, NTL, TILE, RADIX>(tile, red, blockIdx.x, seg, out, ny, R, tw, bsum, skip);
+  x_r2c_body<T, LOGN, NTL, TILE, RADIX>(tile, blockIdx.x, seg, out, ny, R, tw, bsum, skip);
 }
 
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
@@ -68,8 +67,7 @@ void k_x_c2r(const cpx<T>* __restrict__ in, OutSegments seg, int ny, int R, doub
 
 template <typename T>
 __global__ __launch_bounds__(NT) void k_x_r2c_batch(XformBatch b) {
-  __shared__ double red[NT / 64];
-  x_r2c_batch_block<T>(b, (int)blockIdx.x, red);
+  x_r2c_batch_block<T>(b, (int)blockIdx.x);
 }
 
 template <typename T>
@@ -126,13 +124,13 @@ hipError_t with_choice(FftChoice ch, F& f) {
     if (ch.tile == 2) return f.template go<L, 2, 4>();
   }
   return f.template go<L, 1, 4>();
+}
+
 // Planes of at most SEQ rows fill half a default row block or less: the half-sized
 // block then, which still holds the whole plane (the same sums, bit for bit; float32
 // x_fwd / x_inv 14.6 / 13.2 -> 11.3 / 11.0 us at 512 x 4 x 100).
 template <typename T>
 constexpr bool row_halves(int n, int tile) { return tile == 1 && row_seq<T>(n, 0) < row_seq<T>(n, 1); }
-
-}
 
 template <typename T>
 struct R2CLaunch {
@@ -145,10 +143,10 @@ struct R2CLaunch {
   double* bsum;
   bool stream_in;
   const LayerSkip& skip;
-    if constexpr (row_halves<T>(1 << L, TILE))
-      if (ny <= row_seq<T>(1 << L, TILE)) return go<L, 0, RADIX>();
   template <int L, int TILE, int RADIX>
   hipError_t go() {
+    if constexpr (row_halves<T>(1 << L, TILE))
+      if (ny <= row_seq<T>(1 << L, TILE)) return go<L, 0, RADIX>();
     const int R = rows_per_block(row_seq<T>(1 << L, TILE), ny);
     const dim3 grid((unsigned)(nplanes * (size_t)ny / R)), blk(row_threads<T>(1 << L, TILE));
     if (stream_in)
@@ -202,10 +200,10 @@ struct C2RLaunch {
   const double* padd;
   const ResidEpilogue& ep;
   bool stream_out;
-    if constexpr (row_halves<T>(1 << L, TILE))
-      if (ny <= row_seq<T>(1 << L, TILE)) return go<L, 0, RADIX>();
   template <int L, int TILE, int RADIX>
   hipError_t go() {
+    if constexpr (row_halves<T>(1 << L, TILE))
+      if (ny <= row_seq<T>(1 << L, TILE)) return go<L, 0, RADIX>();
     const int R = rows_per_block(row_seq<T>(1 << L, TILE), ny);
     const dim3 grid((unsigned)(nplanes * (size_t)ny / R)), blk(row_threads<T>(1 << L, TILE));
     hipLaunchKernelGGL((k_x_c2r<T, L, TILE, RADIX>), grid, blk, 0, st, in, seg, ny, R, scale, tw, padd, ep,
@@ -221,17 +219,7 @@ FftChoice fft_effective(int logn, FftChoice ch) {
   return ch;
 }
 
-template <typename T>
-int x_r2c_blocks_per_plane(int nx, int ny, FftChoice ch) {
-  return ny / rows_per_block(row_seq<T>(nx, fft_effective(ilog2(nx), ch).tile), ny);
-}
-
-template <typename T>
-int x_r2c_max_blocks_per_plane(int nx, int ny) {
-  int m = 0;
-  for (int t = 0; t < 3; ++t) m = std::max(m, x_r2c_blocks_per_plane<T>(nx, ny, FftChoice{t, 4}));
-  return m;
-}
+int x_r2c_sums_per_plane(int nx, int ny) { return row_sums(nx, ny); }
 
 template <typename T>
 hipError_t launch_x_r2c(const InSegments& seg, cpx<T>* out, int nx, int ny, size_t nplanes, const cpx<T>* tw,
@@ -370,16 +358,7 @@ hipError_t launch_xform_batch(int kind, XformBatch& b, hipStream_t st) {
   return hipGetLastError();
 }
 
-// blocks per plane of the batched x_r2c (the float32 mean-mode sums)
-template <typename T>
-int x_r2c_batch_blocks_per_plane(int nx, int ny) {
-  return ny / rows_per_block(row_seq<T>(nx, 3), ny);
-}
-
 #define FVIM_INST(T)                                                                                            \
-  template int x_r2c_blocks_per_plane<T>(int, int, FftChoice);                                                  \
-  template int x_r2c_max_blocks_per_plane<T>(int, int);                                                         \
-  template int x_r2c_batch_blocks_per_plane<T>(int, int);                                                       \
   template hipError_t launch_x_r2c<T>(const InSegments&, cpx<T>*, int, int, size_t, const cpx<T>*, hipStream_t, \
                                       double*, bool, const LayerSkip&, FftChoice);                              \
   template hipError_t launch_y_fwd<T>(const cpx<T>*, cpx<T>*, int, int, int, int, const cpx<T>*, hipStream_t,   \

@@ -126,6 +126,12 @@ template <typename T>
 __host__ __device__ constexpr int row_lds_bytes(int n, int tile) {
   return row_seq<T>(n, tile) * row_ld<T>(n, tile) * (int)(row_split<T>(n, tile) ? sizeof(T) : sizeof(cpx<T>));
 }
+// Partial sums of a plane of nx x ny reals: one for each wave that holds its row
+// pairs, two rows per nx / row_elems(nx) threads, whatever the block's size.
+__host__ __device__ constexpr int row_sums(int nx, int ny) {
+  const int w = (ny / 2) * (nx / row_elems(nx)) / 64;
+  return w > 1 ? w : 1;
+}
 __host__ __device__ constexpr int ilog2c(int n) { return n <= 1 ? 0 : 1 + ilog2c(n / 2); }
 
 // Radix-R butterfly (R = 2, 4, 8) of the DFT with kernel exp(-2 pi i / R)
@@ -335,17 +341,18 @@ __device__ __forceinline__ void reg_fft(cpx<T> (&v)[V], int t0, L0 lds0, int t1,
 
 // ------------------------------------------------------------------ bodies
 // Each transform is a device body over one block's tile (logical block lb of
-// one grid) using the LDS tile (and red, a double per wave), shared by the
+// one grid) using the LDS tile (and, x_c2r, red, a double per wave), shared by the
 // single-grid kernels and by the kernels that serve several grids in one
 // launch.
 
 // Rows of nx = 2^LOGN reals -> half spectra.  Block = R consecutive rows of
 // one plane (R even, R | ny), two rows per complex sequence.  Output
 // X[(plane * kxh + k) * ny + y].
-// If bsum is not NULL, block lb also writes the float64 sum of its R rows to
-// bsum[lb] (the plane means of the mean mode are then formed in float64).
+// If bsum is not NULL, every wave also writes the float64 sum of its rows there
+// (the plane means of the mean mode are then formed in float64): the waves of a
+// plane hold the same rows with every tile, so that the sums do not depend on it.
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
-__device__ __forceinline__ void x_r2c_body(char* tile, double* red, int lb, const InSegments& seg,
+__device__ __forceinline__ void x_r2c_body(char* tile, int lb, const InSegments& seg,
                                            cpx<T>* __restrict__ out, int ny, int R,
                                            const cpx<T>* __restrict__ tw, double* __restrict__ bsum,
                                            const LayerSkip& skip) {
@@ -357,16 +364,20 @@ __device__ __forceinline__ void x_r2c_body(char* tile, double* red, int lb, cons
   const size_t row0 = (size_t)lb * R;
   const size_t plane = row0 / ny;
   const int y0 = (int)(row0 - plane * ny);
+  const int s = (int)threadIdx.x / M, t = (int)threadIdx.x % M, hp = R / 2;
+  auto put_sum = [&](double v) {         // of the wave (one that holds rows)
+    if ((threadIdx.x & 63) == 0 && s < hp)
+      bsum[plane * row_sums(N, ny) + ((size_t)(y0 / 2) * M + threadIdx.x) / 64] = v;
+  };
   // a layer without plastic strain: its rows sum to zero, nothing to transform
   if (skip.zact && (int)plane < skip.nw && (int)(plane % skip.nz) >= *skip.zact) {
-    if (bsum && threadIdx.x == 0) bsum[lb] = 0.0;
+    if (bsum) put_sum(0.0);
     return;
   }
   const int sg = (seg.n > 1 && (int)plane >= seg.first[1]) ? 1 : 0;
   const double* in = seg.ptr[sg] + ((plane - seg.first[sg]) * ny + y0) * (size_t)N;
   // threads of a row pair in x order; those past the last pair repeat it (never
   // stored), so every load is unconditional
-  const int s = (int)threadIdx.x / M, t = (int)threadIdx.x % M, hp = R / 2;
   const double* r0 = in + (size_t)(2 * min(s, hp - 1)) * N + t;
   double a[V], b[V];
 #pragma unroll
@@ -381,8 +392,10 @@ __device__ __forceinline__ void x_r2c_body(char* tile, double* red, int lb, cons
     double acc = 0.0;
 #pragma unroll
     for (int e = 0; e < V; ++e) acc += a[e] + b[e];
-    acc = block_sum<NTH>(s < hp ? acc : 0.0, red);
-    if (threadIdx.x == 0) bsum[lb] = acc;
+    if (s >= hp) acc = 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+    put_sum(acc);
   }
   E* lds = reinterpret_cast<E*>(tile);
   auto at = [lds](int q, int pos) { return lds + q * ld + pos + (pos >> 4); };
@@ -717,14 +730,14 @@ __device__ __forceinline__ ColTile col_tile(int blk, int kxh, int NP) {
 // One block of each batched transform (block blk of the launch over the
 // table b); the kernels below and the persistent batched operator run them.
 template <typename T>
-__device__ __forceinline__ void x_r2c_batch_block(const XformBatch& b, int blk, double* red) {
+__device__ __forceinline__ void x_r2c_batch_block(const XformBatch& b, int blk) {
   const int c = batch_grid(b, blk);
   const int lb = blk - b.first[c];
   char* tile = reinterpret_cast<char*>(fvim_dyn_lds);
   cpx<T>* out = static_cast<cpx<T>*>(b.out[c]);
   const cpx<T>* tw = static_cast<const cpx<T>*>(b.tw[c]);
 #define CALL(L) \
-  x_r2c_body<T, L, false, 3, 4>(tile, red, lb, b.iseg[c], out, b.ny[c], b.R[c], tw, b.bsum[c], LayerSkip{})
+  x_r2c_body<T, L, false, 3, 4>(tile, lb, b.iseg[c], out, b.ny[c], b.R[c], tw, b.bsum[c], LayerSkip{})
   FVIM_BATCH_LOGN_SWITCH(b.logn[c], CALL)
 #undef CALL
 }

@@ -39,19 +39,16 @@ struct FftChoice {
 constexpr int FFT_TUNE_MIN_LOGN = 5, FFT_TUNE_MAX_LOGN = 10;
 FftChoice fft_effective(int logn, FftChoice ch);
 
-// bsum (optional): float64 sum of the rows of each block, blocks of a plane
-// consecutive (x_r2c_blocks_per_plane of them).  stream_in: the launch reads
+// bsum (optional): float64 sums of the input's planes in parts,
+// x_r2c_sums_per_plane consecutive ones for each plane, the same for every launch
+// choice.  stream_in: the launch reads
 // its input for the last time with streaming (non-temporal) loads (see
 // operator_streaming); every launcher below takes the same flag.
 template <typename T>
 hipError_t launch_x_r2c(const InSegments& seg, cpx<T>* out, int nx, int ny, size_t nplanes, const cpx<T>* tw,
                         hipStream_t st, double* bsum = nullptr, bool stream_in = false,
                         const LayerSkip& skip = LayerSkip{}, FftChoice ch = FftChoice{});
-template <typename T>
-int x_r2c_blocks_per_plane(int nx, int ny, FftChoice ch = FftChoice{});
-// the most blocks per plane any choice gives (buffers sized for tuning)
-template <typename T>
-int x_r2c_max_blocks_per_plane(int nx, int ny);
+int x_r2c_sums_per_plane(int nx, int ny);
 // Column transforms between X[p][kx][y] (p < NP) and the mode-major
 // S[kx][ky][ldp] (record stride ldp >= NP; the padding is not touched).
 template <typename T>
@@ -127,8 +124,6 @@ hipError_t launch_xform_batch(int kind, XformBatch& b, hipStream_t st);
 // and returns the dynamic LDS bytes it needs (0 for an invalid table).
 template <typename T>
 size_t xform_batch_prepare(int kind, XformBatch& b);
-template <typename T>
-int x_r2c_batch_blocks_per_plane(int nx, int ny);
 
 // Per-mode depth pass.  Input spectra (unnormalised DFTs) in mode-major
 // layout in[mode][ld_in]: the plastic strain as [6][nz] at offset 0 (if
@@ -247,11 +242,20 @@ __host__ __device__ inline bool depth_light(const DepthParams& p) {
   return light && p.kxh * p.ny > 3072;
 }
 
-// Mean-mode (k = 0) fields in float64 from the block sums of the input
-// planes: out[plane] for every output plane (strain, stress, displacement,
-// surface u3 segments as in DepthParams).
-hipError_t launch_k0_fields(const double* wsum, int wblocks, const double* tsum, int tblocks, double* out,
-                            const DepthParams& p, hipStream_t st);
+// Mean-mode (k = 0) fields in float64 from the partial sums of the eigenstrain
+// and traction planes (nsum each): out[plane] for every output plane (strain,
+// stress, displacement, surface u3 segments as in DepthParams).
+hipError_t launch_k0_fields(const double* wsum, const double* tsum, int nsum, double* out, const DepthParams& p,
+                            hipStream_t st);
+
+// The same for every grid of a batched depth pass (dtab as launch_depth_batch
+// left it), in one launch: 8 float32 grids of 8 to 64 nodes 147 -> 118 us.
+struct K0Batch {
+  const double *wsum[DEPTH_BATCH_MAX], *tsum[DEPTH_BATCH_MAX];
+  int nsum[DEPTH_BATCH_MAX];
+  double* out[DEPTH_BATCH_MAX];
+};
+hipError_t launch_k0_batch(const DepthBatch& host, const DepthBatch* dtab, const K0Batch& k, hipStream_t st);
 
 // Pointwise kernels (float64).
 hipError_t launch_return_map(const double* d_eps, const double* sig_n, const double* ep_n, double* d_eps_p,

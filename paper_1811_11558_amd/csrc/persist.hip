@@ -31,7 +31,7 @@ __global__ __launch_bounds__(NT) void k_op_persistent(const OpBatch* __restrict_
   // a block's LDS tiles are used again by its next item: the barrier after each
   const XformBatch& x0 = t->x[0];
   for (int blk = b0; blk < x0.first[x0.n]; blk += G) {
-    x_r2c_batch_block<T>(x0, blk, red);
+    x_r2c_batch_block<T>(x0, blk);
     __syncthreads();
   }
   grid.sync();

@@ -119,42 +119,60 @@ __global__ __launch_bounds__(NT) void k_plastic_tangent(const double* __restrict
   for (int c = 0; c < 6; ++c) out[c * V + v] = b[c] - (dfac * d[c] + fac * dd[c]);
 }
 
-// Mean-mode fields in float64 (precision FP32_REFINED).  One thread per
-// depth node: sums the block partials of the 6 eigenstrain planes of that
-// node (and of the 3 traction planes) in a fixed order, forms the laterally
+// Mean-mode fields in float64 (precision FP32_REFINED).  G threads per depth
+// node: sum the partials of the 6 eigenstrain planes of that node (and of the 3
+// traction planes; nsum each) in a fixed order, form the laterally
 // uniform response (sigma . e3 = -t_mean, eps13 = (w13 - t1)/(2 mu),
 // eps23 = (w23 - t2)/(2 mu), eps33 = (w33 - t3)/(lambda + 2 mu), other
-// strains 0, displacement 0) and writes one constant per output plane.
-__global__ __launch_bounds__(NT) void k_k0_fields(const double* __restrict__ wsum, int wblocks,
-                                                 const double* __restrict__ tsum, int tblocks,
-                                                 double* __restrict__ out, DepthParams p) {
-  const int z = blockIdx.x * NT + threadIdx.x;
+// strains 0, displacement 0) and write one constant per output plane.  Bound by
+// the latency of the partials' loads: a thread per node, which reads them one after
+// the other, takes 14.6 us with 64 partials (64 x 1024 x 64), 64 threads 6.1.
+template <int G>
+__device__ __forceinline__ void k0_fields(const double* __restrict__ wsum, const double* __restrict__ tsum, int nsum,
+                                          double* __restrict__ out, const DepthParams& p, int z, int l) {
   const int nz = p.nz;
   if (z >= nz) return;
   const double inv = p.norm;                      // 1 / (nx ny)
   const double mu = p.mu, lam = p.kappa * p.mu;
+  const bool with_t = p.has_t && p.k0_include;
   double e[6] = {0, 0, 0, 0, 0, 0};
   double w[6] = {0, 0, 0, 0, 0, 0};
+  double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  for (int k = l; k < nsum; k += G) {
+    if (p.has_w) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) v[c] += wsum[((size_t)c * nz + z) * nsum + k];
+    }
+    if (with_t) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[6 + c] += tsum[(size_t)c * nsum + k];
+    }
+  }
+#pragma unroll
+  for (int o = (G < 64 ? G : 64) / 2; o > 0; o >>= 1) {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) v[c] += __shfl_xor(v[c], o, 64);
+  }
+  if constexpr (G > 64) {
+    __shared__ double sh[9][NT / 64];
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) sh[c][threadIdx.x >> 6] = v[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 9; ++c) v[c] = (sh[c][0] + sh[c][1]) + (sh[c][2] + sh[c][3]);
+  }
+  if (l != 0) return;
   if (p.has_w) {
     double ep[6];
-    for (int c = 0; c < 6; ++c) {
-      double s = 0.0;
-      const double* b = wsum + ((size_t)c * nz + z) * wblocks;
-      for (int k = 0; k < wblocks; ++k) s += b[k];
-      ep[c] = s * inv;
-    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) ep[c] = v[c] * inv;
     const double tr = ep[0] + ep[1] + ep[2];
+#pragma unroll
     for (int c = 0; c < 6; ++c) w[c] = 2.0 * mu * ep[c] + (c < 3 ? lam * tr : 0.0);
   }
-  double t[3] = {0, 0, 0};
-  if (p.has_t && p.k0_include) {
-    for (int c = 0; c < 3; ++c) {
-      double s = 0.0;
-      const double* b = tsum + (size_t)c * tblocks;
-      for (int k = 0; k < tblocks; ++k) s += b[k];
-      t[c] = s * inv;
-    }
-  }
+  const double t[3] = {v[6] * inv, v[7] * inv, v[8] * inv};
   e[4] = (w[4] - t[0]) / (2.0 * mu);
   e[3] = (w[3] - t[1]) / (2.0 * mu);
   e[2] = (w[2] - t[2]) / (lam + 2.0 * mu);
@@ -169,12 +187,38 @@ __global__ __launch_bounds__(NT) void k_k0_fields(const double* __restrict__ wsu
   if (p.off_u3 >= 0 && z == 0) out[p.off_u3] = 0.0;
 }
 
+template <int G>
+__global__ __launch_bounds__(NT) void k_k0_fields(const double* __restrict__ wsum, const double* __restrict__ tsum,
+                                                 int nsum, double* __restrict__ out, DepthParams p) {
+  k0_fields<G>(wsum, tsum, nsum, out, p, (blockIdx.x * NT + threadIdx.x) / G, threadIdx.x % G);
+}
+// The grids of a batched depth pass, a block per node.  (The lanes' sums are
+// combined in pairs, so with G at least nsum the result does not depend on G: these
+// are the bits of the single launch.)
+__global__ __launch_bounds__(NT) void k_k0_batch(const DepthBatch* __restrict__ b, K0Batch k) {
+  const int c = blockIdx.y;
+  k0_fields<NT>(k.wsum[c], k.tsum[c], k.nsum[c], k.out[c], b->prm[c], blockIdx.x, threadIdx.x);
+}
+
 }  // namespace
 
-hipError_t launch_k0_fields(const double* wsum, int wblocks, const double* tsum, int tblocks, double* out,
-                            const DepthParams& p, hipStream_t st) {
-  hipLaunchKernelGGL(k_k0_fields, dim3((p.nz + NT - 1) / NT), dim3(NT), 0, st, wsum, wblocks, tsum, tblocks, out,
-                     p);
+hipError_t launch_k0_fields(const double* wsum, const double* tsum, int nsum, double* out, const DepthParams& p,
+                            hipStream_t st) {
+#define CALL(G)                                                                                                    \
+  hipLaunchKernelGGL(k_k0_fields<G>, dim3((unsigned)(((size_t)p.nz * G + NT - 1) / NT)), dim3(NT), 0, st, wsum, tsum, \
+                     nsum, out, p)
+  if (nsum <= 1) CALL(1);
+  else if (nsum <= 4) CALL(4);
+  else if (nsum <= 16) CALL(16);
+  else if (nsum <= 64) CALL(64);
+  else CALL(256);
+#undef CALL
+  return hipGetLastError();
+}
+hipError_t launch_k0_batch(const DepthBatch& host, const DepthBatch* dtab, const K0Batch& k, hipStream_t st) {
+  int nz = 0;
+  for (int c = 0; c < host.n; ++c) nz = nz > host.prm[c].nz ? nz : host.prm[c].nz;
+  hipLaunchKernelGGL(k_k0_batch, dim3((unsigned)nz, (unsigned)host.n), dim3(NT), 0, st, dtab, k);
   return hipGetLastError();
 }
 

@@ -621,6 +621,7 @@ def test_batched_grids_run_in_their_own_depth_layout(shapes):
     [(16, 16, 7), (16, 16, 129), (16, 16, 64), (16, 8, 300), (8, 16, 256), (16, 16, 100)],
     [(1024, 4, 5), (16, 16, 40), (4, 1024, 40), (8, 8, 130), (1024, 8, 20)],
     [(1024, 8, 48), (8, 1024, 48)],
+    [(64, 64, 12), (128, 128, 6), (16, 512, 8), (256, 64, 5)],     # (several row blocks a plane)
     [(1024, 128, 12), (16, 16, 40), (1024, 128, 20)]])     # (spectra of the long ones over 256 MB)
 def test_batched_grids_have_the_bits_of_their_own_application(shapes, precision):
     """Any mix of depths and side lengths in a batch: every field is bitwise
