@@ -348,7 +348,7 @@ __device__ __forceinline__ void reg_fft(cpx<T> (&v)[V], int t0, L0 lds0, int t1,
 // Rows of nx = 2^LOGN reals -> half spectra.  Block = R consecutive rows of
 // one plane (R even, R | ny), two rows per complex sequence.  Output
 // X[(plane * kxh + k) * ny + y].
-// If bsum is not NULL, every wave also writes the float64 sum of its rows there
+// If bsum is not NULL (float32), every wave also writes the float64 sum of its rows there
 // (the plane means of the mean mode are then formed in float64): the waves of a
 // plane hold the same rows with every tile, so that the sums do not depend on it.
 template <typename T, int LOGN, bool NTL, int TILE, int RADIX>
@@ -365,13 +365,14 @@ __device__ __forceinline__ void x_r2c_body(char* tile, int lb, const InSegments&
   const size_t plane = row0 / ny;
   const int y0 = (int)(row0 - plane * ny);
   const int s = (int)threadIdx.x / M, t = (int)threadIdx.x % M, hp = R / 2;
+  constexpr bool SUMS = sizeof(T) == 4;  // (float64 has its mean mode in the depth pass)
   auto put_sum = [&](double v) {         // of the wave (one that holds rows)
     if ((threadIdx.x & 63) == 0 && s < hp)
       bsum[plane * row_sums(N, ny) + ((size_t)(y0 / 2) * M + threadIdx.x) / 64] = v;
   };
   // a layer without plastic strain: its rows sum to zero, nothing to transform
   if (skip.zact && (int)plane < skip.nw && (int)(plane % skip.nz) >= *skip.zact) {
-    if (bsum) put_sum(0.0);
+    if (SUMS && bsum) put_sum(0.0);
     return;
   }
   const int sg = (seg.n > 1 && (int)plane >= seg.first[1]) ? 1 : 0;
@@ -388,7 +389,7 @@ __device__ __forceinline__ void x_r2c_body(char* tile, int lb, const InSegments&
   cpx<T> v[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) v[e] = mk((T)a[e], (T)b[e]);
-  if (bsum) {
+  if (SUMS && bsum) {
     double acc = 0.0;
 #pragma unroll
     for (int e = 0; e < V; ++e) acc += a[e] + b[e];
