@@ -495,9 +495,12 @@ int fvim_set_timing(fvim_ctx* ctx, int on);
  * as ONE cooperative persistent launch whose blocks loop over every stage
  * with a grid barrier between stages; results are bitwise those of the
  * multi-launch batch, and other batches take the multi-launch path.
+ * FVIM_OPT_CONTACT_ITERS (1 .. 4096, default 256): the most iterations one
+ * launch runs where one workgroup iterates the contact (16 to 64 points a
+ * side); same results, bit for bit.
  */
 enum { FVIM_OPT_DEPTH_CONFIG = 1, FVIM_OPT_TUNE = 2, FVIM_OPT_GRAPHS = 3, FVIM_OPT_SIDE_STREAM = 4,
-       FVIM_OPT_STREAMING = 5, FVIM_OPT_FFT_CONFIG = 6, FVIM_OPT_PERSISTENT = 7 };
+       FVIM_OPT_STREAMING = 5, FVIM_OPT_FFT_CONFIG = 6, FVIM_OPT_PERSISTENT = 7, FVIM_OPT_CONTACT_ITERS = 8 };
 int fvim_set_option(fvim_ctx* ctx, int key, int value);
 int fvim_get_option(fvim_ctx* ctx, int key, int* value);
 int fvim_stage_times(fvim_ctx* ctx, double* ms, int* count);

@@ -897,6 +897,10 @@ int fvim_set_option(fvim_ctx* c, int key, int value) {
     case FVIM_OPT_PERSISTENT:
       c->persistent = value ? 1 : 0;
       return FVIM_OK;
+    case FVIM_OPT_CONTACT_ITERS:
+      if (value < 1 || value > 4096) return fail(FVIM_EINVAL, "contact iterations per launch: 1 to 4096");
+      c->contact_iters = value;
+      return FVIM_OK;
     case FVIM_OPT_FFT_CONFIG: {
       if (value < 0 || value >= (1 << 12)) return fail(FVIM_EINVAL, "fft config: 12 bits");
       const int prec = c->precision == FVIM_FP32_REFINED ? 1 : 0;
@@ -935,6 +939,9 @@ int fvim_get_option(fvim_ctx* c, int key, int* value) {
       return FVIM_OK;
     case FVIM_OPT_PERSISTENT:
       *value = c->persistent;
+      return FVIM_OK;
+    case FVIM_OPT_CONTACT_ITERS:
+      *value = c->contact_iters;
       return FVIM_OK;
     case FVIM_OPT_FFT_CONFIG:
       *value = fft_pack(c, c->precision == FVIM_FP32_REFINED ? 1 : 0);

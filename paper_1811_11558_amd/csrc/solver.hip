@@ -646,8 +646,6 @@ static int compliance(fvim_ctx* c, const double* p, double* u, hipStream_t st) {
 
 // Contact iterations between two reads of the convergence measure.
 static int pk_check_period(size_t n) { return n <= 4096 ? 1 : 4; }
-// and most iterations of a one-workgroup launch (a few ms)
-constexpr int PK_SOLO_ITERS = 256;
 
 // The iterations up to the next check and their convergence measure, as a
 // fixed sequence of launches on st (no host dependency: every scalar lives in
@@ -734,7 +732,7 @@ int pk_solve(fvim_ctx* c, const double* h, double W, double tol, int max_iter, d
   }
   // (solo: the first launch also forms the gap, so there is one at max_iter = 0 too)
   for (bool first = true; it < max_iter || (solo && first); first = false) {
-    const int count = std::max(std::min(solo ? PK_SOLO_ITERS : check, max_iter - it), 0);
+    const int count = std::max(std::min(solo ? c->contact_iters : check, max_iter - it), 0);
     if (solo) {
       if ((e = launch_pk_solo(pk, count, tol, first, it + count >= max_iter, st)) != hipSuccess)
         return fail_hip(e, "contact iteration");

@@ -62,6 +62,7 @@ struct fvim_ctx {
   int force_fp64 = 0;
   // replay the contact iteration as a captured HIP graph
   int use_graphs = 1;
+  int contact_iters = 256;      // FVIM_OPT_CONTACT_ITERS (a few ms of one launch)
   int tune_pending = 0;
   // stage timing: pairs of events per launch, tagged by stage
   int timing = 0;

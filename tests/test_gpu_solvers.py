@@ -112,6 +112,62 @@ def test_contact_of_one_workgroup_matches_oracle(nx, ny):
     ctx.close()
 
 
+def _rough_case(nx, ny):
+    ly = ny / nx
+    h = rough_surface(nx, ny, hurst=0.8, k_roll=1, k_cut=max(1, max(nx, ny) // 4), rms_slope=0.1, seed=nx + 3 * ny,
+                      ly=ly)
+    return grid_dict(nx, ny, 2, 1.0, ly), torch.from_numpy(h).cuda(), 0.02 * ly
+
+
+def _stopped(ctx, h, W, max_iter):
+    """Pressure after max_iter iterations, well before convergence."""
+    p = torch.zeros_like(h)
+    with pytest.raises(RuntimeError, match="iteration limit"):
+        ctx.contact_solve(h, W, tol=1e-300, max_iter=max_iter, p=p)
+    torch.cuda.synchronize()
+    return p
+
+
+@pytest.mark.parametrize("nx,ny", [(16, 16), (32, 64), (64, 64)])
+def test_contact_of_one_workgroup_resumes_where_a_launch_ended(nx, ny):
+    """Launches of 1, 3 and 7 iterations against one of them all: the same
+    bits, part of the way (where a lost direction, restart flag or gap shows)
+    and at convergence."""
+    g, h, W = _rough_case(nx, ny)
+    ctx = _ctx(g)
+    out = {}
+    for n in (256, 1, 3, 7):
+        ctx.set_option(ctx.OPT_CONTACT_ITERS, n)
+        parts = [_stopped(ctx, h, W, k) for k in (2, 3, 8, 20)]
+        p, gap, info = ctx.contact_solve(h, W, tol=1e-10, max_iter=20000, want_gap=True)
+        torch.cuda.synchronize()
+        out[n] = (*parts, p, gap)
+        _say("one workgroup", (nx, ny), "iterations a launch", n, info)
+        assert info["iters"] == out.setdefault("iters", info["iters"]) and info["iters"] > 20
+        assert all(torch.equal(a, b) for a, b in zip(out[n], out[256])), n
+    assert not any(torch.equal(a, out[256][-2]) for a in out[256][:4])
+    for bad in (0, -1, 4097):
+        with pytest.raises(RuntimeError):
+            ctx.set_option(ctx.OPT_CONTACT_ITERS, bad)
+    ctx.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(128, 128), (128, 16), (8, 8)])
+def test_contact_iteration_limit_between_two_checks(nx, ny):
+    """A limit that is no multiple of the iterations between two checks, with
+    and without the captured graph: the same bits."""
+    g, h, W = _rough_case(nx, ny)
+    ctx = _ctx(g)
+    for k in (1, 3, 5, 6, 8, 11):
+        got = []
+        for graphs in (1, 0):
+            ctx.set_option(ctx.OPT_GRAPHS, graphs)
+            got.append(_stopped(ctx, h, W, k))
+        _say("limit", (nx, ny), k, float(got[0].sum()))
+        assert torch.equal(*got), k
+    ctx.close()
+
+
 def test_contact_matches_oracle_rough_1024():
     """The rough-surface workload's contact solve at its full size: 1024^2,
     Hurst 0.8, PSD plateau for 1 <= |k| < 4, cut-off |k| = 256, rms slope
