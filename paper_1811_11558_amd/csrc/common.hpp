@@ -84,6 +84,28 @@ __device__ __forceinline__ cpx<T> mul_mi(cpx<T> a) { return mk(a.y, -a.x); }
 template <typename T>
 __device__ __forceinline__ cpx<T> zero() { return mk(T(0), T(0)); }
 
+// Logical block index such that the blocks dispatched to one XCD (physical
+// blocks b, b + 8, b + 16, ...) take consecutive logical indices.
+__device__ __forceinline__ int xcd_block() {
+  const int b = blockIdx.x, n = gridDim.x;
+  const int x = b & 7, slot = b >> 3, per = n >> 3, rem = n & 7;
+  return x * per + (x < rem ? x : rem) + slot;
+}
+
+// Radix-4 butterfly of the DFT with kernel exp(-2 pi i / 4) (its conjugate for
+// INV), in place on a[0 .. 4).
+template <bool INV, typename T>
+__device__ __forceinline__ void butterfly4(cpx<T>* a) {
+  const cpx<T> s02 = add(a[0], a[2]), d02 = sub(a[0], a[2]);
+  const cpx<T> s13 = add(a[1], a[3]), d13 = sub(a[1], a[3]);
+  // forward: y1 = d02 - i d13, y3 = d02 + i d13 (conjugate for inverse)
+  const cpx<T> id13 = INV ? mul_i(d13) : mul_mi(d13);
+  a[0] = add(s02, s13);
+  a[1] = add(d02, id13);
+  a[2] = sub(s02, s13);
+  a[3] = sub(d02, id13);
+}
+
 // Launch helpers defined in the individual translation units.  All take the
 // stream explicitly and return hipError_t of the launch.
 struct FftPlan1D {

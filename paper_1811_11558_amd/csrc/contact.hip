@@ -13,7 +13,10 @@
 //   gap      rows transformed back to u = M[p]; p renormalised, g = u - h;
 //            sum |p - p_old|, and the sums for the next dir
 // Every global sum is one kernel boundary: its block sums are totalled, in one
-// fixed order, by each block of the next kernel that needs them.  The two
+// fixed order, by each block of the next kernel that needs them.  (Where two
+// kernels take the same total, the load scale of columns and gap, blocks of other
+// sizes, nx != ny, may add it in another order: p and u then differ in their scale's
+// last bit.)  The two
 // centred sums, sum (g - mean)^2 and sum (r - mean r) t, take no pass of their
 // own either: a block centres its values on its own means and the blocks'
 // moments are combined about the total mean,
@@ -157,7 +160,7 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_columns(cpx<double>* __rest
   __shared__ double sh[2 * S::NW];
   const int kxh = nx / 2 + 1;
   const int b = threadIdx.x / S::M, jj = threadIdx.x & (S::M - 1);
-  const int kx = surf_xcd_block() * S::SEQ + b;
+  const int kx = xcd_block() * S::SEQ + b;
   const bool on = kx < kxh;
   SurfTw<LOGN> t;
   cpx<double> v[1][4];
@@ -484,7 +487,7 @@ __global__ __launch_bounds__(GT) void k_pk_err(const double* __restrict__ part, 
 // barriers (about 45 per iteration) and, at 64 x 64, by one CU's LDS.  us per
 // iteration of a solve to 1e-12, launches with a test on the host after each
 // iteration -> one workgroup: 16^2 39.5 -> 6.2, 64 x 16 40.5 -> 8.9, 32^2 41.0 -> 10.9,
-// 64^2 42.2 -> 20.9.  (128^2 does not fit the LDS; its launches take 28.6.)
+// 64^2 42.2 -> 20.9.  (128^2 does not fit the LDS; its launches take 28.2.)
 template <int LX, int LY>
 struct Solo {
   static constexpr int NX = 1 << LX, NY = 1 << LY, KXH = NX / 2 + 1;
@@ -776,7 +779,8 @@ hipError_t launch_pk_iteration(const PkBufs& b, hipStream_t st) {
   return hipGetLastError();
 }
 
-// 16: the threads of a shorter side would not fill a wave; 64: see k_pk_solo
+// 16: the threads of a shorter side would not fill a wave; 64: see k_pk_solo.  (Longer
+// sides of as few points, 128 x 16, would fit too: not built, six launches.)
 bool pk_solo_fits(int nx, int ny) { return nx >= 16 && nx <= 64 && ny >= 16 && ny <= 64; }
 
 hipError_t launch_pk_solo(const PkBufs& b, int count, double tol, bool first, bool last, hipStream_t st) {

@@ -141,7 +141,7 @@ hipError_t launch_two(const cpx<T>* in, cpx<T>* out, const DepthParams& p, hipSt
   }
   if (part != 1) {
     if (p.rep_out) {
-      if (!mean_in_pass<T>())
+      if constexpr (!mean_in_pass<T>())
         hipLaunchKernelGGL(k_nyq_average<T>, dim3((unsigned)nnyq), dim3(NT), 0, st, out,
                            static_cast<const cpx<T>*>(p.rep_out), p.nx, p.ny, p.kxh, p.ld_out, p.np_out);
     } else {

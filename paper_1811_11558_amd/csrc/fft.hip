@@ -19,7 +19,8 @@
 // The tile (runs of half, default or twice the default length on the strided
 // side) and the radix are choices of each launch (FftChoice), timed by the context's tuner for
 // lengths 2^5 .. 2^10; other lengths use the default.  Kernels over several
-// grids (XformBatch) run the default choice of each grid's length.
+// grids (XformBatch) have blocks of NT threads: rows in a tile of that size, columns
+// in the default tile or half of it, radix 4.
 #include <algorithm>
 
 #include "common.hpp"
@@ -285,8 +286,8 @@ int x_c2r_max_blocks(int nx, int ny, size_t nplanes) {
 // ------------------------------------------------- launches over grids
 namespace {
 
-// block count and LDS bytes of one grid's part of a batched launch (the
-// default tile), and its rows per block (row kernels)
+// block count and LDS bytes of one grid's part of a batched launch, and its rows
+// per block (row kernels)
 template <typename T>
 struct BatchGeom {
   int blocks = 0, R = 0;

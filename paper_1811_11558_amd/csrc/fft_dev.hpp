@@ -143,14 +143,7 @@ __device__ __forceinline__ void butterfly(cpx<T>* a) {
     a[0] = add(a0, a1);
     a[1] = sub(a0, a1);
   } else if constexpr (R == 4) {
-    const cpx<T> s02 = add(a[0], a[2]), d02 = sub(a[0], a[2]);
-    const cpx<T> s13 = add(a[1], a[3]), d13 = sub(a[1], a[3]);
-    // forward: y1 = d02 - i d13, y3 = d02 + i d13 (conjugate for inverse)
-    const cpx<T> id13 = INV ? mul_i(d13) : mul_mi(d13);
-    a[0] = add(s02, s13);
-    a[1] = add(d02, id13);
-    a[2] = sub(s02, s13);
-    a[3] = sub(d02, id13);
+    butterfly4<INV>(a);
   } else {
     static_assert(R == 8, "radix 2, 4 or 8");
     // two length-4 transforms (even and odd inputs), then the odd ones
@@ -446,14 +439,6 @@ __device__ __forceinline__ void x_r2c_body(char* tile, int lb, const InSegments&
   }
 }
 
-// Logical block index such that the blocks dispatched to one XCD (physical
-// blocks b, b + 8, b + 16, ...) take consecutive logical indices.
-__device__ __forceinline__ int xcd_block() {
-  const int b = blockIdx.x, n = gridDim.x;
-  const int x = b & 7, slot = b >> 3, per = n >> 3, rem = n & 7;
-  return x * per + (x < rem ? x : rem) + slot;
-}
-
 // Threads of a column tile in two orders: y fastest (t consecutive, for the
 // X side, contiguous in y) and plane fastest (b consecutive, for the mode-major
 // side, runs of B planes).  The exchange tile [pos][b] has the planes of each
@@ -679,7 +664,8 @@ __device__ __forceinline__ void x_c2r_body(char* tile, double* red, int lb, cons
 
 // --------------------------------------------- kernels over several grids
 // One launch serves the grids of an XformBatch (transform lengths up to
-// 2^XFORM_BATCH_MAX_LOGN, default tile and radix 4): block b belongs to grid
+// 2^XFORM_BATCH_MAX_LOGN; rows in blocks of NT threads, columns in the default tile or,
+// where it takes more, half of it; radix 4): block b belongs to grid
 // c with first[c] <= b < first[c + 1] and runs that grid's body with the
 // block index b - first[c]; the tile lives in dynamic LDS sized by the host
 // for the largest grid.  A grid's results are those of its own launch.

@@ -25,8 +25,8 @@
 // A row transform carries the two components of one row as one complex
 // sequence.  Block sums are totalled, in one fixed order, by each block of the
 // kernel that uses them.  The separate form (a 5-launch compliance, 7 more
-// launches) was bound by launch latency: 61 us per iteration at 512^2 against
-// 32 us (a solve of some 2000 iterations 136 -> 70 ms).
+// launches) was bound by launch latency: a solve at 512^2 132 ms against 75 (38 us
+// per iteration).
 // The host reads the change measure dA sum |q_new - q| / (mu_f W) every few
 // iterations.
 //
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(Surf<LOGN>::NTH) void k_f_columns(cpx<double>* __re
   __shared__ cpx<double> buf[(STEP ? 4 : 2) * S::TILE];
   const int kxh = nx / 2 + 1;
   const int b = threadIdx.x / S::M, jj = threadIdx.x & (S::M - 1);
-  const int kx = surf_xcd_block() * S::SEQ + b;
+  const int kx = xcd_block() * S::SEQ + b;
   const bool on = kx < kxh;
   const size_t plane = (size_t)S::N * kxh;
   SurfTw<LOGN> t;

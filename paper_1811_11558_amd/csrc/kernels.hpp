@@ -94,8 +94,8 @@ template <typename T>
 int x_c2r_max_blocks(int nx, int ny, size_t nplanes);
 
 // One launch of a transform kernel over several grids (up to
-// XFORM_BATCH_MAX, lengths up to 2^XFORM_BATCH_MAX_LOGN), each with the
-// default choice of its length: the grids' parameters travel as the kernel
+// XFORM_BATCH_MAX, lengths up to 2^XFORM_BATCH_MAX_LOGN), in blocks of one size
+// and radix 4: the grids' parameters travel as the kernel
 // argument.  logn: log2 of the kernel's transform length (nx for the row
 // kernels, ny for the column kernels); NP: planes (row kernels: planes of
 // ny rows; column kernels: planes NP with record stride ldp); R and first

@@ -620,19 +620,18 @@ size_t solver_footprint(const fvim_grid* g, size_t V) {
 // Host copy of device scalars [first, first + n) (synchronises the stream).
 // The slots kernels mirror (S_ERR, S_DOT0..S_DOT2) are taken from the
 // mapped mirror once the stream is idle; others are copied.
-static int read_scalars_on(fvim_ctx* c, hipStream_t st, int first, int n) {
+static int read_scalars(fvim_ctx* c, int first, int n) {
   SolverWork* w = c->sw;
   const bool mirrored = (first == S_ERR && n == 1) || (first >= S_DOT0 && first + n <= S_DOT2 + 1);
   hipError_t e = hipSuccess;
-  if (!mirrored) e = hipMemcpyAsync(w->hsc + first, w->sc + first, sizeof(double) * n, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (!mirrored)
+    e = hipMemcpyAsync(w->hsc + first, w->sc + first, sizeof(double) * n, hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return fail_hip(e, "scalar readback");
   if (mirrored)
     for (int k = first; k < first + n; ++k) w->hsc[k] = w->hmap[k];
   return FVIM_OK;
 }
-
-static int read_scalars(fvim_ctx* c, int first, int n) { return read_scalars_on(c, c->stream, first, n); }
 
 static double contact_modulus(const fvim_ctx* c) { return c->mat.E / (1.0 - c->mat.nu * c->mat.nu); }
 
@@ -1860,7 +1859,7 @@ int elastoplastic_solve(fvim_ctx* c, const double* h, const double* W_steps, int
   SolverWork* w = c->sw;
   hipStream_t st = c->stream;
   const size_t n = w->ns, V = w->V;
-  // surface work arrays (after the 5 used by the contact solver)
+  // surface work arrays (after the 3 used by the contact solver)
   double* H0 = w->surf + 3 * n;
   double* H = w->surf + 4 * n;
   double* dUp = w->surf + 5 * n;

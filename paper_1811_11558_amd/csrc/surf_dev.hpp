@@ -60,17 +60,6 @@ __device__ __forceinline__ void surf_load_tw(const cpx<double>* __restrict__ tw,
   }
 }
 
-template <bool INV>
-__device__ __forceinline__ void surf_butterfly4(cpx<double>* a) {
-  const cpx<double> s02 = add(a[0], a[2]), d02 = sub(a[0], a[2]);
-  const cpx<double> s13 = add(a[1], a[3]), d13 = sub(a[1], a[3]);
-  const cpx<double> id13 = INV ? mul_i(d13) : mul_mi(d13);
-  a[0] = add(s02, s13);
-  a[1] = add(d02, id13);
-  a[2] = sub(s02, s13);
-  a[3] = sub(d02, id13);
-}
-
 // Stockham transform (radix 4, one radix-2 stage first when LOGN is odd) of
 // the block's sequences, NPL of them per thread (PL planes in step): on entry
 // v[q][m] is element jj + m M of the thread's sequence of plane q, on return
@@ -86,7 +75,7 @@ __device__ __forceinline__ void surf_fft(cpx<double> (&v)[NPL][4], cpx<double>* 
   for (int q = 0; q < NPL; ++q) {
     cpx<double>* a = v[q];
     if constexpr (S::L0 == 2) {
-      surf_butterfly4<INV>(a);
+      butterfly4<INV>(a);
       if constexpr (S::NST > 0) {
         cpx<double>* d = buf + (2 * q + cur) * S::TILE + b * S::LD + 4 * jj;
 #pragma unroll
@@ -116,7 +105,7 @@ __device__ __forceinline__ void surf_fft(cpx<double> (&v)[NPL][4], cpx<double>* 
         const cpx<double> w = t.w[s][m - 1];
         a[m] = INV ? mulc(src[m * S::M], w) : mul(src[m * S::M], w);
       }
-      surf_butterfly4<INV>(a);
+      butterfly4<INV>(a);
       if (s + 1 < S::NST) {
         cpx<double>* d = buf + (2 * q + (cur ^ 1)) * S::TILE + b * S::LD + ((jj >> ls) << (ls + 2)) + k;
 #pragma unroll
@@ -135,14 +124,6 @@ __device__ constexpr int surf_last(int first) {
   // NST tiles are written in turn from `first` (none when NST = 0 and the
   // first stage is the only one)
   return S::NST > 0 ? (first + S::NST - 1) & 1 : first ^ (S::L0 == 2 ? 1 : 0);
-}
-
-// Logical block index such that the blocks dispatched to one XCD (physical
-// blocks b, b + 8, b + 16, ...) take consecutive logical indices.
-__device__ __forceinline__ int surf_xcd_block() {
-  const int b = blockIdx.x, n = gridDim.x;
-  const int x = b & 7, slot = b >> 3, per = n >> 3, rem = n & 7;
-  return x * per + (x < rem ? x : rem) + slot;
 }
 
 // Half spectra of the two real rows packed in the thread's sequence (v on
@@ -238,7 +219,8 @@ __device__ __forceinline__ void surf_sums(const double (&v)[K], double* sh, doub
 // Totals of K quantities over the nb blocks of an earlier kernel, formed by
 // every block of the kernel that uses them (a launch of its own would cost
 // more than the sums); f(i, s) adds block i's share to s[0 .. K).  Fixed order:
-// every block gets the same bits.
+// every block gets the same bits (of one kernel: another wave count adds in another
+// order).
 template <int K, int NW, typename F>
 __device__ __forceinline__ void surf_totals(int nb, double* sh, double (&out)[K], F f) {
   double s[K];
