@@ -475,8 +475,9 @@ NOALLOC_BYTES = 128 << 20
 
 
 def operator_apply_batch(ctxs, eps_p=None, traction=None, want=("strain",)):
-    """The fused operator for several contexts (grids may differ) with the
-    depth pass of up to 8 of them in one launch; ordered on ctxs[0]'s stream.
+    """The fused operator for several contexts (grids may differ) with shared
+    launches: each transform stage of those with sides up to 512, and the depth
+    pass of up to 8 of at most 128 (256, more) nodes; ordered on ctxs[0]'s stream.
     eps_p / traction: lists of tensors (one per context) or None.  Returns a
     list of output dicts."""
     n = len(ctxs)
